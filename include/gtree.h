@@ -151,7 +151,10 @@ uint64_t tree_arena_bytes(const gt_params* p /*host*/, uint64_t n, uint64_t leaf
  * leaves are chained in key order.  n = 0 builds an empty tree.
  * This call synchronises `stream` before it returns.  On success *out
  * receives a new handle; GT_ERR_DEVICE if the device sort of the keys
- * failed (a bounded wait between its workgroups gave up: not expected).
+ * failed (the keys changed while they were sorted, or, above 2^26 keys, a
+ * bounded wait between its workgroups gave up: not expected).  On an error the
+ * arena's contents are unspecified (the keys are sorted inside it where they
+ * fit).
  */
 gt_status tree_build(const gt_params* p /*host*/, const void* keys, const void* values, uint64_t n,
                      void* arena, uint64_t arena_bytes, hipStream_t stream, gt_tree** out /*host*/);
@@ -186,7 +189,7 @@ gt_status tree_lookup_batch(gt_tree* t, const void* keys, uint64_t B, void* valu
  * flags or B too large; GT_ERR_CAPACITY when workspace_bytes is too small.
  * Nothing is enqueued on an error.  No memory is allocated; the call is
  * graph-capturable.  Should the device sort of a batch above 2048 keys fail
- * (a bounded wait between its workgroups gives up: not expected) the tree's
+ * (the keys changed while they were sorted: not expected) the tree's
  * device error word gets the internal bit (tree_device_error: GT_ERR_DEVICE)
  * and the results are not valid.
  */
@@ -232,7 +235,7 @@ gt_status tree_lookup_levelwise_noalloc(gt_tree* t, const void* keys, uint64_t B
  * GT_DEVERR_CAPACITY, the tree is left unchanged and status_out is
  * unspecified.  A batch is not applied either while the word holds
  * GT_DEVERR_INTERNAL (set, for one, when the device sort of a batch above
- * 2048 keys gives up a bounded wait between its workgroups: not expected);
+ * 2048 keys fails because the keys changed meanwhile: not expected);
  * tree_device_error clears the word.
  */
 gt_status tree_insert_batch(gt_tree* t, const void* keys, const void* values, uint64_t B,

@@ -108,7 +108,7 @@ template <class T>
 void scan_exclusive(const T* in, T* out, T* total, const uint32_t* n_dev, uint64_t n_max,
                     void* tmp, hipStream_t s);
 
-// Scratch bytes needed by sort_pairs for n elements.
+// Scratch bytes needed by sort_pairs and sort_from for n elements.
 uint64_t sort_tmp_bytes(uint64_t n, int key_bytes);
 
 // Stable sort of (keys[i], idx[i]) by key, n host-known.  keys_alt/idx_alt
@@ -120,11 +120,25 @@ template <class K>
 void sort_pairs(K* keys, uint32_t* idx, K* keys_alt, uint32_t* idx_alt, uint64_t n, void* tmp,
                 hipStream_t s, uint32_t* err = nullptr, uint32_t err_bit = 1u);
 
-// The same sort of (src[i], i): src is read, keys/idx receive the result,
-// keys_alt/idx_alt are ping-pong buffers.  Saves staging the pairs.
+// The same sort of (src[i], i), n > 2048: src is read, keys/idx receive the
+// result, keys_alt/idx_alt are ping-pong buffers.
 template <class K>
 void sort_from(const K* src, K* keys, uint32_t* idx, K* keys_alt, uint32_t* idx_alt, uint64_t n, void* tmp,
                hipStream_t s, uint32_t* err = nullptr, uint32_t err_bit = 1u);
+
+// The sample sort (sample_sort.hip), which sort_from takes up to
+// sample_sort_max() elements: a stable sort of (src[i], i) as sort_from
+// describes it; tmp holds sample_sort_tmp_bytes, which from 2049 elements on
+// (the callers' smallest) is less than sort_tmp_bytes.  force_fail makes it report a
+// failure (testing hook).
+uint64_t sample_sort_max();
+uint64_t sample_sort_tmp_bytes(uint64_t n, int key_bytes);
+template <class K>
+void sample_sort_from(const K* src, K* keys, uint32_t* idx, K* keys_alt, uint32_t* idx_alt, uint64_t n, void* tmp,
+                      hipStream_t s, uint32_t* err, uint32_t err_bit, bool force_fail);
+
+// Whether the testing hook makes a sort of n elements fail.
+bool sort_forced_to_fail(uint64_t n);
 
 // Empty look-back steps after which a sort gives up (process-wide; 0 makes
 // every tile after the first give up at once).  Returns the previous value.
