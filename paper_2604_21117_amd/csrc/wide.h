@@ -6,17 +6,20 @@
 //
 // Layout in the caller's arena (256-byte aligned regions):
 //   WideHeader                     root, height, key count, node counts
-//   ikeys[inner][kw][m]            word-sliced 8-byte words: word w of
-//                                  entry i (w = 0 most significant; a
-//                                  32-byte key's words as big-endian
-//                                  numbers).  Entry i < c-1: the largest key
+//   ikeys[inner][kw][m]            word-sliced 8-byte words.  A node's
+//                                  deciding word w is the first word (0 =
+//                                  most significant; a 32-byte key's words as
+//                                  big-endian numbers) in which the keys
+//                                  below the node differ.  Slice 0 holds word
+//                                  w of the m entries, the other words follow
+//                                  in order.  Entry i < c-1: the largest key
 //                                  below child i; entries from c-1 on: the
 //                                  largest key value (all bytes 0xFF)
-//   imeta[inner]                   {first child, children, tie mask (2 x
-//                                  32 bits, low first)}: a bulk-loaded
+//   imeta[inner]                   {first child, children | w << 8, tie mask
+//                                  (2 x 32 bits, low first)}: a bulk-loaded
 //                                  node's children are consecutive ids of
 //                                  the level below; bit i of the mask: entry
-//                                  i's leading word equals that of the next
+//                                  i's deciding word equals that of the next
 //                                  key in key order (the first key of child
 //                                  i+1).  One 16-byte record per node, read
 //                                  in one load
@@ -24,9 +27,10 @@
 //     paper's k_max = m - 1), slots from count on repeating the last key;
 //     lvals[leaves][m] 8-byte values, all ones from count on
 //   leaves of 32-byte keys (lkeys only, 40 bytes per entry): per leaf the
-//     m leading words, then m 32-byte records {words 1..3, value}, words as
+//     m entries' deciding words (the parent's w; 0 without a parent), then m
+//     32-byte records {the other three words in order, value}, words as
 //     big-endian numbers; the same ordering and padding
-//   lmeta[leaves]                  {count, next leaf}
+//   lmeta[leaves]                  {count | w << 8, next leaf}
 // A key is kb = 8 * kw bytes: kw = 1 holds an 8-byte unsigned integer in
 // native (little-endian) order, compared as an integer; kw = 4 holds the
 // caller's 32 bytes as given, compared as a byte string.  Inner ids number

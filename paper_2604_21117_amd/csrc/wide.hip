@@ -7,14 +7,20 @@
 // cascading priority comparison resolves its 32 per-byte comparators), and
 // the group's ballot of "entry < query" counted by popcount is the priority
 // encoder: the child is the first one whose entry is >= the query.  Inner
-// entries are stored word-sliced, so a level first reads only the leading
-// words and goes on to a further word only for entries that tie the query
+// entries are stored word-sliced, so a level first reads only one word of
+// each and goes on to a further word only for entries that tie the query
 // (and, for exact-match lookups, only where the node's tie mask says the
-// tie does not decide).  The node's child range comes from one 16-byte
-// record read in the same round as the leading words, so a level costs one
+// tie does not decide).  That word is the node's deciding word, the first in
+// which its keys differ: keys with a common prefix (2^20 lookups on 10 M keys
+// behind 256 stems of 16 bytes) took 291 / 592 / 1001 us at orders 16 / 32 / 64
+// by the leading word, which all of a node's entries tie, and take 135 / 157 /
+// 260 by the deciding one (keys without a common prefix 99 / 129 / 195 before
+// and 99 / 111 / 160 now, the lanes' counts added with DPP moves where a ballot
+// per entry stood).  The node's child range comes from one 16-byte
+// record read in the same round as the deciding words, so a level costs one
 // dependent round unless an entry ties.  At the leaf each lane compares its
 // key for equality; small batches read every entry's key and value in one
-// round, large ones read the leading words first and only the lanes that
+// round, large ones read the deciding words first and only the lanes that
 // tie read the rest of their entry and its value.  Large batches also give
 // a query fewer lanes (8 or 16, each holding several entries), so that more
 // queries are in flight per wave.  The first matching lane
@@ -23,8 +29,8 @@
 // leaves (Section III).
 //
 // Build (Section V-B's one-time build, done on the device): the keys are
-// sorted (8-byte keys by the library's radix sort; 32-byte keys by four
-// stable radix sorts of one 64-bit word each, least significant word first,
+// sorted (8-byte keys by the library's sort; 32-byte keys by four
+// stable sorts of one 64-bit word each, least significant word first,
 // each pass reordering the permutation the previous ones produced), checked
 // for duplicates, packed evenly into leaves of at most m - 1 keys, and the
 // inner levels are packed bottom-up with at most m and (below the root) at
@@ -54,6 +60,12 @@ constexpr uint64_t kWTwoRound = 1u << 13;
 // 2^20 queries, 8 lanes for orders 16 and 32, 16 for order 64
 template <int M>
 constexpr int large_lanes() { return M == 64 ? 16 : 8; }
+
+// ... and from this size on, with 8-byte keys, two queries per lane group at
+// once (2^20 queries on 10 M keys, us, one and two: order 32 81.4 / 80.0, order
+// 64 118.9 / 117.7; at 2^16 two leave CUs without waves, 10.3 / 11.3).  With
+// 32-byte keys two queries' words cost wave slots: order 32 111 / 117.
+constexpr uint64_t kWTwoQueries = 1u << 18;
 
 // ---------------------------------------------------------------- keys
 
@@ -132,57 +144,110 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
 
 // ------------------------------------------------------------- search
 
+// A node's deciding word w is the first word in which the keys below it
+// differ (keys with a common prefix agree in all words before it).  An inner
+// node's entries are word-sliced: slice 0 is word w (as a big-endian number)
+// of its m entries in m consecutive 8-byte words, the other words follow in
+// order (word x > w is slice x), so a level reads its deciding words alone
+// (one 128-byte line at m = 16) whatever prefix the keys share.
+
+// word x of a key, x the same for the lanes of a group (with masks: a select
+// of two array elements would become an indexed read, and the key's array a
+// memory object)
+template <int KW>
+__device__ __forceinline__ uint64_t word_of(const uint64_t (&k)[KW], uint32_t x) {
+    if constexpr (KW == 1) return k[0];
+    uint64_t r = 0;
+#pragma unroll
+    for (int i = 0; i < KW; ++i) r |= k[i] & (x == static_cast<uint32_t>(i) ? ~0ull : 0ull);
+    return r;
+}
+
+// slice of word x in a node whose deciding word is w
+__device__ __forceinline__ uint32_t slice_of(uint32_t x, uint32_t w) { return x == w ? 0u : (x < w ? x + 1u : x); }
+
+// The fields of a node's record: children, deciding word, tie mask.
+__device__ __forceinline__ uint32_t meta_word(const uint4& m) { return m.y >> 8; }
+__device__ __forceinline__ uint64_t meta_ties(const uint4& m) { return static_cast<uint64_t>(m.w) << 32 | m.z; }
+
+// Whether entry `slot` of node `ref`, whose deciding word ties the query's,
+// lies below the query by the words behind it.  (A present key agrees with
+// the node's common prefix; where an absent one goes does not matter, since
+// the leaf compares whole keys.)
+template <int KW, int M>
+__device__ __forceinline__ bool tie_less(const uint64_t* ik, uint32_t ref, uint32_t slot, uint32_t w,
+                                         const uint64_t (&key)[KW]) {
+    uint64_t e[KW];
+#pragma unroll
+    for (int x = 1; x < KW; ++x)
+        e[x] = static_cast<uint32_t>(x) > w ? ik[(static_cast<uint64_t>(ref) * KW + x) * M + slot] : 0ull;
+    bool l = false;
+#pragma unroll
+    for (int x = KW - 1; x >= 1; --x)
+        if (static_cast<uint32_t>(x) > w) l = (e[x] < key[x]) || (e[x] == key[x] && l);
+    return l;
+}
+
 // Descend from the root to the leaf whose key range holds `key` (the first
-// child whose entry is >= key at every level).  Every lane of the group
-// takes part; `ref` ends as a leaf id.
-// An inner node's entries are word-sliced: word w (0 = most significant,
-// as a big-endian number) of its m entries sits in m consecutive 8-byte
-// words, so a level reads the leading words alone (one 128-byte line at
-// m = 16).  A lane whose leading word ties the query's goes on to the
-// entry's other words (read together, one more round) -- the cascade of the
-// paper's priority comparison, taken through memory -- unless the tie
+// child whose entry is >= key at every level), one lane per entry.  Every
+// lane of the group takes part; the result is a leaf id, lw its deciding word
+// (that of its parent).  A lane whose word ties the query's goes on to the
+// entry's words behind it (read together, one more round) -- the cascade of
+// the paper's priority comparison, taken through memory -- unless the tie
 // already decides: when the key after the entry in key order (the first of
-// the next child) has a larger leading word, no key of a later child shares
-// the query's leading word, so a present query lies at or below the entry.
-// Exact-match lookups take that shortcut (bit s of the node's mask is set
-// when it does not apply); range descents, which need the exact first key
-// >= lo, compare in full.  Entries below the child count are sorted, so the
-// "entry < query" lanes stay a prefix of the group either way.
+// the next child) has a larger deciding word, no key of a later child shares
+// the query's, so a present query lies at or below the entry.  Exact-match
+// lookups take that shortcut (bit s of the node's mask is set when it does
+// not apply) and go by the deciding word alone; range descents, which need
+// the exact first key >= lo, compare in full.  Entries below the child count
+// are sorted, so the "entry < query" lanes stay a prefix of the group either
+// way.
 template <int KW, int M, bool Exact>
 __device__ __forceinline__ uint32_t descend(const WideView& v, const Key<KW>& key, bool valid, uint32_t root,
-                                            uint32_t height, int s, int gbase) {
+                                            uint32_t height, int s, int gbase, uint32_t& lw) {
     const uint64_t* ik = reinterpret_cast<const uint64_t*>(v.ikeys);
     uint32_t ref = root;
+    lw = 0;
     for (uint32_t d = 0; d + 1 < height; ++d) {
         const uint64_t base = static_cast<uint64_t>(ref) * KW * M + s;
         const uint64_t e0 = ik[base];
         const uint4 meta = v.imeta[ref];
-        bool lt = e0 < key.w[0];
-        if constexpr (KW > 1) {
-            const uint64_t mask = Exact ? ~0ull : (static_cast<uint64_t>(meta.w) << 32 | meta.z);
-            const bool need = valid && e0 == key.w[0] && ((mask >> s) & 1ull);
+        const uint32_t w = KW > 1 ? meta_word(meta) : 0u;
+        bool lt;
+        if constexpr (KW == 1) {
+            lt = e0 < key.w[0];
+        } else if constexpr (Exact) {
+            lt = e0 < key.w[0];
+            const bool need = valid && (w != 0 || e0 == key.w[0]);
             if (__ballot(need)) {
                 if (need) {
-                    uint64_t e[KW];
+                    Key<KW> e;
 #pragma unroll
-                    for (int w = 1; w < KW; ++w) e[w] = ik[base + static_cast<uint64_t>(w) * M];
-                    bool l = e[KW - 1] < key.w[KW - 1];
-#pragma unroll
-                    for (int w = KW - 2; w >= 1; --w) l = (e[w] < key.w[w]) || (e[w] == key.w[w] && l);
-                    lt = l;
+                    for (int x = 0; x < KW; ++x)
+                        e.w[x] = ik[base + static_cast<uint64_t>(slice_of(static_cast<uint32_t>(x), w)) * M];
+                    lt = key_less<KW>(e, key);
                 }
+            }
+        } else {
+            const uint64_t kx = word_of<KW>(key.w, w);
+            lt = e0 < kx;
+            const bool need = valid && e0 == kx && ((meta_ties(meta) >> s) & 1ull);
+            if (__ballot(need)) {
+                if (need) lt = tie_less<KW, M>(ik, ref, static_cast<uint32_t>(s), w, key.w);
             }
         }
         lt = valid && lt;
         const uint32_t ci = static_cast<uint32_t>(__popcll(group_bits<M>(__ballot(lt), gbase)));
         ref = meta.x + ci;
+        lw = w;
     }
     return ref;
 }
 
-// Leaves of 32-byte keys: per leaf, the m leading words (big-endian
-// numbers), then m 32-byte records {words 1..3 as big-endian numbers,
-// value}.  Leaves of 8-byte keys: lkeys[leaf][m] keys, lvals[leaf][m].
+// Leaves of 32-byte keys: per leaf, the m entries' deciding words (those of
+// the leaf's parent; big-endian numbers), then m 32-byte records {the other
+// three words in order, value}.  Leaves of 8-byte keys: lkeys[leaf][m] keys,
+// lvals[leaf][m].
 constexpr uint64_t kLeafEntry32 = 40;  // bytes per entry of a 32-byte-key leaf
 
 template <int KW, int M>
@@ -190,7 +255,7 @@ __device__ __forceinline__ const uint64_t* leaf_words(const WideView& v, uint32_
     return reinterpret_cast<const uint64_t*>(v.lkeys + static_cast<uint64_t>(leaf) * M * (KW == 1 ? 8 : kLeafEntry32));
 }
 
-// words 1..3 and the value of entry s of a 32-byte-key leaf
+// the other words and the value of entry s of a 32-byte-key leaf
 template <int M>
 __device__ __forceinline__ void leaf_record(const WideView& v, uint32_t leaf, int s, uint64_t (&w)[3], uint64_t& val) {
     const uint4* r = reinterpret_cast<const uint4*>(v.lkeys + static_cast<uint64_t>(leaf) * M * kLeafEntry32 + M * 8 +
@@ -202,9 +267,16 @@ __device__ __forceinline__ void leaf_record(const WideView& v, uint32_t leaf, in
     val = (static_cast<uint64_t>(b.w) << 32) | b.z;
 }
 
+// word i of the three a record holds when the deciding word is lw
+template <int KW>
+__device__ __forceinline__ uint64_t other_word(const uint64_t (&k)[KW], int i, uint32_t lw) {
+    const uint64_t m = lw > static_cast<uint32_t>(i) ? ~0ull : 0ull;
+    return (k[i] & m) | (k[i + 1] & ~m);
+}
+
 // entry s of a leaf as a key (and its value)
 template <int KW, int M>
-__device__ __forceinline__ Key<KW> leaf_entry(const WideView& v, uint32_t leaf, int s, uint64_t& val) {
+__device__ __forceinline__ Key<KW> leaf_entry(const WideView& v, uint32_t leaf, uint32_t lw, int s, uint64_t& val) {
     Key<KW> k;
     const uint64_t w0 = leaf_words<KW, M>(v, leaf)[s];
     if constexpr (KW == 1) {
@@ -213,13 +285,26 @@ __device__ __forceinline__ Key<KW> leaf_entry(const WideView& v, uint32_t leaf, 
     } else {
         uint64_t w[3];
         leaf_record<M>(v, leaf, s, w, val);
-        k.w[0] = w0;
 #pragma unroll
-        for (int i = 1; i < KW; ++i) k.w[i] = w[i - 1];
+        for (int i = 0; i < KW; ++i) {
+            const uint64_t lo = i < KW - 1 ? w[i < 3 ? i : 2] : w0, hi = i > 0 ? w[i - 1] : w0;
+            k.w[i] = lw == static_cast<uint32_t>(i) ? w0 : (lw > static_cast<uint32_t>(i) ? lo : hi);
+        }
 #pragma unroll
         for (int i = 0; i < KW; ++i) k.raw[i] = __builtin_bswap64(k.w[i]);
     }
     return k;
+}
+
+// a lane's part of a sum over its group of G = 8 or 16 lanes, in every lane
+template <int G>
+__device__ __forceinline__ uint32_t group_sum(uint32_t x) {
+    static_assert(G == 8 || G == 16, "half a DPP row or a row");
+    x += __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0xB1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]
+    x += __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x4E, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
+    x += __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x141, 0xf, 0xf, false);  // row_half_mirror
+    if constexpr (G == 16) x += __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x140, 0xf, 0xf, false);
+    return x;
 }
 
 // Lookup of a small batch: M lanes per query, every entry of the leaf --
@@ -238,11 +323,12 @@ __global__ __launch_bounds__(kWBlock) void k_wlookup(WideView v, const uint8_t* 
         const uint64_t i = base + lane / M;
         const bool valid = i < B;
         const Key<KW> key = valid ? load_key<KW>(q + i * KB) : max_key<KW>();
-        const uint32_t leaf = descend<KW, M, false>(v, key, valid, root, height, s, gbase);
+        uint32_t lw;
+        const uint32_t leaf = descend<KW, M, false>(v, key, valid, root, height, s, gbase, lw);
         // the padding repeats the last key, so the first equal slot is a
         // real one; an empty tree's one leaf holds only padding
         uint64_t val = 0;
-        const Key<KW> lk = leaf_entry<KW, M>(v, leaf, s, val);
+        const Key<KW> lk = leaf_entry<KW, M>(v, leaf, lw, s, val);
         const bool eq = valid && !empty && key_eq<KW>(lk, key);
         const uint64_t gb = group_bits<M>(__ballot(eq), gbase);
         const int f = gb ? __ffsll(static_cast<long long>(gb)) - 1 : 0;
@@ -255,18 +341,19 @@ __global__ __launch_bounds__(kWBlock) void k_wlookup(WideView v, const uint8_t* 
 }
 
 // Large batches: G lanes per query (64 / G queries per wave instead of
-// 64 / M), lane l holding entries [l E, (l + 1) E) of a node, E = M / G.
-// The leading words of a lane's entries are one vector load; the ballots of
-// each entry position add up to the child index.
-// Inner ties and the leaf follow k_wlookup's two-round rules: an inner
-// entry whose leading word ties the query reads its other words only where
-// the node's tie mask says the tie does not decide; at the leaf a lane
-// reads the rest and the value of an entry whose leading word equals the
-// query's; the first equal entry answers.
-template <int KW, int M, int G>
+// 64 / M), lane l holding entries [l E, (l + 1) E) of a node, E = M / G, and
+// Q queries per lane group at once.  The deciding words of a lane's entries
+// are vector loads; the lanes' counts of smaller entries add up to the child
+// index.  An inner entry whose word ties the query reads on only where the
+// node's tie mask says the tie does not decide, a word of all the lane's
+// entries at a time (one vector load, where entry after entry would be three
+// scattered reads each); at the leaf a lane reads the
+// rest and the value of an entry whose deciding word equals the query's; the
+// first equal entry answers.
+template <int KW, int M, int G, int Q>
 __global__ __launch_bounds__(kWBlock) void k_wlookupg(WideView v, const uint8_t* __restrict__ q, uint64_t B,
                                                       uint64_t* __restrict__ vout, uint8_t* __restrict__ fout) {
-    constexpr int E = M / G, QPW = 64 / G;
+    constexpr int E = M / G, QPW = 64 / G * Q;
     constexpr uint64_t KB = 8 * KW;
     static_assert(E == 2 || E == 4 || E == 8, "two to eight entries per lane");
     const int lane = threadIdx.x & 63, gl = lane % G, gbase = lane - gl;
@@ -275,89 +362,132 @@ __global__ __launch_bounds__(kWBlock) void k_wlookupg(WideView v, const uint8_t*
     const uint32_t root = v.hdr->root, height = v.hdr->height;
     const bool empty = v.hdr->n_keys == 0;
     const uint64_t* ik = reinterpret_cast<const uint64_t*>(v.ikeys);
+    auto load_words = [](const uint64_t* p, uint64_t (&e)[E]) {
+        const uint4* p4 = reinterpret_cast<const uint4*>(p);
+#pragma unroll
+        for (int h = 0; h < E / 2; ++h) {
+            const uint4 x = p4[h];
+            e[2 * h] = (static_cast<uint64_t>(x.y) << 32) | x.x;
+            e[2 * h + 1] = (static_cast<uint64_t>(x.w) << 32) | x.z;
+        }
+    };
     for (uint64_t base = wave * QPW; base < B; base += nwaves * QPW) {
-        const uint64_t i = base + lane / G;
-        const bool valid = i < B;
-        const Key<KW> key = valid ? load_key<KW>(q + i * KB) : max_key<KW>();
-        uint32_t ref = root;
-        for (uint32_t d = 0; d + 1 < height; ++d) {
-            const uint64_t nb = static_cast<uint64_t>(ref) * KW * M + static_cast<uint64_t>(gl) * E;
-            uint64_t e0[E];
+        uint64_t i[Q];
+        bool valid[Q];
+        uint64_t key[Q][KW];
+        uint32_t ref[Q], lw[Q];
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            i[j] = base + static_cast<uint64_t>(j) * (64 / G) + lane / G;
+            valid[j] = i[j] < B;
             {
-                const uint4* p4 = reinterpret_cast<const uint4*>(ik + nb);
+                // a query past the end reads the last one's key
+                const Key<KW> k = load_key<KW>(q + (valid[j] ? i[j] : B - 1) * KB);
 #pragma unroll
-                for (int h = 0; h < E / 2; ++h) {
-                    const uint4 x = p4[h];
-                    e0[2 * h] = (static_cast<uint64_t>(x.y) << 32) | x.x;
-                    e0[2 * h + 1] = (static_cast<uint64_t>(x.w) << 32) | x.z;
-                }
+                for (int x = 0; x < KW; ++x) key[j][x] = k.w[x];
             }
-            const uint4 meta = v.imeta[ref];
-            uint32_t ci = 0;
+            ref[j] = root;
+            lw[j] = 0;
+        }
+        for (uint32_t d = 0; d + 1 < height; ++d) {
+            uint64_t e0[Q][E];
+            uint4 meta[Q];
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                bool lt = e0[e] < key.w[0];
+            for (int j = 0; j < Q; ++j) {
+                load_words(ik + static_cast<uint64_t>(ref[j]) * KW * M + static_cast<uint64_t>(gl) * E, e0[j]);
+                meta[j] = v.imeta[ref[j]];
+            }
+#pragma unroll
+            for (int j = 0; j < Q; ++j) {
+                const uint32_t w = KW > 1 ? meta_word(meta[j]) : 0u;
+                const uint64_t kx = word_of<KW>(key[j], w);
+                uint32_t c = 0, tied = 0;
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    c += e0[j][e] < kx ? 1u : 0u;
+                    tied |= (e0[j][e] == kx ? 1u : 0u) << e;
+                }
                 if constexpr (KW > 1) {
-                    const uint32_t slot = static_cast<uint32_t>(gl * E + e);
-                    const uint64_t mask = (static_cast<uint64_t>(meta.w) << 32) | meta.z;
-                    const bool need = valid && e0[e] == key.w[0] && ((mask >> slot) & 1ull);
-                    if (need) {
-                        uint64_t w[KW];
+                    // a lane with ties goes on to its entries' next word,
+                    // until none ties any more
+                    tied &= valid[j] ? static_cast<uint32_t>(meta_ties(meta[j]) >> (gl * E)) : 0u;
 #pragma unroll
-                        for (int x = 1; x < KW; ++x) w[x] = ik[nb + e + static_cast<uint64_t>(x) * M];
-                        bool l = w[KW - 1] < key.w[KW - 1];
+                    for (int x = 1; x < KW; ++x)
+                        if (tied && static_cast<uint32_t>(x) > w) {
+                            uint64_t ex[E];
+                            load_words(ik + (static_cast<uint64_t>(ref[j]) * KW + x) * M + gl * E, ex);
+                            uint32_t eq = 0;
 #pragma unroll
-                        for (int x = KW - 2; x >= 1; --x) l = (w[x] < key.w[x]) || (w[x] == key.w[x] && l);
-                        lt = l;
+                            for (int e = 0; e < E; ++e) {
+                                c += (tied >> e & 1u) && ex[e] < key[j][x] ? 1u : 0u;
+                                eq |= (ex[e] == key[j][x] ? 1u : 0u) << e;
+                            }
+                            tied &= eq;
+                        }
+                }
+                ref[j] = meta[j].x + group_sum<G>(c);
+                lw[j] = w;
+            }
+        }
+        // leaf: deciding words of this lane's entries, then the rest and the
+        // value of the entries that tie
+        uint64_t w0[Q][E];
+#pragma unroll
+        for (int j = 0; j < Q; ++j) load_words(leaf_words<KW, M>(v, ref[j]) + gl * E, w0[j]);
+        uint32_t tied[Q];
+        uint64_t val[Q];
+        bool hit[Q];
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            const uint64_t kx = word_of<KW>(key[j], lw[j]);
+            uint32_t m = 0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) m |= (w0[j][e] == kx ? 1u : 0u) << e;
+            tied[j] = valid[j] && !empty ? m : 0u;
+            val[j] = 0;
+            hit[j] = false;
+        }
+        // one tied entry per lane and query in flight at a time
+        auto any = [&] {
+            uint32_t m = 0;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) m |= tied[j];
+            return m != 0;
+        };
+        while (any()) {
+#pragma unroll
+            for (int j = 0; j < Q; ++j)
+                if (tied[j]) {
+                    const int slot = gl * E + __builtin_ctz(tied[j]);
+                    uint64_t vv;
+                    bool eq = true;
+                    if constexpr (KW == 1) {
+                        vv = v.lvals[static_cast<uint64_t>(ref[j]) * M + slot];
+                    } else {
+                        uint64_t w[3];
+                        leaf_record<M>(v, ref[j], slot, w, vv);
+#pragma unroll
+                        for (int x = 0; x < 3; ++x) eq = eq && w[x] == other_word<KW>(key[j], x, lw[j]);
+                    }
+                    tied[j] &= tied[j] - 1;
+                    if (eq) {
+                        hit[j] = true;
+                        val[j] = vv;
+                        tied[j] = 0;
                     }
                 }
-                ci += static_cast<uint32_t>(__popcll(group_bits<G>(__ballot(valid && lt), gbase)));
-            }
-            ref = meta.x + ci;
-        }
-        // leaf: leading words of this lane's entries, then the rest and the
-        // value of the entries that tie
-        const uint64_t* lw = leaf_words<KW, M>(v, ref) + gl * E;
-        uint64_t w0[E];
-        {
-            const uint4* p4 = reinterpret_cast<const uint4*>(lw);
-#pragma unroll
-            for (int h = 0; h < E / 2; ++h) {
-                const uint4 x = p4[h];
-                w0[2 * h] = (static_cast<uint64_t>(x.y) << 32) | x.x;
-                w0[2 * h + 1] = (static_cast<uint64_t>(x.w) << 32) | x.z;
-            }
-        }
-        int first = -1;
-        uint64_t val = 0;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            bool eq = valid && !empty && first < 0 && w0[e] == key.w[0];
-            if (eq) {
-                const int slot = gl * E + e;
-                uint64_t vv;
-                if constexpr (KW == 1) {
-                    vv = v.lvals[static_cast<uint64_t>(ref) * M + slot];
-                } else {
-                    uint64_t w[3];
-                    leaf_record<M>(v, ref, slot, w, vv);
-#pragma unroll
-                    for (int x = 1; x < KW; ++x) eq = eq && w[x - 1] == key.w[x];
-                }
-                if (eq) {
-                    first = e;
-                    val = vv;
-                }
-            }
         }
         // the padding repeats the last key, so the first equal entry is a
         // real one: the lowest lane with a match holds it
-        const uint64_t gb = group_bits<G>(__ballot(first >= 0), gbase);
-        const int f = gb ? __ffsll(static_cast<long long>(gb)) - 1 : 0;
-        const uint64_t fv = shfl_u64(val, gbase + f);
-        if (valid && gl == 0) {
-            vout[i] = gb ? fv : ~0ull;
-            fout[i] = gb ? 1 : 0;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            const uint64_t gb = group_bits<G>(__ballot(hit[j]), gbase);
+            const int f = gb ? __ffsll(static_cast<long long>(gb)) - 1 : 0;
+            const uint64_t fv = shfl_u64(val[j], gbase + f);
+            if (valid[j] && gl == 0) {
+                vout[i[j]] = gb ? fv : ~0ull;
+                fout[i[j]] = gb ? 1 : 0;
+            }
         }
     }
 }
@@ -382,7 +512,8 @@ __global__ __launch_bounds__(kWBlock) void k_wrange(WideView v, const uint8_t* _
         const Key<KW> b = valid ? load_key<KW>(hi + i * KB) : max_key<KW>();
         const uint32_t mx = valid ? maxc[i] : 0u;
         const uint64_t o = valid ? off[i] : 0ull;
-        uint32_t leaf = descend<KW, M, true>(v, a, valid, root, height, s, gbase);
+        uint32_t lw;
+        uint32_t leaf = descend<KW, M, true>(v, a, valid, root, height, s, gbase, lw);
         uint32_t c = 0;
         bool active = valid && !empty && mx > 0 && !key_less<KW>(b, a);
         // walk the chain; the loop runs while any group of the wave is active
@@ -391,8 +522,8 @@ __global__ __launch_bounds__(kWBlock) void k_wrange(WideView v, const uint8_t* _
             if (active) {
                 const uint2 meta = v.lmeta[leaf];
                 uint64_t val;
-                const Key<KW> k = leaf_entry<KW, M>(v, leaf, s, val);
-                const bool real = static_cast<uint32_t>(s) < meta.x;
+                const Key<KW> k = leaf_entry<KW, M>(v, leaf, meta.x >> 8, s, val);
+                const bool real = static_cast<uint32_t>(s) < (meta.x & 0xFFu);
                 const bool above = real && key_less<KW>(b, k);
                 const bool in = real && !key_less<KW>(k, a) && !above;
                 const uint64_t ib = group_bits<M>(__ballot(in), gbase);
@@ -456,12 +587,23 @@ __global__ void k_wdup(const uint8_t* __restrict__ sk, uint64_t n, uint32_t* fla
         if (key_eq<KW>(load_key<KW>(sk + i * KB), load_key<KW>(sk + (i + 1) * KB))) atomicOr(flag, 1u);
 }
 
-// leaf j holds sorted pairs [j n / L, (j+1) n / L); its largest key goes to
-// maxk[j]
+// the deciding word of keys a..b in key order: the first in which they differ
+template <int KW>
+__device__ __forceinline__ uint32_t deciding_word(const Key<KW>& a, const Key<KW>& b) {
+    uint32_t w = KW - 1;
+#pragma unroll
+    for (int x = KW - 2; x >= 0; --x)
+        if (a.w[x] != b.w[x]) w = static_cast<uint32_t>(x);
+    return w;
+}
+
+// leaf j holds sorted pairs [j n / L, (j+1) n / L); its smallest and largest
+// keys go to mink[j] and maxk[j].  P1: nodes of the level above (0: none); a
+// leaf's deciding word is its parent's.
 template <int KW, int M>
 __global__ void k_wleaves(uint8_t* __restrict__ lkeys, uint64_t* __restrict__ lvals, uint2* __restrict__ lmeta,
                           const uint8_t* __restrict__ sk, const uint64_t* __restrict__ sv, uint64_t n, uint64_t L,
-                          uint8_t* __restrict__ maxk, uint64_t* __restrict__ succ) {
+                          uint64_t P1, uint8_t* __restrict__ mink, uint8_t* __restrict__ maxk) {
     constexpr uint64_t KB = 8 * KW;
     for (uint64_t t = blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; t < L * M;
          t += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
@@ -469,24 +611,31 @@ __global__ void k_wleaves(uint8_t* __restrict__ lkeys, uint64_t* __restrict__ lv
         const uint64_t b = part_start(j, n, L), e = part_start(j + 1, n, L), c = e - b;
         Key<KW> k = c ? load_key<KW>(sk + (b + (s < c ? s : c - 1)) * KB) : max_key<KW>();
         const uint64_t val = s < c ? sv[b + s] : ~0ull;
+        uint32_t w = 0;
         if constexpr (KW == 1) {
             store_key<KW>(lkeys + t * KB, k);
             lvals[t] = val;
         } else {
+            if (P1) {
+                const uint64_t p = part_of(j, L, P1);
+                const uint64_t kb = part_start(part_start(p, L, P1), n, L);
+                const uint64_t ke = part_start(part_start(p + 1, L, P1), n, L);
+                w = deciding_word<KW>(load_key<KW>(sk + kb * KB), load_key<KW>(sk + (ke - 1) * KB));
+            }
             uint8_t* lb = lkeys + j * M * kLeafEntry32;
-            reinterpret_cast<uint64_t*>(lb)[s] = k.w[0];
+            reinterpret_cast<uint64_t*>(lb)[s] = word_of<KW>(k.w, w);
+            const uint64_t o0 = other_word<KW>(k.w, 0, w), o1 = other_word<KW>(k.w, 1, w), o2 = other_word<KW>(k.w, 2, w);
             uint4* r = reinterpret_cast<uint4*>(lb + M * 8 + s * 32);
-            r[0] = make_uint4(static_cast<uint32_t>(k.w[1]), static_cast<uint32_t>(k.w[1] >> 32),
-                              static_cast<uint32_t>(k.w[2]), static_cast<uint32_t>(k.w[2] >> 32));
-            r[1] = make_uint4(static_cast<uint32_t>(k.w[3]), static_cast<uint32_t>(k.w[3] >> 32),
-                              static_cast<uint32_t>(val), static_cast<uint32_t>(val >> 32));
+            r[0] = make_uint4(static_cast<uint32_t>(o0), static_cast<uint32_t>(o0 >> 32), static_cast<uint32_t>(o1),
+                              static_cast<uint32_t>(o1 >> 32));
+            r[1] = make_uint4(static_cast<uint32_t>(o2), static_cast<uint32_t>(o2 >> 32), static_cast<uint32_t>(val),
+                              static_cast<uint32_t>(val >> 32));
         }
         if (s == 0) {
-            lmeta[j] = make_uint2(static_cast<uint32_t>(c), j + 1 < L ? static_cast<uint32_t>(j + 1) : kNone);
+            lmeta[j] = make_uint2(static_cast<uint32_t>(c) | w << 8,
+                                  j + 1 < L ? static_cast<uint32_t>(j + 1) : kNone);
+            store_key<KW>(mink + j * KB, k);
             store_key<KW>(maxk + j * KB, c ? load_key<KW>(sk + (e - 1) * KB) : max_key<KW>());
-            // leading word of the key after the leaf's last one (all ones
-            // past the end)
-            succ[j] = e < n ? load_key<KW>(sk + e * KB).w[0] : ~0ull;
         }
     }
 }
@@ -496,8 +645,8 @@ __global__ void k_wleaves(uint8_t* __restrict__ lkeys, uint64_t* __restrict__ lv
 // largest key, later entries the largest key value
 template <int KW, int M>
 __global__ void k_winner(uint8_t* __restrict__ ikeys, uint4* __restrict__ imeta,
-                         const uint8_t* __restrict__ cmax, const uint64_t* __restrict__ csucc, uint64_t C, uint64_t P,
-                         uint32_t node_base, uint8_t* __restrict__ nmax, uint64_t* __restrict__ nsucc) {
+                         const uint8_t* __restrict__ cmin, const uint8_t* __restrict__ cmax, uint64_t C, uint64_t P,
+                         uint32_t node_base, uint8_t* __restrict__ nmin, uint8_t* __restrict__ nmax) {
     constexpr uint64_t KB = 8 * KW;
     // the stride is a multiple of 64 and M divides 64, so a node's M
     // entries are M consecutive lanes of one wave in every pass
@@ -506,20 +655,26 @@ __global__ void k_winner(uint8_t* __restrict__ ikeys, uint4* __restrict__ imeta,
          t += static_cast<uint64_t>(gridDim.x) * blockDim.x) {
         const uint64_t j = t / M, s = t % M;
         const uint64_t b = part_start(j, C, P), e = part_start(j + 1, C, P), c = e - b;
+        const Key<KW> first = load_key<KW>(cmin + b * KB), last = load_key<KW>(cmax + (e - 1) * KB);
+        const uint32_t w = KW > 1 ? deciding_word<KW>(first, last) : 0u;
         const Key<KW> k = (s + 1 < c) ? load_key<KW>(cmax + (b + s) * KB) : max_key<KW>();
-        // word-sliced: word w of entry s at ((node * KW) + w) * M + s, as a
+        // word-sliced, the deciding word's slice first, each word as a
         // big-endian number (the order the search compares in)
         uint64_t* ik = reinterpret_cast<uint64_t*>(ikeys);
 #pragma unroll
-        for (int w = 0; w < KW; ++w) ik[((node_base + j) * KW + w) * M + s] = k.w[w];
-        // the entry's leading word is shared with the next key in key order
-        const bool shared = s + 1 < c && k.w[0] == csucc[b + s];
+        for (int x = 0; x < KW; ++x)
+            ik[((node_base + j) * KW + slice_of(static_cast<uint32_t>(x), w)) * M + s] = k.w[x];
+        // the entry's deciding word is shared with the next key in key order,
+        // the first of the next child
+        bool shared = false;
+        if (KW > 1 && s + 1 < c)
+            shared = word_of<KW>(k.w, w) == word_of<KW>(load_key<KW>(cmin + (b + s + 1) * KB).w, w);
         const uint64_t bits = group_bits<M>(__ballot(shared), gbase);
         if (s == 0) {
-            imeta[node_base + j] = make_uint4(static_cast<uint32_t>(b), static_cast<uint32_t>(c),
+            imeta[node_base + j] = make_uint4(static_cast<uint32_t>(b), static_cast<uint32_t>(c) | w << 8,
                                               static_cast<uint32_t>(bits), static_cast<uint32_t>(bits >> 32));
-            store_key<KW>(nmax + j * KB, load_key<KW>(cmax + (e - 1) * KB));
-            nsucc[j] = csucc[e - 1];
+            store_key<KW>(nmin + j * KB, first);
+            store_key<KW>(nmax + j * KB, last);
         }
     }
 }
@@ -597,10 +752,20 @@ void launch_wlookup(const WideView& v, const void* keys, uint64_t B, void* vout,
     const uint64_t g = std::min<uint64_t>((B + qpb - 1) / qpb, kWGridMax);
     if (B >= kWTwoRound) {
         constexpr int G = large_lanes<M>();
-        constexpr uint64_t qpbg = kWBlock / G;
-        const uint64_t gg = std::min<uint64_t>((B + qpbg - 1) / qpbg, kWGridMax);
-        hipLaunchKernelGGL((k_wlookupg<KW, M, G>), dim3(static_cast<uint32_t>(gg)), dim3(kWBlock), 0, s, v,
-                           reinterpret_cast<const uint8_t*>(keys), B, reinterpret_cast<uint64_t*>(vout), fout);
+        auto large = [&](auto Qc) {
+            constexpr int Q = decltype(Qc)::value;
+            constexpr uint64_t qpbg = kWBlock / G * Q;
+            const uint64_t gg = std::min<uint64_t>((B + qpbg - 1) / qpbg, kWGridMax);
+            hipLaunchKernelGGL((k_wlookupg<KW, M, G, Q>), dim3(static_cast<uint32_t>(gg)), dim3(kWBlock), 0, s, v,
+                               reinterpret_cast<const uint8_t*>(keys), B, reinterpret_cast<uint64_t*>(vout), fout);
+        };
+        if constexpr (KW == 1) {
+            if (B >= kWTwoQueries) {
+                large(std::integral_constant<int, 2>{});
+                return;
+            }
+        }
+        large(std::integral_constant<int, 1>{});
     } else {
         hipLaunchKernelGGL((k_wlookup<KW, M>), dim3(static_cast<uint32_t>(g)), dim3(kWBlock), 0, s, v,
                            reinterpret_cast<const uint8_t*>(keys), B, reinterpret_cast<uint64_t*>(vout), fout);
@@ -619,24 +784,20 @@ void launch_wrange(const WideView& v, const void* lo, const void* hi, const uint
 
 template <int KW, int M>
 void launch_wpack(WideTree* w, const uint8_t* sk, const uint64_t* sv, uint64_t n, const std::vector<uint64_t>& lv,
-                  uint8_t* maxa, uint8_t* maxb, uint64_t* succa, uint64_t* succb, hipStream_t s) {
+                  uint8_t* mina, uint8_t* minb, uint8_t* maxa, uint8_t* maxb, hipStream_t s) {
     const uint64_t L = lv[0];
     hipLaunchKernelGGL((k_wleaves<KW, M>), dim3(grid_for(L * M, kWBlock)), dim3(kWBlock), 0, s, w->lkeys, w->lvals,
-                       w->lmeta, sk, sv, n, L, maxa, succa);
+                       w->lmeta, sk, sv, n, L, lv.size() > 1 ? lv[1] : 0, mina, maxa);
     // inner ids top-down: the level just above the leaves gets the last ids
     uint64_t below = L;
     uint64_t base = w->inner_cap;
-    uint8_t* cur = maxa;
-    uint8_t* nxt = maxb;
-    uint64_t* scur = succa;
-    uint64_t* snxt = succb;
     for (size_t l = 1; l < lv.size(); ++l) {
         const uint64_t P = lv[l];
         base -= P;
         hipLaunchKernelGGL((k_winner<KW, M>), dim3(grid_for(P * M, kWBlock)), dim3(kWBlock), 0, s, w->ikeys, w->imeta,
-                           cur, scur, below, P, static_cast<uint32_t>(base), nxt, snxt);
-        std::swap(cur, nxt);
-        std::swap(scur, snxt);
+                           mina, maxa, below, P, static_cast<uint32_t>(base), minb, maxb);
+        std::swap(mina, minb);
+        std::swap(maxa, maxb);
         below = P;
     }
 }
@@ -756,12 +917,12 @@ gt_status wide_build(const gt_params* p, const void* keys, const void* values, u
 
     // temporary buffers: sorted keys and values, the permutation and its
     // ping-pong, one word column (the sort's input) with the sort's output
-    // and ping-pong, sort scratch, level maxima (two levels), the duplicate /
+    // and ping-pong, sort scratch, level bounds (two levels), the duplicate /
     // sort-failure flag
     const uint64_t nn = n ? n : 1;
     const uint64_t b_keys = al(nn * kb), b_vals = al(nn * 8), b_idx = al(nn * 4), b_word = al(nn * 8);
-    const uint64_t b_sort = al(sort_tmp_bytes(nn, 8)), b_max = al(z.leaves * kb), b_succ = al(z.leaves * 8);
-    const uint64_t total = b_keys + b_vals + 4 * b_idx + 3 * b_word + b_sort + 2 * b_max + 2 * b_succ + kAl;
+    const uint64_t b_sort = al(sort_tmp_bytes(nn, 8)), b_max = al(z.leaves * kb);
+    const uint64_t total = b_keys + b_vals + 4 * b_idx + 3 * b_word + b_sort + 4 * b_max + kAl;
     uint8_t* tmp = nullptr;
     if (hipMalloc(&tmp, total) != hipSuccess) {
         delete w;
@@ -780,8 +941,8 @@ gt_status wide_build(const gt_params* p, const void* keys, const void* values, u
     void* stmp = q; q += b_sort;
     uint8_t* maxa = q; q += b_max;
     uint8_t* maxb = q; q += b_max;
-    uint64_t* succa = reinterpret_cast<uint64_t*>(q); q += b_succ;
-    uint64_t* succb = reinterpret_cast<uint64_t*>(q); q += b_succ;
+    uint8_t* mina = q; q += b_max;
+    uint8_t* minb = q; q += b_max;
     uint32_t* flag = reinterpret_cast<uint32_t*>(q);
 
     gt_status st = GT_OK;
@@ -791,7 +952,7 @@ gt_status wide_build(const gt_params* p, const void* keys, const void* values, u
         if (n) {
             const uint8_t* kin = reinterpret_cast<const uint8_t*>(keys);
             if (kw == 1) {
-                // one radix sort of the integers; positions come from the sort
+                // one sort of the integers; positions come from it
                 sort_from<uint64_t>(reinterpret_cast<const uint64_t*>(kin), col, perm, col2, si2, n, stmp, s, flag,
                                     2u);
             } else {
@@ -831,7 +992,7 @@ gt_status wide_build(const gt_params* p, const void* keys, const void* values, u
         if (hflag & 2u) { st = GT_ERR_DEVICE; break; }  // a sort gave up its bounded wait
         if (hflag) { st = GT_ERR_DUPLICATE; break; }
         dispatch(kw, m, [&](auto KWc, auto Mc) {
-            launch_wpack<decltype(KWc)::value, decltype(Mc)::value>(w, sk, sv, n, lv, maxa, maxb, succa, succb, s);
+            launch_wpack<decltype(KWc)::value, decltype(Mc)::value>(w, sk, sv, n, lv, mina, minb, maxa, maxb, s);
         });
         fix_child_bases(w, lv, s);
         hipLaunchKernelGGL(k_wheader, dim3(1), dim3(64), 0, s, w->hdr, static_cast<uint32_t>(z.height), n,
@@ -941,10 +1102,12 @@ gt_status wide_export(const WideTree* w, void* host_buf, uint64_t* bytes, hipStr
     for (uint64_t i = 0; i < ni; ++i) {
         // inner entries back from word slices to key bytes: a 32-byte key's
         // words are big-endian numbers, an 8-byte key's word is native
+        const uint64_t dw = im[i].y >> 8, kids = im[i].y & 0xFFu;
         for (uint64_t j = 0; j < m; ++j)
             for (uint64_t wd = 0; wd < kw; ++wd) {
+                const uint64_t slice = wd == dw ? 0 : (wd < dw ? wd + 1 : wd);
                 uint64_t x;
-                memcpy(&x, ik.data() + ((i * kw + wd) * m + j) * 8, 8);
+                memcpy(&x, ik.data() + ((i * kw + slice) * m + j) * 8, 8);
                 if (kw > 1) x = __builtin_bswap64(x);
                 memcpy(o + j * kb + wd * 8, &x, 8);
             }
@@ -952,7 +1115,7 @@ gt_status wide_export(const WideTree* w, void* host_buf, uint64_t* bytes, hipStr
         const bool leaf_kids = i >= leaf_parents_first;
         for (uint64_t j = 0; j < m; ++j) {
             uint32_t r = kNone;
-            if (j < im[i].y) r = (leaf_kids ? kLeafTag : 0u) | (im[i].x + static_cast<uint32_t>(j));
+            if (j < kids) r = (leaf_kids ? kLeafTag : 0u) | (im[i].x + static_cast<uint32_t>(j));
             memcpy(ch + j, &r, 4);
         }
         o += rin;
@@ -968,14 +1131,16 @@ gt_status wide_export(const WideTree* w, void* host_buf, uint64_t* bytes, hipStr
                 uint64_t x[5];
                 memcpy(&x[0], lb + j * 8, 8);
                 memcpy(&x[1], lb + m * 8 + j * 32, 32);
+                const int dw = static_cast<int>(lm[i].x >> 8);
                 for (int wd = 0; wd < 4; ++wd) {
-                    const uint64_t be = __builtin_bswap64(x[wd]);
+                    const uint64_t be = __builtin_bswap64(x[wd == dw ? 0 : (wd < dw ? wd + 1 : wd)]);
                     memcpy(o + j * kb + wd * 8, &be, 8);
                 }
                 memcpy(o + C * kb + j * 8, &x[4], 8);
             }
         }
-        memcpy(o + C * (kb + 8), &lm[i], 8);
+        const uint2 meta = make_uint2(lm[i].x & 0xFFu, lm[i].y);
+        memcpy(o + C * (kb + 8), &meta, 8);
         o += rlf;
     }
     *bytes = need;
