@@ -58,32 +58,6 @@ __device__ __forceinline__ T block_excl_scan(T v, T* sh, T* total) {
     return res;
 }
 
-// Bitonic sort of (key, index) pairs held in LDS, n2 a power of two, by the
-// whole workgroup; pairs compare by key then index, so equal keys keep their
-// index order.
-template <class K>
-__device__ __forceinline__ void bitonic_lds(K* sk, uint32_t* si, uint32_t n2) {
-    const uint32_t half = n2 >> 1;
-    for (uint32_t k = 2; k <= n2; k <<= 1) {
-        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-            // pair q compares slots t and t + j, where t has bit j clear
-            for (uint32_t q = threadIdx.x; q < half; q += blockDim.x) {
-                const uint32_t t = ((q & ~(j - 1)) << 1) | (q & (j - 1));
-                const uint32_t p = t | j;
-                const K a = sk[t], b = sk[p];
-                const uint32_t ia = si[t], ib = si[p];
-                const bool gt = (a > b) || (a == b && ia > ib);
-                const bool up = (t & k) == 0;
-                if (gt == up) {
-                    sk[t] = b; sk[p] = a;
-                    si[t] = ib; si[p] = ia;
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
 // ------------------------------------------------------------ host side
 
 // Largest batch rank_sort_small takes (all keys sit in each workgroup's LDS).
@@ -108,28 +82,21 @@ template <class T>
 void scan_exclusive(const T* in, T* out, T* total, const uint32_t* n_dev, uint64_t n_max,
                     void* tmp, hipStream_t s);
 
-// Scratch bytes needed by sort_pairs and sort_from for n elements.
+// Scratch bytes needed by sort_from for n elements.
 uint64_t sort_tmp_bytes(uint64_t n, int key_bytes);
 
-// Stable sort of (keys[i], idx[i]) by key, n host-known.  keys_alt/idx_alt
-// are ping-pong buffers of n entries.  The result ends in keys/idx.  If a
-// tile's look-back wait gives up (never expected: it waits only on running
-// tiles), err_bit is or-ed into *err (a device word; by default one in tmp)
-// and the order is not valid.
-template <class K>
-void sort_pairs(K* keys, uint32_t* idx, K* keys_alt, uint32_t* idx_alt, uint64_t n, void* tmp,
-                hipStream_t s, uint32_t* err = nullptr, uint32_t err_bit = 1u);
-
-// The same sort of (src[i], i), n > 2048: src is read, keys/idx receive the
-// result, keys_alt/idx_alt are ping-pong buffers.
+// Stable sort of (src[i], i) by key, n host-known: src is read, keys/idx
+// receive the result, keys_alt/idx_alt are ping-pong buffers of n entries.  If
+// the sort fails (never expected), err_bit is or-ed into *err (a device word,
+// optional) and the result is every key 0, index i at position i.
 template <class K>
 void sort_from(const K* src, K* keys, uint32_t* idx, K* keys_alt, uint32_t* idx_alt, uint64_t n, void* tmp,
                hipStream_t s, uint32_t* err = nullptr, uint32_t err_bit = 1u);
 
 // The sample sort (sample_sort.hip), which sort_from takes up to
 // sample_sort_max() elements: a stable sort of (src[i], i) as sort_from
-// describes it; tmp holds sample_sort_tmp_bytes, which from 2049 elements on
-// (the callers' smallest) is less than sort_tmp_bytes.  force_fail makes it report a
+// describes it; tmp holds sample_sort_tmp_bytes, which is less than
+// sort_tmp_bytes.  force_fail makes it report a
 // failure (testing hook).
 uint64_t sample_sort_max();
 uint64_t sample_sort_tmp_bytes(uint64_t n, int key_bytes);

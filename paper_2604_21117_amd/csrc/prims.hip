@@ -10,12 +10,9 @@
 // and 31 us for 2^16 where the eight passes below took 175 and 88 (2^24: 480
 // against 1700, with the leaves of a bulk load written as well).
 //
-// sort_pairs, whose indices may come in any order (the sample sort orders
-// equal keys by position), and larger inputs: up to 2048 elements sort inside
-// one workgroup with a bitonic network on (key, index) pairs, which orders
-// equal keys by index and so is stable.  Larger inputs use LSD radix sort with
-// 8-bit digits, one stable scatter kernel per pass whose tiles find their
-// output offsets by decoupled look-back (below).
+// Larger inputs use LSD radix sort with 8-bit digits, one stable scatter
+// kernel per pass whose tiles find their output offsets by decoupled
+// look-back (below).
 #include <atomic>
 
 #include "prims.h"
@@ -137,7 +134,7 @@ template void scan_exclusive<uint64_t>(const uint64_t*, uint64_t*, uint64_t*, co
 
 // ------------------------------------------------------------------ sort
 //
-// For n > kBitonicMax: LSD radix sort with 8-bit digits, one scatter kernel
+// For n > sample_sort_max(): LSD radix sort with 8-bit digits, one scatter kernel
 // per pass (the decoupled look-back of single-pass prefix scans, Merrill and
 // Garland, "Single-pass Parallel Prefix Scan with Decoupled Look-back",
 // NVIDIA technical report NVR-2016-002, 2016; written here for wave64 tiles).
@@ -160,7 +157,6 @@ template void scan_exclusive<uint64_t>(const uint64_t*, uint64_t*, uint64_t*, co
 constexpr int kSortBlock = 1024;
 constexpr int kSortRounds = 4;
 constexpr uint64_t kSortTile = kSortBlock * kSortRounds;  // 4096
-constexpr uint64_t kBitonicMax = 2048;
 constexpr uint32_t kSpinMax = 1u << 20;       // a look-back that waits longer gives up
 static std::atomic<uint32_t> g_spin_max{kSpinMax};  // set by the testing hook (0: give up at once)
 
@@ -190,22 +186,6 @@ static SortLayout sort_layout(uint64_t n, int key_bytes) {
 }
 
 uint64_t sort_tmp_bytes(uint64_t n, int key_bytes) { return sort_layout(n, key_bytes).bytes; }
-
-template <class K>
-__global__ __launch_bounds__(kSortBlock) void k_bitonic(K* keys, uint32_t* idx, uint32_t n, uint32_t n2) {
-    __shared__ K sk[kBitonicMax];
-    __shared__ uint32_t si[kBitonicMax];
-    for (uint32_t t = threadIdx.x; t < n2; t += kSortBlock) {
-        sk[t] = t < n ? keys[t] : kmax<K>();
-        si[t] = t < n ? idx[t] : 0xFFFFFFFFu;
-    }
-    __syncthreads();
-    bitonic_lds<K>(sk, si, n2);
-    for (uint32_t t = threadIdx.x; t < n; t += kSortBlock) {
-        keys[t] = sk[t];
-        idx[t] = si[t];
-    }
-}
 
 __global__ __launch_bounds__(256) void k_sort_clear(uint32_t* w, uint64_t words) {
     for (uint64_t i = blockIdx.x * 256ull + threadIdx.x; i < words; i += gridDim.x * 256ull) w[i] = 0;
@@ -430,11 +410,11 @@ static void sort_onesweep(const K* src, K* keys, uint32_t* idx, K* keys_alt, uin
     hipLaunchKernelGGL(k_sort_clear, dim3(static_cast<uint32_t>(cg < 4096 ? cg : 4096)), dim3(256), 0, s,
                        reinterpret_cast<uint32_t*>(b), words);
     const uint32_t hg = nt < 512 ? nt : 512;
-    hipLaunchKernelGGL(k_sort_hist<K>, dim3(hg), dim3(kSortBlock), 0, s, src ? src : keys, n, totals);
-    // pass 0 reads the source (indices 0..n-1) or keys/idx and writes the
-    // alternates; sizeof(K) passes is even, so the result ends in keys/idx
-    const K* ka = src ? src : keys;
-    const uint32_t* ia = src ? nullptr : idx;
+    hipLaunchKernelGGL(k_sort_hist<K>, dim3(hg), dim3(kSortBlock), 0, s, src, n, totals);
+    // pass 0 reads the source (indices 0..n-1) and writes the alternates;
+    // sizeof(K) passes is even, so the result ends in keys/idx
+    const K* ka = src;
+    const uint32_t* ia = nullptr;
     K* kb = keys_alt; uint32_t* ib = idx_alt;
     for (int p = 0; p < P; ++p) {
         hipLaunchKernelGGL((k_sort_pass<K, W>), dim3(nt), dim3(kSortBlock), 0, s, ka, ia, kb, ib, n, 8 * p,
@@ -446,20 +426,6 @@ static void sort_onesweep(const K* src, K* keys, uint32_t* idx, K* keys_alt, uin
         ib = (p & 1) ? idx_alt : idx;
     }
     hipLaunchKernelGGL(k_sort_fix<K>, dim3(1), dim3(1024), 0, s, keys, idx, n, fail);
-}
-
-template <class K>
-void sort_pairs(K* keys, uint32_t* idx, K* keys_alt, uint32_t* idx_alt, uint64_t n, void* tmp, hipStream_t s,
-                uint32_t* err, uint32_t err_bit) {
-    if (n <= 1) return;
-    if (n <= kBitonicMax) {
-        uint32_t n2 = 2;
-        while (n2 < n) n2 <<= 1;
-        hipLaunchKernelGGL(k_bitonic<K>, dim3(1), dim3(kSortBlock), 0, s, keys, idx, static_cast<uint32_t>(n), n2);
-        return;
-    }
-    if (n < kNarrowMax) sort_onesweep<K, uint32_t>(nullptr, keys, idx, keys_alt, idx_alt, n, tmp, s, err, err_bit);
-    else sort_onesweep<K, uint64_t>(nullptr, keys, idx, keys_alt, idx_alt, n, tmp, s, err, err_bit);
 }
 
 template <class K>
@@ -531,13 +497,9 @@ template void rank_sort_small<uint32_t>(const uint32_t*, uint32_t, uint32_t*, ui
 template void rank_sort_small<uint64_t>(const uint64_t*, uint32_t, uint64_t*, uint32_t*, uint32_t*, uint32_t,
                                         hipStream_t);
 
-template void sort_pairs<uint32_t>(uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint64_t, void*, hipStream_t,
-                                   uint32_t*, uint32_t);
 template void sort_from<uint32_t>(const uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint64_t, void*,
                                   hipStream_t, uint32_t*, uint32_t);
 template void sort_from<uint64_t>(const uint64_t*, uint64_t*, uint32_t*, uint64_t*, uint32_t*, uint64_t, void*,
                                   hipStream_t, uint32_t*, uint32_t);
-template void sort_pairs<uint64_t>(uint64_t*, uint32_t*, uint64_t*, uint32_t*, uint64_t, void*, hipStream_t,
-                                   uint32_t*, uint32_t);
 
 }  // namespace gt
