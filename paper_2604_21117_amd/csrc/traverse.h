@@ -148,6 +148,17 @@ struct Trav {
     }
 };
 
+// The value of lane group's query j = gl (gl < QPG) out of its QPG registers
+// (with masks: a select of two array elements would become an indexed read,
+// and the array a memory object).
+template <int QPG>
+__device__ __forceinline__ uint32_t own_query(const uint32_t (&x)[QPG], int gl) {
+    uint32_t r = 0;
+#pragma unroll
+    for (int j = 0; j < QPG; ++j) r |= x[j] & (gl == j ? ~0u : 0u);
+    return r;
+}
+
 // Copy the first `nodes` mirror nodes (header, keys, children, first-child
 // indices) from global memory into LDS.  Called by the whole workgroup.
 template <class K>
@@ -174,15 +185,18 @@ __device__ __forceinline__ void stage_mirror(const uint8_t* mirror, uint8_t* lds
 //            with mnodes = kMirrorMaxNodes)
 //   use_lv   mirror levels to use (clamped to the levels the mirror holds)
 // On return leaf[j] is the leaf index (tag removed) for key[j].
-// If REC is set, path_node[l][j] / path_idx[l][j] receive the inner node and
-// child slot taken at inner level l (0 = root level) for l < height-1, and
-// path_cnt[l][j] (if given) that node's number of children.
+// If REC is set, path_node[l][qidx[j]] / path_idx / path_cnt receive the inner
+// node, the child slot taken and the node's number of children at inner level
+// l (0 = root level) for l < height-1.  Lane j of the group writes query j's
+// (qidx is that lane's query index, ~0 for none), so that a level's records of
+// a wave's queries leave in one store per array.
 template <class K, int G, int QPG, bool REC>
 __device__ __forceinline__ void descend(const TreeView<K>& t, const uint8_t* mir, uint32_t mnodes, int use_lv,
                                         const K (&key)[QPG], uint32_t (&leaf)[QPG], int gl, int gbase,
                                         uint32_t* path_node = nullptr, uint8_t* path_idx = nullptr,
-                                        uint64_t path_stride = 0, const uint64_t* qidx = nullptr,
+                                        uint64_t path_stride = 0, uint64_t qidx = ~0ull,
                                         uint8_t* path_cnt = nullptr) {
+    static_assert(!REC || QPG <= G, "one recording lane per query");
     using T = Trav<K, G>;
     using ML = MirrorLayout<K>;
     const MirrorHeader* mh = reinterpret_cast<const MirrorHeader*>(mir);
@@ -198,6 +212,20 @@ __device__ __forceinline__ void descend(const TreeView<K>& t, const uint8_t* mir
     const uint32_t root = mh->root;
 #pragma unroll
     for (int j = 0; j < QPG; ++j) node[j] = root;
+
+    uint32_t at_node[QPG], at_slot[QPG];  // the level's records: node, slot | children << 8
+    auto record = [&](int l) {
+        const uint32_t n = own_query<QPG>(at_node, gl), sc = own_query<QPG>(at_slot, gl);
+        if (gl < QPG && qidx != ~0ull) {
+            const uint64_t at = static_cast<uint64_t>(l) * path_stride + qidx;
+            path_node[at] = n;
+            path_idx[at] = static_cast<uint8_t>(sc);
+            path_cnt[at] = static_cast<uint8_t>(sc >> 8);
+        }
+    };
+    (void)at_node;
+    (void)at_slot;
+    (void)record;
 
     int level = 0;
     if (lv > 0) {
@@ -217,16 +245,13 @@ __device__ __forceinline__ void descend(const TreeView<K>& t, const uint8_t* mir
                 uint32_t idx = T::child_index(kv[j], key[j], gbase);
                 uint32_t c = T::pick_child(cv[j], idx, gbase);
                 if constexpr (REC) {
-                    const uint32_t nc = path_cnt ? T::child_count(kv[j], gl, gbase) : 0u;
-                    if (gl == 0 && qidx[j] != ~0ull) {
-                        path_node[level * path_stride + qidx[j]] = node[j];
-                        path_idx[level * path_stride + qidx[j]] = static_cast<uint8_t>(idx);
-                        if (path_cnt) path_cnt[level * path_stride + qidx[j]] = static_cast<uint8_t>(nc);
-                    }
+                    at_node[j] = node[j];
+                    at_slot[j] = idx | T::child_count(kv[j], gl, gbase) << 8;
                 }
                 node[j] = c;
                 if (level + 1 < lv) m[j] = mfirst[m[j]] + idx;
             }
+            if constexpr (REC) record(level);
         }
     }
     // HBM levels: a node whose children are consecutive gives its child
@@ -248,15 +273,12 @@ __device__ __forceinline__ void descend(const TreeView<K>& t, const uint8_t* mir
                 c = T::pick_child(cv, idx, gbase);
             }
             if constexpr (REC) {
-                const uint32_t nc = path_cnt ? T::child_count(kv[j], gl, gbase) : 0u;
-                if (gl == 0 && qidx[j] != ~0ull) {
-                    path_node[level * path_stride + qidx[j]] = node[j];
-                    path_idx[level * path_stride + qidx[j]] = static_cast<uint8_t>(idx);
-                    if (path_cnt) path_cnt[level * path_stride + qidx[j]] = static_cast<uint8_t>(nc);
-                }
+                at_node[j] = node[j];
+                at_slot[j] = idx | T::child_count(kv[j], gl, gbase) << 8;
             }
             node[j] = c;
         }
+        if constexpr (REC) record(level);
     }
 #pragma unroll
     for (int j = 0; j < QPG; ++j) leaf[j] = node[j] & ~kLeafTag;
