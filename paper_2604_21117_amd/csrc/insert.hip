@@ -2055,73 +2055,119 @@ __device__ __forceinline__ bool leaf_run_head(const Ins<K>& v, uint64_t u) {
     return u == 0 || v.uleaf[u - 1] != v.uleaf[u];
 }
 
+// Or over a row of 16 lanes, in every lane.
+__device__ __forceinline__ uint32_t row_or(uint32_t x) {
+    x |= __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x128, 0xf, 0xf, false);  // row_ror:8, 4, 2, 1
+    x |= __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x124, 0xf, 0xf, false);
+    x |= __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x122, 0xf, 0xf, false);
+    x |= __builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x121, 0xf, 0xf, false);
+    return x;
+}
+
 // 16 lanes per touched leaf, lane s on slot s: the lanes read the run's
-// distinct keys 16 at a time for the slots to remove, then move the kept
-// pairs down (new slot = kept slots below) and pad the rest.  The deleted
-// count is added once per wave at the end (one atomic per leaf on a single
-// address would serialise); k_del_list then lists the leaves left below
+// distinct keys 16 at a time for the slots to remove, then the kept pairs move
+// down (each lane reads the pair its slot gets from the lane that holds it)
+// and the leaf's lines are written whole.  A group's first read is its 16
+// next keys' records, its second the leaf of its own key, needed or not, so a
+// leaf costs two dependent rounds; R keys a group are in flight.  Returns
+// how many keys the wave removed; k_del_list then lists the leaves left below
 // half full, one thread per distinct key.
-template <class K>
-__device__ __forceinline__ void ph_del_leaf(TreeView<K> t, Ins<K> v) {
-    if (t.hdr->error & kErrInternal) return;  // e.g. the batch's device sort gave up
+template <class K, int R>
+__device__ __forceinline__ uint32_t ph_del_leaf(TreeView<K> t, Ins<K> v) {
+    if (t.hdr->error & kErrInternal) return 0;  // e.g. the batch's device sort gave up
     const uint64_t U = v.st->U;
     const int h = static_cast<int>(v.st->height);
     const int lane = static_cast<int>(threadIdx.x) & 63, s = lane & (kSlots - 1), gbase = lane - s;
     const uint64_t g0 = gtid() / kSlots, gs = gstride() / kSlots;
     uint32_t del = 0;  // keys this group removed (lane 0 of the group)
-    for (uint64_t u = g0;; u += gs) {
-        if (__ballot(u < U) == 0) break;  // the wave's four groups are done
-        const bool head = u < U && leaf_run_head(v, u);  // the same for the group's 16 lanes
-        if (u < U && s == 0) v.nu[u] = 0u;  // set to 1 below for a run left below half full
-        if (head) {
-            const uint32_t leaf = v.uleaf[u];
-            uint32_t gone = 0, nd = 0;
-            for (uint64_t e0 = u;; e0 += kSlots) {
-                const uint64_t e = e0 + static_cast<uint64_t>(s);
-                const bool in = e < U && v.uleaf[e] == leaf;
-                const bool hit = in && v.ufound[e];
-                uint32_t bit = hit ? (1u << v.uslot[e]) : 0u;
-                bit |= __shfl_xor(bit, 1);
-                bit |= __shfl_xor(bit, 2);
-                bit |= __shfl_xor(bit, 4);
-                bit |= __shfl_xor(bit, 8);
-                gone |= bit;
-                nd += static_cast<uint32_t>(__popcll((__ballot(hit) >> gbase) & 0xFFFFull));
-                if (((__ballot(in) >> gbase) & 0xFFFFull) != 0xFFFFull) break;  // the run ended in this round
+    for (uint64_t ub = g0;; ub += R * gs) {
+        if (__ballot(ub < U) == 0) break;  // the wave's four groups are done
+        uint32_t le[R], prev[R];  // key u + s: its leaf; the leaf of the key before u
+        uint32_t rec[R];          // key u + s: found, and its slot
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint64_t u = ub + r * gs, e = u + static_cast<uint64_t>(s);
+            const bool in = e < U;
+            le[r] = in ? v.uleaf[e] : kNone;
+            rec[r] = in ? (v.ufound[e] ? 0x100u : 0u) | v.uslot[e] : 0u;
+            prev[r] = u < U && u > 0 ? v.uleaf[u - 1] : kNone;
+        }
+        K key[R], val[R];
+        uint32_t cnt[R], leaf[R];
+        bool head[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint64_t u = ub + r * gs;
+            leaf[r] = row_lane<0>(le[r]);
+            head[r] = u < U && (u == 0 || prev[r] != leaf[r]);  // the same for the group's 16 lanes
+            cnt[r] = 0;
+            key[r] = val[r] = K(0);
+            if (head[r]) {
+                cnt[r] = t.lmeta[leaf[r]].x;
+                key[r] = t.lkeys[static_cast<uint64_t>(leaf[r]) * kSlots + s];
+                val[r] = t.lvals[static_cast<uint64_t>(leaf[r]) * kSlots + s];
             }
-            const uint32_t c = t.lmeta[leaf].x;
-            const uint32_t w = c - nd;
+            if (u < U && s == 0 && !head[r]) v.nu[u] = 0u;  // only a run left below half full sets 1
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint64_t u = ub + r * gs;
+            uint32_t gone = 0, nd = 0;
+            {
+                uint32_t lx = le[r], rx = rec[r];
+                bool more = head[r];
+                for (uint64_t e0 = u; __ballot(more);) {
+                    const bool in = more && lx == leaf[r];
+                    const bool hit = in && (rx & 0x100u);
+                    const uint32_t bits = row_or(hit ? 1u << (rx & 0xFFu) : 0u);
+                    gone |= bits;
+                    nd += static_cast<uint32_t>(__popcll((__ballot(hit) >> gbase) & 0xFFFFull));
+                    more = ((__ballot(in) >> gbase) & 0xFFFFull) == 0xFFFFull;  // else the run ended here
+                    if (!__ballot(more)) break;
+                    e0 += kSlots;
+                    const uint64_t e = e0 + static_cast<uint64_t>(s);
+                    const bool ok = more && e < U;
+                    lx = ok ? v.uleaf[e] : kNone;
+                    rx = ok ? (v.ufound[e] ? 0x100u : 0u) | v.uslot[e] : 0u;
+                }
+            }
+            const uint32_t c = cnt[r], w = c - nd;
             const bool under = h > 1 && w < kHalf;
-            if (s == 0) {
+            if (head[r] && s == 0) {
                 v.f0[u] = under ? 1u : 0u;
                 v.nu[u] = under ? 1u : 0u;
             }
-            if (nd) {
-                K* kl = t.lkeys + static_cast<uint64_t>(leaf) * kSlots;
-                K* vl = t.lvals + static_cast<uint64_t>(leaf) * kSlots;
-                const K key = kl[s], val = vl[s];
-                const bool keep = static_cast<uint32_t>(s) < c && !((gone >> s) & 1u);
-                const uint32_t km = static_cast<uint32_t>((__ballot(keep) >> gbase) & 0xFFFFull);
-                const uint32_t at = static_cast<uint32_t>(__popc(km & ((1u << s) - 1u)));
-                // the new largest key: from the highest kept slot
-                const int top = km ? 31 - __clz(km) : 0;
-                const K pk = km ? static_cast<K>(__shfl(key, gbase + top, 64)) : kmax<K>();
-                if (keep) {
-                    kl[at] = key;
-                    vl[at] = val;
+            // slot s gets the pair of the s-th kept slot; past the count the
+            // last kept key with an all-ones value
+            const uint32_t km = ((1u << c) - 1u) & ~gone;  // c <= 16
+            const uint32_t want = static_cast<uint32_t>(s) < w ? static_cast<uint32_t>(s) : (w ? w - 1u : 0u);
+            uint32_t src = 0;  // the position of bit number `want` of km
+            {
+                uint32_t m = km, k = want;
+#pragma unroll
+                for (int half = 8; half > 0; half >>= 1) {
+                    const uint32_t lowc = static_cast<uint32_t>(__popc(m & ((1u << half) - 1u)));
+                    if (k >= lowc) {
+                        k -= lowc;
+                        m >>= half;
+                        src += static_cast<uint32_t>(half);
+                    }
                 }
-                if (static_cast<uint32_t>(s) >= w) {
-                    kl[s] = pk;
-                    vl[s] = kmax<K>();
-                }
-                if (s == 0) {
-                    t.lmeta[leaf].x = w;
+            }
+            const K mk = static_cast<K>(__shfl(key[r], gbase + static_cast<int>(src), 64));
+            const K mv = static_cast<K>(__shfl(val[r], gbase + static_cast<int>(src), 64));
+            if (head[r] && nd) {
+                const uint64_t line = static_cast<uint64_t>(leaf[r]) * kSlots + s;
+                t.lkeys[line] = w ? mk : kmax<K>();
+                t.lvals[line] = static_cast<uint32_t>(s) < w ? mv : kmax<K>();
+                if (static_cast<uint32_t>(s) == kSlots - 1) {  // this lane holds the new largest key
+                    t.lmeta[leaf[r]].x = w;
                     del += nd;
                     if (!under && w > 0 && ((gone >> (c - 1)) & 1u)) {
                         for (int l = h - 2; l >= 0; --l) {
                             const uint64_t o2 = static_cast<uint64_t>(l) * v.Bm + u;
                             if (v.pi[o2] + 1u < v.pc[o2]) {
-                                t.ikeys[static_cast<uint64_t>(v.pn[o2]) * kSlots + v.pi[o2]] = pk;
+                                t.ikeys[static_cast<uint64_t>(v.pn[o2]) * kSlots + v.pi[o2]] = mk;
                                 note_inner_write(v, l);
                                 break;
                             }
@@ -2131,14 +2177,25 @@ __device__ __forceinline__ void ph_del_leaf(TreeView<K> t, Ins<K> v) {
             }
         }
     }
-    // one add per wave
     for (int o = 32; o > 0; o >>= 1) del += static_cast<uint32_t>(__shfl_xor(static_cast<int>(del), o));
-    if (lane == 0 && del) atomicAdd(&v.st->deleted, del);
+    return del;
 }
 
-template <class K>
-__global__ __launch_bounds__(kBlk) void k_del_leaf(TreeView<K> t, Ins<K> v) {
-    ph_del_leaf<K>(t, v);
+// The workgroup's count goes to its own word of parts (the sort's second key
+// buffer, at least a word per workgroup), which the commit adds up: one add a
+// wave to a single word took 12 ns each, 390 of this kernel's 394 us for 2^20
+// keys on 2^24 (88 now).
+template <class K, int R>
+__global__ __launch_bounds__(kBlk) void k_del_leaf(TreeView<K> t, Ins<K> v, uint32_t* __restrict__ parts) {
+    __shared__ uint32_t s_del[kBlk / 64];
+    const uint32_t del = ph_del_leaf<K, R>(t, v);
+    if ((threadIdx.x & 63) == 0) s_del[threadIdx.x / 64] = del;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t d = 0;
+        for (int w = 0; w < kBlk / 64; ++w) d += s_del[w];
+        parts[blockIdx.x] = d;
+    }
 }
 
 // The leaf runs left below half full, listed for the merge pass: small
@@ -2496,12 +2553,11 @@ __global__ __launch_bounds__(1024) void k_del_merge2(TreeView<K> t, Ins<K> v) {
     ph_del_merge2<K>(t, v);
 }
 
-// Commit the count and the epoch, then refresh the top-levels mirror if a
+// Commit the count d of removed keys and the epoch, then refresh the top-levels mirror if a
 // mirrored node changed, else only its key count (one launch).
 template <class K, int NT>
-__device__ __forceinline__ void ph_del_commit(TreeView<K> t, Ins<K> v) {
+__device__ __forceinline__ void ph_del_commit(TreeView<K> t, Ins<K> v, uint32_t d) {
     if (threadIdx.x == 0 && !(t.hdr->error & kErrInternal)) {
-        const uint32_t d = counter(&v.st->deleted);
         if (d) {
             t.hdr->n_keys -= d;
             t.hdr->epoch += 1;
@@ -2515,9 +2571,17 @@ __device__ __forceinline__ void ph_del_commit(TreeView<K> t, Ins<K> v) {
     }
 }
 
+constexpr int kDelCommitBlock = 1024;
+
 template <class K>
-__global__ __launch_bounds__(256) void k_del_commit(TreeView<K> t, Ins<K> v, uint64_t* host_word, uint32_t seq) {
-    ph_del_commit<K, 256>(t, v);
+__global__ __launch_bounds__(kDelCommitBlock) void k_del_commit(TreeView<K> t, Ins<K> v,
+                                                                 const uint32_t* __restrict__ parts, uint32_t nparts,
+                                                                 uint64_t* host_word, uint32_t seq) {
+    __shared__ uint32_t sh[33];
+    uint32_t d = 0, all;
+    for (uint32_t i = threadIdx.x; i < nparts; i += kDelCommitBlock) d += parts[i];
+    block_excl_scan<uint32_t>(d, sh, &all);
+    ph_del_commit<K, kDelCommitBlock>(t, v, all);
     // the call's number and the rebuild flag (raised by the merge kernels
     // before this one), in one word, straight into host memory
     if (host_word && threadIdx.x == 0) {
@@ -2588,7 +2652,10 @@ __global__ __launch_bounds__(kDelOneBlock) void k_del_small(TreeView<K> t, Ins<K
     phase_boundary();
     ph_locate<K, 16, 1, 2, kDelOneBlock>(t, v, status);
     phase_boundary();
-    ph_del_leaf<K>(t, v);
+    {
+        const uint32_t del = ph_del_leaf<K, 1>(t, v);
+        if ((tid & 63) == 0 && del) atomicAdd(&v.st->deleted, del);
+    }
     phase_boundary();
     ph_del_list<K>(t, v);
     phase_boundary();
@@ -2596,7 +2663,7 @@ __global__ __launch_bounds__(kDelOneBlock) void k_del_small(TreeView<K> t, Ins<K
     phase_boundary();
     ph_del_merge2<K>(t, v);
     phase_boundary();
-    ph_del_commit<K, kDelOneBlock>(t, v);
+    ph_del_commit<K, kDelOneBlock>(t, v, counter(&v.st->deleted));
     // the call's number and the rebuild flag, in one word, straight into
     // host memory (the merges that raise the flag are behind the barriers
     // above): the host waits for this word rather than for the stream
@@ -2653,8 +2720,13 @@ const uint32_t* launch_delete(const TreeView<K>& t, const InsertCtx& c, const K*
         hipLaunchKernelGGL(k_del_unique<K>, dim3(gB), dim3(kBlk), 0, s, v, B);
     }
     launch_locate<K>(t, v, c.cfg, B, status, s);
-    const uint64_t gl = grid_for(B * kSlots, kBlk);
-    hipLaunchKernelGGL(k_del_leaf<K>, dim3(gl < 65536 ? static_cast<uint32_t>(gl) : 65536u), dim3(kBlk), 0, s, t, v);
+    // two keys in flight per lane group once every group of the grid has more
+    const uint32_t gl = grid_for(B * kSlots, kBlk);
+    uint32_t* parts = reinterpret_cast<uint32_t*>(v.sk2);
+    if (B >= 2ull * gl * (kBlk / kSlots))
+        hipLaunchKernelGGL((k_del_leaf<K, 2>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
+    else
+        hipLaunchKernelGGL((k_del_leaf<K, 1>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
     const bool ordered = B > kDelListScan;
     if (ordered) {
         scan_exclusive<uint32_t>(v.nu, v.nleaf, &v.st->merges, &v.st->U, B, v.scan_tmp, s);
@@ -2665,7 +2737,7 @@ const uint32_t* launch_delete(const TreeView<K>& t, const InsertCtx& c, const K*
     const uint32_t gm = B < 16384 ? static_cast<uint32_t>(B) : 16384u;
     hipLaunchKernelGGL(k_del_merge<K>, dim3(gm), dim3(64), 0, s, t, v, ordered);
     hipLaunchKernelGGL(k_del_merge2<K>, dim3(B < 256 ? static_cast<uint32_t>(B) : 256u), dim3(1024), 0, s, t, v);
-    hipLaunchKernelGGL(k_del_commit<K>, dim3(1), dim3(256), 0, s, t, v, host_word, seq);
+    hipLaunchKernelGGL(k_del_commit<K>, dim3(1), dim3(kDelCommitBlock), 0, s, t, v, parts, gl, host_word, seq);
     *flag_on_host = host_word != nullptr;
     return &v.st->rebuild;
 }
