@@ -481,17 +481,6 @@ __global__ void k_apply_updates(TreeView<K> t, Ins<K> v) {
         if (v.ufound[u]) t.lvals[static_cast<uint64_t>(v.uleaf[u]) * kSlots + v.uslot[u]] = v.uv[u];
 }
 
-// first index in a[0..n) whose key is >= k
-template <class K>
-__device__ __forceinline__ uint32_t lower_bound_dev(const K* a, uint32_t n, K k) {
-    uint32_t lo = 0, hi = n;
-    while (lo < hi) {
-        uint32_t mid = (lo + hi) >> 1;
-        if (a[mid] < k) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
 // part_start and part_of for the splits the rebuilds make: below 2^16
 // entries every product j * total fits in 32 bits, and a 32-bit division is
 // a few instructions where a 64-bit one is a long sequence (a rebuild makes
@@ -541,6 +530,145 @@ __device__ __forceinline__ ItemView items_in(const Ins<K>& v) {
     return ItemView{v.it_node, v.it_first, v.it_end, v.it_cold, v.it_k, v.it_off, v.it_cs};
 }
 
+// A leaf that does not split, so holds at most 16 entries in the end, by its
+// 16 lanes: lane q holds new pair q, a ballot per new key counts the old keys
+// below it, which gives its slot, and the merged lines are stored whole, each
+// lane picking the pair that comes to its slot.  (2^20 keys on 2^24: the leaf
+// kernel took 145 us when every leaf went the way of a split, whose moves,
+// compares and piece bounds, some 480 vector instructions per four leaves,
+// were its bound, and takes 104; two kernels, merges with two leaves in flight
+// and splits, took 81 + 27.)
+template <class K>
+__device__ __forceinline__ void merge_leaf(TreeView<K> t, uint32_t leaf, K okey, K oval, uint2 meta, uint32_t c,
+                                           const K* nk, const K* nv, uint32_t r, int gl, int gbase) {
+    const uint32_t total = c + r;
+    K mine = K(0), mval = K(0);
+    if (static_cast<uint32_t>(gl) < r) {
+        mine = nk[gl];
+        mval = nv[gl];
+    }
+    const bool old = static_cast<uint32_t>(gl) < c;
+    uint32_t newpos = 0;  // bit s: a new key comes to slot s
+    for (uint32_t q = 0; q < r; ++q) {
+        const K kq = static_cast<K>(__shfl(mine, gbase + static_cast<int>(q), 64));
+        const uint32_t m = static_cast<uint32_t>(group_bits<kNodeLanes>(__ballot(old && okey < kq), gbase));
+        newpos |= 1u << (q + static_cast<uint32_t>(__popc(m)));
+    }
+    // slot s: the new pair of rank #{new slots below s}, else the old pair of
+    // rank s less that; past the count the last pair's key
+    const uint32_t s = static_cast<uint32_t>(gl) < total ? static_cast<uint32_t>(gl) : total - 1u;
+    const uint32_t nb = static_cast<uint32_t>(__popc(newpos & ((1u << s) - 1u)));
+    const bool fresh = (newpos >> s) & 1u;
+    const int src = gbase + static_cast<int>(fresh ? nb : s - nb);
+    const K ko = static_cast<K>(__shfl(okey, src, 64)), kn = static_cast<K>(__shfl(mine, src, 64));
+    const K vo = static_cast<K>(__shfl(oval, src, 64)), vn = static_cast<K>(__shfl(mval, src, 64));
+    const uint64_t line = static_cast<uint64_t>(leaf) * kSlots + gl;
+    t.lkeys[line] = fresh ? kn : ko;
+    t.lvals[line] = static_cast<uint32_t>(gl) < total ? (fresh ? vn : vo) : kmax<K>();
+    if (gl == 0) t.lmeta[leaf] = make_uint2(total, meta.y);
+}
+
+// Item `it` of the leaf level by its lane group: merge, and split where the
+// leaf overflows.
+template <class K>
+__device__ __forceinline__ void apply_leaf(const TreeView<K>& t, const Ins<K>& v, uint64_t it, uint32_t alloc, int gl,
+                                           int gbase, const ItemView& iv) {
+    const uint32_t leaf = iv.node[it];
+    const uint32_t first = iv.first[it];
+    const uint32_t r = iv.end[it] - first;
+    const uint32_t c = iv.cold[it];
+    const uint32_t k = iv.k[it];
+    const uint32_t off = iv.off[it];
+    const uint32_t total = c + r;  // r is at most the batch size
+    const uint32_t base_new = alloc + off;
+    const K okey = t.lkeys[static_cast<uint64_t>(leaf) * kSlots + gl];
+    const K oval = t.lvals[static_cast<uint64_t>(leaf) * kSlots + gl];
+    const uint2 meta = t.lmeta[leaf];
+    __threadfence_block();  // the old leaf is in registers before any write
+    const K* nk = v.nk + first;
+    const K* nv = v.nv + first;
+    // the groups of a wave take one of the two ways on their own
+    if (k == 1) {
+        merge_leaf<K>(t, leaf, okey, oval, meta, c, nk, nv, r, gl, gbase);
+        return;
+    }
+    // one run of new keys (the common case): each lane holds at most one
+    // old and one new element, and the group pads the pieces together
+    const bool one_run = r <= static_cast<uint32_t>(kNodeLanes);
+    auto place = [&](uint32_t pos, K key, K val) {
+        const uint32_t j = ppart(pos, total, k);
+        const uint32_t s0 = pstart(j, total, k), s1 = pstart(j + 1, total, k);
+        const uint32_t slot = pos - s0;
+        const uint64_t dest = j == 0 ? leaf : base_new + j - 1;
+        t.lkeys[dest * kSlots + slot] = key;
+        t.lvals[dest * kSlots + slot] = val;
+        if (pos + 1 == s1) {
+            const uint32_t cnt = static_cast<uint32_t>(s1 - s0);
+            if (!one_run) {
+                for (uint32_t s = cnt; s < kSlots; ++s) {
+                    t.lkeys[dest * kSlots + s] = key;
+                    t.lvals[dest * kSlots + s] = kmax<K>();
+                }
+            }
+            const uint32_t nxt = (j + 1 < k) ? static_cast<uint32_t>(base_new + j) : meta.y;
+            t.lmeta[dest] = make_uint2(cnt, nxt);
+            if (j + 1 < k) v.psep[off + j] = key;
+        }
+    };
+    // new keys 16 at a time, the next ones' reads in flight: a new key goes
+    // behind its smaller old keys, and an old key behind the new keys that it
+    // is not below (their ranks tell; reading them again by a binary search
+    // of the run took six dependent reads)
+    const bool has_old = gl < static_cast<int>(c);
+    uint64_t npos = ~0ull;
+    K nkey = K(0);
+    uint32_t below = 0;
+    K key = static_cast<uint32_t>(gl) < r ? nk[gl] : K(0);
+    K val = static_cast<uint32_t>(gl) < r ? nv[gl] : K(0);
+    for (uint32_t q0 = 0; q0 < r; q0 += kNodeLanes) {
+        const uint32_t q = q0 + gl, qn = q + kNodeLanes;
+        const bool act = q < r;
+        const K key2 = qn < r ? nk[qn] : K(0), val2 = qn < r ? nv[qn] : K(0);
+        uint32_t rank = 0;
+        static_for<0, kNodeLanes>([&](auto S) {
+            const K ks = row_lane<decltype(S)::value>(okey);
+            rank += (static_cast<uint32_t>(decltype(S)::value) < c && ks < key) ? 1u : 0u;
+        });
+        const uint32_t rk = act ? rank : kNone;
+        static_for<0, kNodeLanes>(
+            [&](auto S) { below += row_lane<decltype(S)::value>(rk) <= static_cast<uint32_t>(gl) ? 1u : 0u; });
+        if (act) {
+            place(q + rank, key, val);
+            npos = q + rank;
+            nkey = key;
+        }
+        key = key2;
+        val = val2;
+    }
+    const uint64_t opos = has_old ? gl + static_cast<uint64_t>(below) : ~0ull;
+    if (has_old) place(static_cast<uint32_t>(opos), okey, oval);
+    if (one_run) {
+        // slots past a piece's count repeat its last key with an all-ones
+        // value: the piece's last element sits on one lane, as an old or
+        // a new element; lanes past the count write one slot each
+        for (uint32_t j = 0; j < k; ++j) {
+            const uint64_t s0 = pstart(j, total, k), s1 = pstart(j + 1, total, k);
+            const uint32_t cnt = static_cast<uint32_t>(s1 - s0);
+            if (cnt >= static_cast<uint32_t>(kSlots)) continue;
+            const uint64_t mo = group_bits<kNodeLanes>(__ballot(opos == s1 - 1), gbase);
+            const uint64_t mn = group_bits<kNodeLanes>(__ballot(npos == s1 - 1), gbase);
+            const K ko = __shfl(okey, gbase + (mo ? __builtin_ctzll(mo) : 0), 64);
+            const K kn = __shfl(nkey, gbase + (mn ? __builtin_ctzll(mn) : 0), 64);
+            const K lastk = mo ? ko : kn;
+            const uint64_t dest = j == 0 ? leaf : base_new + j - 1;
+            if (static_cast<uint32_t>(gl) >= cnt) {
+                t.lkeys[dest * kSlots + gl] = lastk;
+                t.lvals[dest * kSlots + gl] = kmax<K>();
+            }
+        }
+    }
+}
+
 template <class K>
 __device__ __forceinline__ void apply_leaves_body(TreeView<K> t, Ins<K> v, uint64_t grp, uint64_t ngrp,
                                                   const ItemView& iv) {
@@ -549,98 +677,7 @@ __device__ __forceinline__ void apply_leaves_body(TreeView<K> t, Ins<K> v, uint6
     if (!ok || T0 == 0) return;
     const int gl = lane_id() % kNodeLanes, gbase = lane_id() - gl;
     const uint32_t alloc = v.st->lvl_alloc[0];
-    for (uint64_t it = grp; it < T0; it += ngrp) {
-        const uint32_t leaf = iv.node[it];
-        const uint32_t first = iv.first[it];
-        const uint32_t r = iv.end[it] - first;
-        const uint32_t c = iv.cold[it];
-        const uint32_t k = iv.k[it];
-        const uint32_t off = iv.off[it];
-        const uint32_t total = c + r;  // r is at most the batch size
-        const uint32_t base_new = alloc + off;
-        const K okey = t.lkeys[static_cast<uint64_t>(leaf) * kSlots + gl];
-        const K oval = t.lvals[static_cast<uint64_t>(leaf) * kSlots + gl];
-        const uint2 meta = t.lmeta[leaf];
-        __threadfence_block();  // the old leaf is in registers before any write
-        const K* nk = v.nk + first;
-        const K* nv = v.nv + first;
-        // one run of new keys (the common case): each lane holds at most one
-        // old and one new element, and the group pads the pieces together
-        const bool one_run = r <= static_cast<uint32_t>(kNodeLanes);
-        auto place = [&](uint32_t pos, K key, K val) {
-            const uint32_t j = ppart(pos, total, k);
-            const uint32_t s0 = pstart(j, total, k), s1 = pstart(j + 1, total, k);
-            const uint32_t slot = pos - s0;
-            const uint64_t dest = j == 0 ? leaf : base_new + j - 1;
-            t.lkeys[dest * kSlots + slot] = key;
-            t.lvals[dest * kSlots + slot] = val;
-            if (pos + 1 == s1) {
-                const uint32_t cnt = static_cast<uint32_t>(s1 - s0);
-                if (!one_run) {
-                    for (uint32_t s = cnt; s < kSlots; ++s) {
-                        t.lkeys[dest * kSlots + s] = key;
-                        t.lvals[dest * kSlots + s] = kmax<K>();
-                    }
-                }
-                const uint32_t nxt = (j + 1 < k) ? static_cast<uint32_t>(base_new + j) : meta.y;
-                t.lmeta[dest] = make_uint2(cnt, nxt);
-                if (j + 1 < k) v.psep[off + j] = key;
-            }
-        };
-        const bool has_old = gl < static_cast<int>(c);
-        uint64_t opos = ~0ull;
-        if (one_run) {
-            // new keys below this lane's old key, from the group's lanes
-            // (a group is a row of 16 lanes: the moves are row broadcasts)
-            const K mine = static_cast<uint32_t>(gl) < r ? nk[gl] : K(0);
-            uint32_t below = 0;
-            static_for<0, kNodeLanes>([&](auto S) {
-                const K ks = row_lane<decltype(S)::value>(mine);
-                below += (static_cast<uint32_t>(decltype(S)::value) < r && ks < okey) ? 1u : 0u;
-            });
-            if (has_old) opos = gl + below;
-        } else if (has_old) {
-            opos = gl + lower_bound_dev(nk, r, okey);
-        }
-        if (has_old) place(opos, okey, oval);
-        uint64_t npos = ~0ull;
-        K nkey = K(0);
-        for (uint32_t q0 = 0; q0 < r; q0 += kNodeLanes) {
-            const uint32_t q = q0 + gl;
-            const bool act = q < r;
-            const K key = act ? nk[q] : K(0);
-            uint32_t rank = 0;
-            static_for<0, kNodeLanes>([&](auto S) {
-                const K ks = row_lane<decltype(S)::value>(okey);
-                rank += (static_cast<uint32_t>(decltype(S)::value) < c && ks < key) ? 1u : 0u;
-            });
-            if (act) {
-                place(q + rank, key, nv[q]);
-                npos = q + rank;
-                nkey = key;
-            }
-        }
-        if (one_run) {
-            // slots past a piece's count repeat its last key with an all-ones
-            // value: the piece's last element sits on one lane, as an old or
-            // a new element; lanes past the count write one slot each
-            for (uint32_t j = 0; j < k; ++j) {
-                const uint64_t s0 = pstart(j, total, k), s1 = pstart(j + 1, total, k);
-                const uint32_t cnt = static_cast<uint32_t>(s1 - s0);
-                if (cnt >= static_cast<uint32_t>(kSlots)) continue;
-                const uint64_t mo = group_bits<kNodeLanes>(__ballot(opos == s1 - 1), gbase);
-                const uint64_t mn = group_bits<kNodeLanes>(__ballot(npos == s1 - 1), gbase);
-                const K ko = __shfl(okey, gbase + (mo ? __builtin_ctzll(mo) : 0), 64);
-                const K kn = __shfl(nkey, gbase + (mn ? __builtin_ctzll(mn) : 0), 64);
-                const K lastk = mo ? ko : kn;
-                const uint64_t dest = j == 0 ? leaf : base_new + j - 1;
-                if (static_cast<uint32_t>(gl) >= cnt) {
-                    t.lkeys[dest * kSlots + gl] = lastk;
-                    t.lvals[dest * kSlots + gl] = kmax<K>();
-                }
-            }
-        }
-    }
+    for (uint64_t it = grp; it < T0; it += ngrp) apply_leaf<K>(t, v, it, alloc, gl, gbase, iv);
 }
 
 // Rebuild the changed parents of level d: kNodeLanes lanes per parent, group
