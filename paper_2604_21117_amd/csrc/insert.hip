@@ -70,12 +70,12 @@ template <class K>
 struct Ins {
     InsState* st;
     K* sk; K* sk2; uint32_t* si; uint32_t* si2; void* sort_tmp;
-    uint32_t* f0; uint32_t* f1; void* scan_tmp;
+    uint32_t* f0; uint32_t* f1;
     K* uk; K* uv; uint32_t* upos; uint32_t* uleaf; uint8_t* uslot; uint8_t* ufound;
     uint32_t* pn; uint8_t* pi; uint8_t* pc;  // per level: node, child slot taken, node's children
     uint8_t* ulc;                             // per distinct key: its leaf's key count
     K* nk; K* nv; uint32_t* nleaf; uint32_t* nu;
-    uint32_t* it_node; uint32_t* it_rep; uint32_t* it_first; uint32_t* it_end;
+    uint32_t* it_node; uint32_t* it_first; uint32_t* it_end;
     uint32_t* it_cold; uint32_t* it_k; uint32_t* it_off;
     uint8_t* it_cs;  // slot of the item's node in its parent
     K* psep;
@@ -125,7 +125,7 @@ static uint64_t carve(Ins<K>* v, uint8_t* base, uint64_t Bm, uint64_t leaf_cap, 
     x.sort_tmp = take(sort_tmp_bytes(Bm, sizeof(K)));
     x.f0 = reinterpret_cast<uint32_t*>(take((Bm + 1) * 4));
     x.f1 = reinterpret_cast<uint32_t*>(take((Bm + 1) * 4));
-    x.scan_tmp = take(scan_tmp_bytes(Bm + 1));
+    take(scan_tmp_bytes(Bm + 1));  // (unused: the sizes programs have computed stay)
     x.uk = reinterpret_cast<K*>(take(Bm * sizeof(K)));
     x.uv = reinterpret_cast<K*>(take(Bm * sizeof(K)));
     x.upos = reinterpret_cast<uint32_t*>(take(Bm * 4));
@@ -141,7 +141,7 @@ static uint64_t carve(Ins<K>* v, uint8_t* base, uint64_t Bm, uint64_t leaf_cap, 
     x.nleaf = reinterpret_cast<uint32_t*>(take(Bm * 4));
     x.nu = reinterpret_cast<uint32_t*>(take(Bm * 4));
     x.it_node = reinterpret_cast<uint32_t*>(take(ip * 4));
-    x.it_rep = reinterpret_cast<uint32_t*>(take(ip * 4));
+    take(ip * 4);  // (unused, as above)
     x.it_first = reinterpret_cast<uint32_t*>(take(ip * 4));
     x.it_end = reinterpret_cast<uint32_t*>(take(ip * 4));
     x.it_cold = reinterpret_cast<uint32_t*>(take(ip * 4));
@@ -167,34 +167,146 @@ uint64_t insert_scratch_bytes(uint64_t max_batch, int key_bytes, uint64_t leaf_c
 __device__ __forceinline__ uint64_t gtid() { return blockIdx.x * static_cast<uint64_t>(blockDim.x) + threadIdx.x; }
 __device__ __forceinline__ uint64_t gstride() { return static_cast<uint64_t>(gridDim.x) * blockDim.x; }
 
-// Clear the batch state (one workgroup).
-template <class K>
-__global__ void k_init(Ins<K> v, const DevHeader* hdr) {
-    uint32_t* s = reinterpret_cast<uint32_t*>(v.st);
-    for (uint32_t i = threadIdx.x; i < sizeof(InsState) / 4; i += blockDim.x) s[i] = 0;
-    __syncthreads();
-    if (threadIdx.x == 0) v.st->height = hdr->height;
+// ------------------------------------- chunks of a batch (above 2048 keys)
+//
+// The plan of a large batch is a row of counts and prefix sums: distinct keys,
+// new keys, the items of every level, the pieces of a level's items.  Each is
+// a pair of launches over the same chunks, contiguous runs of tiles of
+// kChTile entries, one workgroup each: the first leaves the chunk's total (in
+// `sums`), the second adds up the totals before it, scans its tiles and writes
+// what the prefix is for.  (Flags, a three-kernel scan and a kernel that used
+// it, per count and level, were some 70 launches of 2 to 7 us, 300 us of an
+// insert of 2^20 keys; these are 13 and take 100.)
+constexpr int kChBlock = 512;
+constexpr uint32_t kChItems = 4;                         // entries of a tile a thread takes, kChBlock apart
+constexpr uint32_t kChTile = kChBlock * kChItems;        // 2048
+constexpr uint32_t kChMax = 1024;                        // chunks at most
+
+struct Chunks {
+    uint32_t n, tiles;  // chunks, tiles of each
+};
+
+static Chunks chunks_for(uint64_t n) {
+    const uint64_t all = n ? (n + kChTile - 1) / kChTile : 1;
+    Chunks c;
+    c.n = static_cast<uint32_t>(all < kChMax ? all : kChMax);
+    c.tiles = static_cast<uint32_t>((all + c.n - 1) / c.n);
+    return c;
 }
 
-template <class K>
-__global__ void k_heads(Ins<K> v, uint64_t B, uint8_t* __restrict__ status) {
-    for (uint64_t p = gtid(); p < B; p += gstride()) {
-        const bool head = p == 0 || v.sk[p] != v.sk[p - 1];
-        v.f0[p] = head ? 1u : 0u;
-        if (!head) status[v.si[p]] = 1;  // UPDATED: an earlier occurrence exists
+// Total of x over the workgroup, in every thread.
+__device__ __forceinline__ uint32_t chunk_total(uint32_t x, uint32_t* sh) {
+    uint32_t all;
+    block_excl_scan<uint32_t>(x, sh, &all);
+    return all;
+}
+
+// The chunk totals before this chunk, and of all.
+__device__ __forceinline__ uint32_t chunk_before(const uint32_t* __restrict__ sums, uint32_t* sh, uint32_t* all) {
+    uint32_t pre = 0, tot = 0;
+    for (uint32_t i = threadIdx.x; i < gridDim.x; i += kChBlock) {
+        const uint32_t x = sums[i];
+        tot += x;
+        pre += i < blockIdx.x ? x : 0u;
     }
+    *all = chunk_total(tot, sh);
+    return chunk_total(pre, sh);
 }
 
+// Ranks within a tile: entry j * kChBlock + t is thread t's j-th, on[j] says
+// whether it counts.  rank[j]: the counted entries before it (entries kChBlock
+// apart, so that a wave reads and writes neighbours); returns how many count.
+// `cnt` holds a count per wave and j; two barriers.
+constexpr uint32_t kChWaves = kChBlock / 64;
+
+__device__ __forceinline__ uint32_t ch_rank(const bool (&on)[kChItems], uint32_t (&rank)[kChItems],
+                                            uint32_t (&cnt)[kChItems * kChWaves + 1]) {
+    const uint32_t w = threadIdx.x / 64, lane = threadIdx.x & 63;
+    uint64_t m[kChItems];
+#pragma unroll
+    for (uint32_t j = 0; j < kChItems; ++j) {
+        m[j] = __ballot(on[j]);
+        if (lane == 0) cnt[j * kChWaves + w] = static_cast<uint32_t>(__popcll(m[j]));
+    }
+    __syncthreads();
+    if (w == 0) {
+        const uint32_t x = lane < kChItems * kChWaves ? cnt[lane] : 0u, inc = wave_incl_scan(x);
+        if (lane < kChItems * kChWaves) cnt[lane] = inc - x;
+        if (lane == 63) cnt[kChItems * kChWaves] = inc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < kChItems; ++j)
+        rank[j] = cnt[j * kChWaves + w] + static_cast<uint32_t>(__popcll(m[j] & ((1ull << lane) - 1ull)));
+    return cnt[kChItems * kChWaves];
+}
+
+// Distinct keys of the sorted batch, counted: the heads of runs.  Repeats get
+// `repeat` as their status (the insert: UPDATED, an earlier occurrence exists;
+// the delete: ABSENT, an earlier one deleted it).  Also clears the batch state.
 template <class K>
-__global__ void k_unique(Ins<K> v, uint64_t B, const K* __restrict__ vals) {
-    for (uint64_t p = gtid(); p < B; p += gstride()) {
-        const uint32_t f = v.f0[p], e = v.f1[p];
-        if (f) {
-            v.uk[e] = v.sk[p];
-            v.upos[e] = static_cast<uint32_t>(p);
+__global__ __launch_bounds__(kChBlock) void k_ch_heads(Ins<K> v, const DevHeader* hdr, uint64_t B, uint32_t tiles,
+                                                        uint8_t repeat, uint8_t* __restrict__ status,
+                                                        uint32_t* __restrict__ sums) {
+    __shared__ uint32_t sh[33];
+    if (blockIdx.x == 0) {
+        uint32_t* s = reinterpret_cast<uint32_t*>(v.st);
+        for (uint32_t i = threadIdx.x; i < sizeof(InsState) / 4; i += kChBlock) s[i] = 0;
+        __syncthreads();
+        if (threadIdx.x == 0) v.st->height = hdr->height;
+    }
+    uint32_t n = 0;
+    for (uint32_t x = 0; x < tiles; ++x) {
+        const uint64_t p0 = (static_cast<uint64_t>(blockIdx.x) * tiles + x) * kChTile + threadIdx.x;
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) {
+            const uint64_t p = p0 + j * kChBlock;
+            if (p >= B) continue;
+            if (p == 0 || v.sk[p] != v.sk[p - 1]) ++n;
+            else status[v.si[p]] = repeat;
         }
-        const bool last = p + 1 == B || v.sk[p + 1] != v.sk[p];
-        if (last) v.uv[e + f - 1] = vals[v.si[p]];  // the run's last writer
+    }
+    n = chunk_total(n, sh);
+    if (threadIdx.x == 0) sums[blockIdx.x] = n;
+}
+
+// ... and written: the key, the place of its first occurrence and (with vals)
+// the value of its last.
+template <class K>
+__global__ __launch_bounds__(kChBlock) void k_ch_unique(Ins<K> v, uint64_t B, uint32_t tiles,
+                                                         const K* __restrict__ vals,
+                                                         const uint32_t* __restrict__ sums) {
+    __shared__ uint32_t sh[33], cnt[kChItems * kChWaves + 1];
+    uint32_t all, at = chunk_before(sums, sh, &all);
+    if (blockIdx.x == 0 && threadIdx.x == 0) v.st->U = all;
+    for (uint32_t x = 0; x < tiles; ++x) {
+        const uint64_t p0 = (static_cast<uint64_t>(blockIdx.x) * tiles + x) * kChTile + threadIdx.x;
+        K k[kChItems];
+        uint32_t rank[kChItems], i[kChItems];
+        bool on[kChItems], last[kChItems];
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) {
+            const uint64_t p = p0 + j * kChBlock;
+            k[j] = p < B ? v.sk[p] : K(0);
+            on[j] = p < B && (p == 0 || k[j] != v.sk[p - 1]);
+            last[j] = vals && p < B && (p + 1 == B || k[j] != v.sk[p + 1]);
+            i[j] = last[j] ? v.si[p] : 0u;
+        }
+        K val[kChItems];
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) val[j] = last[j] ? vals[i[j]] : K(0);
+        const uint32_t n = ch_rank(on, rank, cnt);
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) {
+            const uint32_t e = at + rank[j];
+            if (on[j]) {
+                v.uk[e] = k[j];
+                v.upos[e] = static_cast<uint32_t>(p0 + j * kChBlock);
+            }
+            if (last[j]) v.uv[e + (on[j] ? 1u : 0u) - 1u] = val[j];  // the run's last writer
+        }
+        at += n;
+        __syncthreads();
     }
 }
 
@@ -259,171 +371,310 @@ __global__ __launch_bounds__(kBlk) void k_locate(TreeView<K> t, Ins<K> v, uint8_
     ph_locate<K, G, QPG, LV, kBlk>(t, v, status);
 }
 
-template <class K>
-__device__ __forceinline__ void ph_compact_new(Ins<K> v, uint64_t tid, uint64_t nth) {
-    const uint64_t U = v.st->U;
-    for (uint64_t u = tid; u < U; u += nth) {
-        if (!v.ufound[u]) {
-            const uint32_t r = v.f1[u];
-            v.nk[r] = v.uk[u];
-            v.nv[r] = v.uv[u];
-            v.nleaf[r] = v.uleaf[u];
-            v.nu[r] = static_cast<uint32_t>(u);
+// Entries u < U that count: new keys (not found in their leaf), or, for the
+// delete, runs that left their leaf below half full.
+template <class K, bool NEW>
+__device__ __forceinline__ bool ch_counts(const Ins<K>& v, uint64_t u) {
+    if constexpr (NEW) return !v.ufound[u];
+    else return v.nu[u] != 0;
+}
+
+template <class K, bool NEW>
+__global__ __launch_bounds__(kChBlock) void k_ch_count(TreeView<K> t, Ins<K> v, uint32_t tiles,
+                                                        uint32_t* __restrict__ sums) {
+    __shared__ uint32_t sh[33];
+    const uint64_t U = !NEW && (t.hdr->error & kErrInternal) ? 0 : v.st->U;
+    uint32_t n = 0;
+    for (uint32_t x = 0; x < tiles; ++x) {
+        const uint64_t u0 = (static_cast<uint64_t>(blockIdx.x) * tiles + x) * kChTile + threadIdx.x;
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) {
+            const uint64_t u = u0 + j * kChBlock;
+            n += u < U && ch_counts<K, NEW>(v, u) ? 1u : 0u;
         }
+    }
+    n = chunk_total(n, sh);
+    if (threadIdx.x == 0) sums[blockIdx.x] = n;
+}
+
+// NEW: the new keys, in key order, with their leaf.  Else the delete's merge
+// list (f1), in key order.
+template <class K, bool NEW>
+__global__ __launch_bounds__(kChBlock) void k_ch_collect(TreeView<K> t, Ins<K> v, uint32_t tiles,
+                                                          const uint32_t* __restrict__ sums) {
+    __shared__ uint32_t sh[33], cnt[kChItems * kChWaves + 1];
+    const uint64_t U = !NEW && (t.hdr->error & kErrInternal) ? 0 : v.st->U;
+    uint32_t all, at = chunk_before(sums, sh, &all);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if constexpr (NEW) v.st->R = all;
+        else v.st->merges = all;
+    }
+    for (uint32_t x = 0; x < tiles; ++x) {
+        const uint64_t u0 = (static_cast<uint64_t>(blockIdx.x) * tiles + x) * kChTile + threadIdx.x;
+        bool on[kChItems];
+        uint32_t rank[kChItems];
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) {
+            const uint64_t u = u0 + j * kChBlock;
+            on[j] = u < U && ch_counts<K, NEW>(v, u);
+        }
+        const uint32_t n = ch_rank(on, rank, cnt);
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) {
+            if (!on[j]) continue;
+            const uint64_t u = u0 + j * kChBlock;
+            const uint32_t e = at + rank[j];
+            if constexpr (NEW) {
+                v.nk[e] = v.uk[u];
+                v.nv[e] = v.uv[u];
+                v.nleaf[e] = v.uleaf[u];
+                v.nu[e] = static_cast<uint32_t>(u);
+            } else {
+                v.f1[e] = static_cast<uint32_t>(u);
+            }
+        }
+        at += n;
+        __syncthreads();
     }
 }
 
+// Items of every level, counted: sums[chunk * kMaxLevels + level].  A run of
+// new keys through one node at a level is cut wherever a run below it is not,
+// so the levels at which key r starts an item, the leaves (level 0) first, are
+// 0 .. its depth - 1; the depth goes to f0[r].
 template <class K>
-__global__ void k_compact_new(Ins<K> v) {
-    ph_compact_new<K>(v, gtid(), gstride());
-}
-
-template <class K>
-__device__ __forceinline__ void ph_leaf_heads(Ins<K> v, uint64_t tid, uint64_t nth) {
+__global__ __launch_bounds__(kChBlock) void k_ch_level_count(Ins<K> v, uint32_t tiles, uint32_t* __restrict__ sums) {
+    __shared__ uint32_t s_n[kMaxLevels];
     const uint64_t R = v.st->R;
-    for (uint64_t r = tid; r < R; r += nth)
-        v.f0[r] = (r == 0 || v.nleaf[r] != v.nleaf[r - 1]) ? 1u : 0u;
+    const int h = static_cast<int>(v.st->height);
+    if (threadIdx.x < kMaxLevels) s_n[threadIdx.x] = 0;
+    __syncthreads();
+    for (uint32_t x = 0; x < tiles; ++x) {
+        const uint64_t r0 = (static_cast<uint64_t>(blockIdx.x) * tiles + x) * kChTile + threadIdx.x;
+        uint32_t dep[kChItems], u[kChItems], w[kChItems];
+        bool on[kChItems];  // still a start at level d
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) {
+            const uint64_t r = r0 + j * kChBlock;
+            const bool in = r < R, cmp = in && r > 0;
+            u[j] = cmp ? v.nu[r] : 0u;
+            w[j] = cmp ? v.nu[r - 1] : 0u;
+            on[j] = cmp && v.nleaf[r] != v.nleaf[r - 1];
+            dep[j] = in && r == 0 ? static_cast<uint32_t>(h) : (on[j] ? 1u : 0u);
+        }
+        for (int d = 1; d < h; ++d) {
+            const uint64_t at = static_cast<uint64_t>(h - 1 - d) * v.Bm;
+            uint32_t a[kChItems], b[kChItems];
+            bool any = false;
+#pragma unroll
+            for (uint32_t j = 0; j < kChItems; ++j) {
+                any = any || on[j];
+                a[j] = on[j] ? v.pn[at + u[j]] : 0u;
+                b[j] = on[j] ? v.pn[at + w[j]] : 0u;
+            }
+            if (!__ballot(any)) break;
+#pragma unroll
+            for (uint32_t j = 0; j < kChItems; ++j) {
+                on[j] = on[j] && a[j] != b[j];
+                dep[j] += on[j] ? 1u : 0u;
+            }
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j)
+            if (r0 + j * kChBlock < R) v.f0[r0 + j * kChBlock] = dep[j];
+        for (int d = 0; d < h; ++d) {
+            uint32_t n = 0;
+#pragma unroll
+            for (uint32_t j = 0; j < kChItems; ++j)
+                n += static_cast<uint32_t>(__popcll(__ballot(dep[j] > static_cast<uint32_t>(d))));
+            if (n && (threadIdx.x & 63) == 0) atomicAdd(&s_n[d], n);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kMaxLevels) sums[blockIdx.x * kMaxLevels + threadIdx.x] = s_n[threadIdx.x];
 }
 
+// ... and written: per item its node, its first child item (leaves: new key),
+// the node's entry count and its slot in its
+// parent, all recorded by locate; the end of the item before it.  The item
+// counts and pool bases of the levels go to the batch state.
 template <class K>
-__global__ void k_leaf_heads(Ins<K> v) {
-    ph_leaf_heads<K>(v, gtid(), gstride());
-}
-
-template <class K>
-__device__ __forceinline__ void ph_leaf_items(Ins<K> v, uint64_t tid, uint64_t nth) {
+__global__ __launch_bounds__(kChBlock) void k_ch_level_items(Ins<K> v, uint32_t tiles,
+                                                              const uint32_t* __restrict__ sums) {
+    __shared__ uint32_t s_at[kMaxLevels], s_all[kMaxLevels], s_base[kMaxLevels];
+    __shared__ uint32_t cnt[kMaxLevels][kChItems * kChWaves];
+    __shared__ uint32_t s_tot[kMaxLevels];
     const uint64_t R = v.st->R;
-    for (uint64_t r = tid; r < R; r += nth) {
-        const uint32_t f = v.f0[r], e = v.f1[r];
-        if (f) {
-            if (e >= v.ip_cap) { v.st->overflow = 1; continue; }
-            v.it_node[e] = v.nleaf[r];
-            v.it_rep[e] = v.nu[r];
-            v.it_first[e] = static_cast<uint32_t>(r);
-        }
-        if (r + 1 == R || v.f0[r + 1]) {
-            const uint32_t seg = e + f - 1;
-            if (seg < v.ip_cap) v.it_end[seg] = static_cast<uint32_t>(r + 1);
-        }
-    }
-}
-
-template <class K>
-__global__ void k_leaf_items(Ins<K> v) {
-    ph_leaf_items<K>(v, gtid(), gstride());
-}
-
-template <class K>
-__device__ __forceinline__ void ph_leaf_plan(TreeView<K> t, Ins<K> v, uint64_t tid, uint64_t nth) {
-    const uint64_t T0 = v.st->lvl_count[0];
     const int h = static_cast<int>(v.st->height);
-    for (uint64_t i = tid; i < T0; i += nth) {
-        if (h >= 2) v.it_cs[i] = v.pi[static_cast<uint64_t>(h - 2) * v.Bm + v.it_rep[i]];
-        const uint32_t c = t.lmeta[v.it_node[i]].x;
-        const uint64_t total = static_cast<uint64_t>(c) + (v.it_end[i] - v.it_first[i]);
-        const uint32_t k = split_pieces(total);
-        v.it_cold[i] = c;
-        v.it_k[i] = k;
-        v.f0[i] = k - 1;
-    }
-}
-
-template <class K>
-__global__ void k_leaf_plan(TreeView<K> t, Ins<K> v) {
-    ph_leaf_plan<K>(t, v, gtid(), gstride());
-}
-
-// heads of the level-d items: runs of level-(d-1) items with the same parent
-template <class K>
-__device__ __forceinline__ void ph_par_heads(Ins<K> v, int d, uint64_t tid, uint64_t nth) {
-    const int h = static_cast<int>(v.st->height);
-    const int l = h - 1 - d;  // parent level, 0 = root level
-    const uint64_t n = v.st->lvl_count[d - 1];
-    const uint32_t b = v.st->lvl_base[d - 1];
-    if (tid == 0) {
-        v.st->lvl_base[d] = b + v.st->lvl_count[d - 1];
-        v.st->lvl_psep[d] = v.st->lvl_psep[d - 1] + v.st->lvl_new[d - 1];
-    }
-    for (uint64_t i = tid; i < n; i += nth) {
-        uint32_t f = 0;
-        if (l >= 0) {
-            const uint32_t p = v.pn[static_cast<uint64_t>(l) * v.Bm + v.it_rep[b + i]];
-            f = (i == 0 || p != v.pn[static_cast<uint64_t>(l) * v.Bm + v.it_rep[b + i - 1]]) ? 1u : 0u;
+    // the totals before this chunk and of all, every level in one pass
+    static_assert(kChBlock % kMaxLevels == 0, "a thread stays with its level");
+    if (threadIdx.x < kMaxLevels) s_at[threadIdx.x] = s_all[threadIdx.x] = 0;
+    __syncthreads();
+    {
+        uint32_t pre = 0, tot = 0;
+        for (uint32_t i = threadIdx.x; i < gridDim.x * kMaxLevels; i += kChBlock) {
+            const uint32_t n = sums[i];
+            tot += n;
+            pre += i / kMaxLevels < blockIdx.x ? n : 0u;
         }
-        v.f0[i] = f;
+        atomicAdd(&s_at[threadIdx.x % kMaxLevels], pre);
+        atomicAdd(&s_all[threadIdx.x % kMaxLevels], tot);
     }
-}
-
-template <class K>
-__global__ void k_par_heads(Ins<K> v, int d) {
-    ph_par_heads<K>(v, d, gtid(), gstride());
-}
-
-template <class K>
-__device__ __forceinline__ void ph_par_items(Ins<K> v, int d, uint64_t tid, uint64_t nth) {
-    const int h = static_cast<int>(v.st->height);
-    const int l = h - 1 - d;
-    if (l < 0) return;
-    const uint64_t n = v.st->lvl_count[d - 1];
-    const uint32_t b = v.st->lvl_base[d - 1];
-    const uint32_t bd = v.st->lvl_base[d];
-    for (uint64_t i = tid; i < n; i += nth) {
-        const uint32_t f = v.f0[i], e = v.f1[i];
-        if (f) {
-            if (bd + e >= v.ip_cap) { v.st->overflow = 1; continue; }
-            v.it_node[bd + e] = v.pn[static_cast<uint64_t>(l) * v.Bm + v.it_rep[b + i]];
-            v.it_rep[bd + e] = v.it_rep[b + i];
-            v.it_first[bd + e] = static_cast<uint32_t>(i);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t base = 0;
+        for (int d = 0; d < h; ++d) {
+            s_base[d] = base;
+            if (blockIdx.x == 0) {
+                v.st->lvl_count[d] = s_all[d];
+                v.st->lvl_base[d] = base;
+                // the last item of a level ends where the level below does
+                const uint64_t e = static_cast<uint64_t>(base) + s_all[d] - 1;
+                if (s_all[d] && e < v.ip_cap) v.it_end[e] = d ? s_all[d - 1] : static_cast<uint32_t>(R);
+            }
+            base += s_all[d];
         }
-        if (i + 1 == n || v.f0[i + 1]) {
-            const uint32_t seg = e + f - 1;
-            if (bd + seg < v.ip_cap) v.it_end[bd + seg] = static_cast<uint32_t>(i + 1);
+        if (blockIdx.x == 0 && base > v.ip_cap) v.st->overflow = 1;
+    }
+    __syncthreads();
+    for (uint32_t x = 0; x < tiles; ++x) {
+        const uint64_t r0 = (static_cast<uint64_t>(blockIdx.x) * tiles + x) * kChTile + threadIdx.x;
+        const uint32_t w = threadIdx.x / 64, lane = threadIdx.x & 63;
+        const uint64_t lt = (1ull << lane) - 1ull;
+        uint32_t dep[kChItems];
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j)
+            dep[j] = r0 + j * kChBlock < R ? v.f0[r0 + j * kChBlock] : 0u;
+        // the counts of every level at once (ch_rank's, a wave per level)
+        for (int d = 0; d < h; ++d)
+#pragma unroll
+            for (uint32_t j = 0; j < kChItems; ++j) {
+                const uint64_t m = __ballot(dep[j] > static_cast<uint32_t>(d));
+                if (lane == 0) cnt[d][j * kChWaves + w] = static_cast<uint32_t>(__popcll(m));
+            }
+        __syncthreads();
+        for (int d = static_cast<int>(w); d < h; d += kChWaves) {
+            const uint32_t n = lane < kChItems * kChWaves ? cnt[d][lane] : 0u, inc = wave_incl_scan(n);
+            if (lane < kChItems * kChWaves) cnt[d][lane] = inc - n;
+            if (lane == 63) s_tot[d] = inc;
+        }
+        __syncthreads();
+        uint32_t below[kChItems];  // the keys' items a level down
+        uint32_t u[kChItems], node[kChItems], cold[kChItems], cs[kChItems];
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) {
+            below[j] = static_cast<uint32_t>(r0 + j * kChBlock);
+            u[j] = dep[j] ? v.nu[below[j]] : 0u;
+        }
+        for (int d = 0; d < h; ++d) {
+            const uint64_t at = static_cast<uint64_t>(d ? h - 1 - d : 0) * v.Bm;
+            uint32_t ix[kChItems];
+            uint64_t any = 0;
+#pragma unroll
+            for (uint32_t j = 0; j < kChItems; ++j) {
+                const bool head = dep[j] > static_cast<uint32_t>(d);
+                const uint64_t m = __ballot(head);
+                any |= m;
+                ix[j] = s_at[d] + cnt[d][j * kChWaves + w] + static_cast<uint32_t>(__popcll(m & lt));
+                node[j] = cold[j] = cs[j] = 0;
+                if (head) {
+                    node[j] = d ? v.pn[at + u[j]] : v.nleaf[below[j]];
+                    cold[j] = d ? v.pc[at + u[j]] : v.ulc[u[j]];
+                    if (h - 2 - d >= 0) cs[j] = v.pi[static_cast<uint64_t>(h - 2 - d) * v.Bm + u[j]];
+                }
+            }
+            if (!any) break;  // no key of the wave starts an item here or above
+#pragma unroll
+            for (uint32_t j = 0; j < kChItems; ++j) {
+                const uint64_t e = static_cast<uint64_t>(s_base[d]) + ix[j];
+                if (dep[j] > static_cast<uint32_t>(d) && e < v.ip_cap) {
+                    v.it_node[e] = node[j];
+                    v.it_cold[e] = cold[j];
+                    v.it_cs[e] = static_cast<uint8_t>(cs[j]);
+                    v.it_first[e] = below[j];
+                    if (ix[j] > 0) v.it_end[e - 1] = below[j];
+                }
+                below[j] = ix[j];
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x < static_cast<uint32_t>(h)) s_at[threadIdx.x] += s_tot[threadIdx.x];
+        __syncthreads();
+    }
+}
+
+// Pieces of item i of level d: the entries it had and those it gains -- its
+// new keys (leaves), or one per piece beyond the first of its child items, a
+// difference of the child level's piece offsets.
+template <class K>
+__device__ __forceinline__ uint32_t item_pieces(const Ins<K>& v, int d, uint32_t i) {
+    const uint32_t at = v.st->lvl_base[d] + i, first = v.it_first[at], end = v.it_end[at];
+    uint64_t gain = end - first;
+    if (d > 0) {
+        const uint32_t bc = v.st->lvl_base[d - 1], nc = v.st->lvl_count[d - 1], all = v.st->lvl_new[d - 1];
+        const uint32_t lo = v.it_off[bc + first], hi = end < nc ? v.it_off[bc + end] : all;
+        gain = hi - lo;
+    }
+    return split_pieces(v.it_cold[at] + gain);
+}
+
+template <class K>
+__global__ __launch_bounds__(kChBlock) void k_ch_pieces(Ins<K> v, int d, uint32_t tiles, uint32_t* __restrict__ sums) {
+    __shared__ uint32_t sh[33];
+    const uint32_t n = v.st->overflow ? 0u : v.st->lvl_count[d], base = v.st->lvl_base[d];
+    uint32_t extra = 0;
+    for (uint32_t x = 0; x < tiles; ++x) {
+        const uint64_t i0 = (static_cast<uint64_t>(blockIdx.x) * tiles + x) * kChTile;
+        if (i0 >= n) break;
+#pragma unroll
+        for (uint32_t j = 0; j < kChItems; ++j) {
+            const uint64_t i = i0 + j * kChBlock + threadIdx.x;
+            if (i >= n) continue;
+            const uint32_t k = item_pieces<K>(v, d, static_cast<uint32_t>(i));
+            v.it_k[base + i] = k;
+            extra += k - 1;
         }
     }
+    extra = chunk_total(extra, sh);
+    if (threadIdx.x == 0) sums[blockIdx.x] = extra;
 }
 
-template <class K>
-__global__ void k_par_items(Ins<K> v, int d) {
-    ph_par_items<K>(v, d, gtid(), gstride());
-}
-
-template <class K>
-__device__ __forceinline__ void ph_par_plan(TreeView<K> t, Ins<K> v, int d, uint64_t tid, uint64_t nth) {
-    const uint64_t n = v.st->lvl_count[d];
-    const uint32_t bd = v.st->lvl_base[d];
-    const uint32_t bc = v.st->lvl_base[d - 1];
-    const int lp = static_cast<int>(v.st->height) - 2 - d;  // tree level of the items' parents
-    for (uint64_t j = tid; j < n; j += nth) {
-        if (lp >= 0) v.it_cs[bd + j] = v.pi[static_cast<uint64_t>(lp) * v.Bm + v.it_rep[bd + j]];
-        const uint32_t node = v.it_node[bd + j];
-        uint32_t C = 0;
-        const uint32_t* ch = t.ichild + static_cast<uint64_t>(node) * kSlots;
-        for (int s = 0; s < kSlots; ++s) C += ch[s] != kNone ? 1u : 0u;
-        uint64_t a = 0;
-        for (uint32_t i = v.it_first[bd + j]; i < v.it_end[bd + j]; ++i) a += v.it_k[bc + i] - 1;
-        const uint32_t k = split_pieces(C + a);
-        v.it_cold[bd + j] = C;
-        v.it_k[bd + j] = k;
-        v.f0[j] = k - 1;
+// The scan of one tile's extra pieces from `at` on into it_off.
+template <class K, int NT>
+__device__ __forceinline__ uint32_t piece_offsets(const Ins<K>& v, uint32_t base, uint64_t i0, uint32_t n, uint32_t at,
+                                                  uint32_t* sh) {
+    uint32_t f[kChItems], sum = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kChItems; ++j) {
+        f[j] = i0 + j < n ? v.it_k[base + i0 + j] - 1u : 0u;
+        sum += f[j];
     }
+    uint32_t tot;
+    uint32_t off = at + block_excl_scan<uint32_t>(sum, sh, &tot);
+#pragma unroll
+    for (uint32_t j = 0; j < kChItems; ++j)
+        if (i0 + j < n) {
+            v.it_off[base + i0 + j] = off;
+            off += f[j];
+        }
+    return tot;
 }
 
 template <class K>
-__global__ void k_par_plan(TreeView<K> t, Ins<K> v, int d) {
-    ph_par_plan<K>(t, v, d, gtid(), gstride());
-}
-
-// this level's allocation offsets, moved to the level's slice of the pool
-template <class K>
-__device__ __forceinline__ void ph_par_off(Ins<K> v, int d, uint64_t tid, uint64_t nth) {
-    const uint64_t n = v.st->lvl_count[d];
-    const uint32_t bd = v.st->lvl_base[d];
-    for (uint64_t j = tid; j < n; j += nth) v.it_off[bd + j] = v.f1[j];
-}
-
-template <class K>
-__global__ void k_par_off(Ins<K> v, int d) {
-    ph_par_off<K>(v, d, gtid(), gstride());
+__global__ __launch_bounds__(kChBlock) void k_ch_offsets(Ins<K> v, int d, uint32_t tiles,
+                                                          const uint32_t* __restrict__ sums) {
+    __shared__ uint32_t sh[33];
+    const uint32_t n = v.st->overflow ? 0u : v.st->lvl_count[d], base = v.st->lvl_base[d];
+    uint32_t all, at = chunk_before(sums, sh, &all);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        v.st->lvl_new[d] = all;
+        v.st->lvl_psep[d] = d ? v.st->lvl_psep[d - 1] + v.st->lvl_new[d - 1] : 0u;
+    }
+    for (uint32_t x = 0; x < tiles; ++x) {
+        const uint64_t i0 = (static_cast<uint64_t>(blockIdx.x) * tiles + x) * kChTile;
+        if (i0 >= n) break;
+        at += piece_offsets<K, kChBlock>(v, base, i0 + threadIdx.x * kChItems, n, at, sh);
+    }
 }
 
 // Capacity check and allocation bases (one thread).
@@ -466,11 +717,6 @@ __device__ __forceinline__ void ph_check(TreeView<K> t, Ins<K> v, uint64_t tid, 
         cur += st->lvl_new[d];
     }
     st->new_root = cur;  // first growth node id
-}
-
-template <class K>
-__global__ void k_check(TreeView<K> t, Ins<K> v) {
-    ph_check<K>(t, v, gtid(), gstride());
 }
 
 template <class K>
@@ -876,47 +1122,28 @@ __device__ __forceinline__ void ph_commit(TreeView<K> t, Ins<K> v) {
     reinterpret_cast<MirrorHeader*>(t.mirror)->n_keys = hdr->n_keys;
 }
 
-// The upper levels of a large batch's plan in one workgroup: from level d0
-// on, every level below holds at most kTailMax items (the pool's per-level
-// bound), so the phases run back to back with block scans in LDS where the
-// lower levels have kernel boundaries and device-wide scans.
-constexpr uint32_t kTailMax = 2048;
+// The upper levels of a large batch's plan, from d0 on, and the capacity check
+// in one workgroup, tile after tile.
 constexpr int kTailBlock = 1024;
 
-// exclusive scan of in[0..n) (n <= 2 * blockDim.x) into out, total to *tot
-__device__ __forceinline__ void tail_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tot,
-                                          uint32_t* sh) {
-    const uint32_t i0 = 2 * threadIdx.x, i1 = i0 + 1;
-    const uint32_t a = i0 < n ? in[i0] : 0u, b = i1 < n ? in[i1] : 0u;
-    uint32_t total;
-    const uint32_t off = block_excl_scan<uint32_t>(a + b, sh, &total);
-    if (i0 < n) out[i0] = off;
-    if (i1 < n) out[i1] = off + a;
-    if (threadIdx.x == 0) *tot = total;
-    __syncthreads();
-}
-
 template <class K>
-__global__ __launch_bounds__(kTailBlock) void k_plan_tail(TreeView<K> t, Ins<K> v0, int d0, int H) {
+__global__ __launch_bounds__(kTailBlock) void k_plan_tail(TreeView<K> t, Ins<K> v, int d0) {
     __shared__ uint32_t sh[33];
-    __shared__ uint32_t sf0[kTailMax + 1], sf1[kTailMax + 1];
-    Ins<K> v = v0;
-    v.f0 = sf0;
-    v.f1 = sf1;
-    const uint64_t tid = threadIdx.x, nth = blockDim.x;
     const int h = static_cast<int>(v.st->height);
-    for (int d = d0; d < H && d < h; ++d) {
-        ph_par_heads<K>(v, d, tid, nth);
+    for (int d = d0; d < h && !v.st->overflow; ++d) {
+        const uint32_t n = v.st->lvl_count[d], base = v.st->lvl_base[d];
+        for (uint32_t i = threadIdx.x; i < n; i += kTailBlock) v.it_k[base + i] = item_pieces<K>(v, d, i);
         __syncthreads();
-        tail_scan(v.f0, v.f1, v.st->lvl_count[d - 1], &v.st->lvl_count[d], sh);
-        ph_par_items<K>(v, d, tid, nth);
-        __syncthreads();
-        ph_par_plan<K>(t, v, d, tid, nth);
-        __syncthreads();
-        tail_scan(v.f0, v.f1, v.st->lvl_count[d], &v.st->lvl_new[d], sh);
-        ph_par_off<K>(v, d, tid, nth);
+        uint32_t at = 0;
+        for (uint64_t i0 = 0; i0 < n; i0 += kTailBlock * kChItems)
+            at += piece_offsets<K, kTailBlock>(v, base, i0 + threadIdx.x * kChItems, n, at, sh);
+        if (threadIdx.x == 0) {
+            v.st->lvl_new[d] = at;
+            v.st->lvl_psep[d] = d ? v.st->lvl_psep[d - 1] + v.st->lvl_new[d - 1] : 0u;
+        }
         __syncthreads();
     }
+    ph_check<K>(t, v, threadIdx.x, kTailBlock);
 }
 
 // The batch state from device memory into LDS or back, by threads tid of nth
@@ -1492,7 +1719,6 @@ __device__ __forceinline__ void ph_small_plan(TreeView<K> t, Ins<K> v, int H) {
             if (hd[j]) {
                 if (e < v.ip_cap) {
                     v.it_node[e] = node[j];
-                    v.it_rep[e] = nu[j];
                     v.it_first[e] = ixp[j];
                     v.it_cold[e] = cnt[j];
                     v.it_cs[e] = static_cast<uint8_t>(cs[j]);
@@ -1689,8 +1915,7 @@ __device__ __forceinline__ void ph_fused_plan(TreeView<K> t, Ins<K> v, int H, co
         s_base[hmax] = items;
     }
     __syncthreads();
-    // the item arrays: node, representative key, range of child items (keys
-    // at the leaves), old entry count, slot in the parent
+    // the item arrays: node, range of child items (keys at the leaves), old entry count, slot in the parent
     if (valid) {
         const uint64_t e = static_cast<uint64_t>(s_base[d]) + ix;
         const uint32_t ixp = d == 0 ? r : s_ix[d - 1][r];
@@ -1699,7 +1924,6 @@ __device__ __forceinline__ void ph_fused_plan(TreeView<K> t, Ins<K> v, int H, co
                 const uint32_t cnt = d == 0 ? rec.ulc[nu] : rec.pc[h - 1 - d][nu];
                 const uint32_t cs = h - 2 - d >= 0 ? rec.pi[h - 2 - d][nu] : 0u;
                 v.it_node[e] = node;
-                v.it_rep[e] = nu;
                 v.it_first[e] = ixp;
                 v.it_cold[e] = cnt;
                 v.it_cs[e] = static_cast<uint8_t>(cs);
@@ -1959,35 +2183,25 @@ void launch_insert(const TreeView<K>& t, const InsertCtx& c, const K* keys, cons
         else launch_apply<K>(t, v, B, c.leaf_cap, H, false, s);  // the plan wrote the updates
         return;
     }
-    hipLaunchKernelGGL(k_init<K>, dim3(1), dim3(kBlk), 0, s, v, t.hdr);
     sort_from<K>(keys, v.sk, v.si, v.sk2, v.si2, B, v.sort_tmp, s, &t.hdr->error, kErrInternal);
-    hipLaunchKernelGGL(k_heads<K>, dim3(gB), dim3(kBlk), 0, s, v, B, status);
-    scan_exclusive<uint32_t>(v.f0, v.f1, &st->U, nullptr, B, v.scan_tmp, s);
-    hipLaunchKernelGGL(k_unique<K>, dim3(gB), dim3(kBlk), 0, s, v, B, vals);
+    uint32_t* sums = v.f1;  // a word per chunk and level: 16 per 2048 keys at most
+    const Chunks cb = chunks_for(B);
+    hipLaunchKernelGGL(k_ch_heads<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, t.hdr, B, cb.tiles, uint8_t(1), status, sums);
+    hipLaunchKernelGGL(k_ch_unique<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, B, cb.tiles, vals, sums);
     launch_locate<K>(t, v, c.cfg, B, status, s);
-    scan_exclusive<uint32_t>(v.f0, v.f1, &st->R, &st->U, B, v.scan_tmp, s);
-    hipLaunchKernelGGL(k_compact_new<K>, dim3(gB), dim3(kBlk), 0, s, v);
-    hipLaunchKernelGGL(k_leaf_heads<K>, dim3(gB), dim3(kBlk), 0, s, v);
-    scan_exclusive<uint32_t>(v.f0, v.f1, &st->lvl_count[0], &st->R, B, v.scan_tmp, s);
-    hipLaunchKernelGGL(k_leaf_items<K>, dim3(gB), dim3(kBlk), 0, s, v);
-    hipLaunchKernelGGL(k_leaf_plan<K>, dim3(gB), dim3(kBlk), 0, s, t, v);
-    scan_exclusive<uint32_t>(v.f0, v.it_off, &st->lvl_new[0], &st->lvl_count[0], B, v.scan_tmp, s);
-    // lower levels: kernels sized by the level's bound; from d0 on (the
-    // level below holds at most kTailMax items) one workgroup plans the rest
-    int d0 = 1;
-    while (d0 < H && level_items_bound(B, c.leaf_cap, d0 - 1) > kTailMax) ++d0;
-    for (int d = 1; d < d0; ++d) {
-        const uint64_t nb = level_items_bound(B, c.leaf_cap, d - 1), nd = level_items_bound(B, c.leaf_cap, d);
-        const uint32_t gb = grid_for(nb, kBlk), gd = grid_for(nd, kBlk);
-        hipLaunchKernelGGL(k_par_heads<K>, dim3(gb), dim3(kBlk), 0, s, v, d);
-        scan_exclusive<uint32_t>(v.f0, v.f1, &st->lvl_count[d], &st->lvl_count[d - 1], nb, v.scan_tmp, s);
-        hipLaunchKernelGGL(k_par_items<K>, dim3(gb), dim3(kBlk), 0, s, v, d);
-        hipLaunchKernelGGL(k_par_plan<K>, dim3(gd), dim3(kBlk), 0, s, t, v, d);
-        scan_exclusive<uint32_t>(v.f0, v.f1, &st->lvl_new[d], &st->lvl_count[d], nd, v.scan_tmp, s);
-        hipLaunchKernelGGL(k_par_off<K>, dim3(gd), dim3(kBlk), 0, s, v, d);
+    hipLaunchKernelGGL((k_ch_count<K, true>), dim3(cb.n), dim3(kChBlock), 0, s, t, v, cb.tiles, sums);
+    hipLaunchKernelGGL((k_ch_collect<K, true>), dim3(cb.n), dim3(kChBlock), 0, s, t, v, cb.tiles, sums);
+    hipLaunchKernelGGL(k_ch_level_count<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, cb.tiles, sums);
+    hipLaunchKernelGGL(k_ch_level_items<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, cb.tiles, sums);
+    // the pieces of the lower levels by chunks, of the others in one workgroup:
+    // a tree level has at most an eighth of the nodes of the one below
+    const int d0 = B <= 8192 ? 0 : (B <= 65536 ? 1 : 3);
+    for (int d = 0; d < d0; ++d) {
+        const Chunks cd = chunks_for(level_items_bound(B, c.leaf_cap, d));
+        hipLaunchKernelGGL(k_ch_pieces<K>, dim3(cd.n), dim3(kChBlock), 0, s, v, d, cd.tiles, sums);
+        hipLaunchKernelGGL(k_ch_offsets<K>, dim3(cd.n), dim3(kChBlock), 0, s, v, d, cd.tiles, sums);
     }
-    if (d0 < H) hipLaunchKernelGGL(k_plan_tail<K>, dim3(1), dim3(kTailBlock), 0, s, t, v, d0, H);
-    hipLaunchKernelGGL(k_check<K>, dim3(1), dim3(64), 0, s, t, v);
+    hipLaunchKernelGGL(k_plan_tail<K>, dim3(1), dim3(kTailBlock), 0, s, t, v, d0);
     launch_apply<K>(t, v, B, c.leaf_cap, H, true, s);
 }
 
@@ -2036,25 +2250,6 @@ __device__ __forceinline__ void note_inner_write(const Ins<K>& v, int depth) {
     if (depth < kMirrorDepth) v.st->mirror_dirty = 1u;
 }
 constexpr uint64_t kDelListScan = 16384;  // above: the merge list comes from a scan, in key order
-
-template <class K>
-__global__ void k_del_heads(Ins<K> v, uint64_t B, uint8_t* __restrict__ status) {
-    for (uint64_t p = gtid(); p < B; p += gstride()) {
-        const bool head = p == 0 || v.sk[p] != v.sk[p - 1];
-        v.f0[p] = head ? 1u : 0u;
-        if (!head) status[v.si[p]] = 0;  // ABSENT: an earlier occurrence deleted it
-    }
-}
-
-template <class K>
-__global__ void k_del_unique(Ins<K> v, uint64_t B) {
-    for (uint64_t p = gtid(); p < B; p += gstride()) {
-        if (v.f0[p]) {
-            v.uk[v.f1[p]] = v.sk[p];
-            v.upos[v.f1[p]] = static_cast<uint32_t>(p);
-        }
-    }
-}
 
 // Batches up to 2048 keys (after the rank sort, which also cleared the
 // batch state): one workgroup, two sorted positions per thread, finds the
@@ -2249,14 +2444,6 @@ __device__ __forceinline__ void ph_del_list(TreeView<K> t, Ins<K> v) {
 template <class K>
 __global__ void k_del_list(TreeView<K> t, Ins<K> v) {
     ph_del_list<K>(t, v);
-}
-
-template <class K>
-__global__ void k_del_list_ordered(TreeView<K> t, Ins<K> v) {
-    if (t.hdr->error & kErrInternal) return;
-    const uint64_t U = v.st->U;
-    for (uint64_t u = gtid(); u < U; u += gstride())
-        if (v.nu[u]) v.f1[v.nleaf[u]] = static_cast<uint32_t>(u);
 }
 
 // A wave's LDS for merging one listed parent.
@@ -2737,6 +2924,8 @@ const uint32_t* launch_delete(const TreeView<K>& t, const InsertCtx& c, const K*
     Ins<K> v;
     carve<K>(&v, c.scratch, c.max_batch, c.leaf_cap, c.inner_cap);
     const uint32_t gB = grid_for(B, kBlk);
+    const Chunks cb = chunks_for(B);
+    uint32_t* sums = reinterpret_cast<uint32_t*>(v.nk);  // (f1 holds the merge list)
     if (B <= kDelFusedMax && one_launch_delete_on()) {
         const uint32_t lds = MirrorLayout<K>::bytes(mirror_nodes_for_levels(2));
         hipLaunchKernelGGL(k_del_small<K>, dim3(1), dim3(kDelOneBlock), lds, s, t, v, keys,
@@ -2750,11 +2939,11 @@ const uint32_t* launch_delete(const TreeView<K>& t, const InsertCtx& c, const K*
         hipLaunchKernelGGL(k_del_small_prefix<K>, dim3(1), dim3(1024), 0, s, v, t.hdr, static_cast<uint32_t>(B),
                            status);
     } else {
-        hipLaunchKernelGGL(k_init<K>, dim3(1), dim3(kBlk), 0, s, v, t.hdr);
         sort_from<K>(keys, v.sk, v.si, v.sk2, v.si2, B, v.sort_tmp, s, &t.hdr->error, kErrInternal);
-        hipLaunchKernelGGL(k_del_heads<K>, dim3(gB), dim3(kBlk), 0, s, v, B, status);
-        scan_exclusive<uint32_t>(v.f0, v.f1, &v.st->U, nullptr, B, v.scan_tmp, s);
-        hipLaunchKernelGGL(k_del_unique<K>, dim3(gB), dim3(kBlk), 0, s, v, B);
+        hipLaunchKernelGGL(k_ch_heads<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, t.hdr, B, cb.tiles, uint8_t(0), status,
+                           sums);
+        hipLaunchKernelGGL(k_ch_unique<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, B, cb.tiles,
+                           static_cast<const K*>(nullptr), sums);
     }
     launch_locate<K>(t, v, c.cfg, B, status, s);
     // two keys in flight per lane group once every group of the grid has more
@@ -2766,8 +2955,8 @@ const uint32_t* launch_delete(const TreeView<K>& t, const InsertCtx& c, const K*
         hipLaunchKernelGGL((k_del_leaf<K, 1>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
     const bool ordered = B > kDelListScan;
     if (ordered) {
-        scan_exclusive<uint32_t>(v.nu, v.nleaf, &v.st->merges, &v.st->U, B, v.scan_tmp, s);
-        hipLaunchKernelGGL(k_del_list_ordered<K>, dim3(gB), dim3(kBlk), 0, s, t, v);
+        hipLaunchKernelGGL((k_ch_count<K, false>), dim3(cb.n), dim3(kChBlock), 0, s, t, v, cb.tiles, sums);
+        hipLaunchKernelGGL((k_ch_collect<K, false>), dim3(cb.n), dim3(kChBlock), 0, s, t, v, cb.tiles, sums);
     } else {
         hipLaunchKernelGGL(k_del_list<K>, dim3(gB), dim3(kBlk), 0, s, t, v);
     }
