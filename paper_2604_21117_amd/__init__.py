@@ -187,11 +187,23 @@ def _ptr(t) -> int:
     return t.data_ptr() if t is not None else 0
 
 
+_raw_stream = None  # the current stream's handle, once torch has initialised the device
+
+
 def _stream(stream):
-    torch = _torch()
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    """The HIP stream of a call: the given one, or the current one of the
+    current device.  The latter without building a stream object, which took
+    2.5 of a small lookup's 7.2 us."""
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        torch = _torch()
+        handle = torch.cuda.current_stream().cuda_stream  # initialises the device, or raises
+        raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+        _raw_stream = lambda: raw(device())  # noqa: E731
+        return handle
+    return _raw_stream()
 
 
 def key_dtype(key_bytes: int):
