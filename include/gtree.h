@@ -97,18 +97,19 @@ typedef struct {
                                  batch size (16 below 2^13 queries, else 8);
                                  ranges and insert location use 8            */
     uint32_t lds_levels;      /* top inner levels read from an LDS copy: 1..3,
-                                 4 = none; 0 = by batch size (none below 2^15
+                                 4 = none; 0 = by batch size (none below 2^17
                                  queries, else 2; ranges and insert location
                                  use 2)                                       */
     uint32_t sorted_mode;     /* reserved, must be 0                          */
     uint32_t queries_per_group; /* queries a lane group walks at once: 1, 2
                                    or 4 for every batch; 0 = by batch size
-                                   (1 below 2^15 queries, else 2)             */
+                                   (1 up to 2^16 queries, else 2)             */
     uint64_t max_batch;       /* largest insert batch; default 2^20           */
     uint32_t value_coload;    /* 1: a lookup reads the leaf's value line with
                                  its key line (one dependent load fewer);
                                  2: it reads the one value after the match;
-                                 0 = default (1)                              */
+                                 0 = by batch size (1 up to 2^16 queries,
+                                 else 2)                                      */
     uint32_t xcd_split;       /* 1: large lookup batches are split by key
                                  range over the 8 XCDs so that each XCD's L2
                                  holds the inner nodes of its own subtrees;
@@ -117,8 +118,9 @@ typedef struct {
                                  (lines that stream should not evict the
                                  inner nodes other queries reuse from L2):
                                  1: key and value lines, every batch; 2:
-                                 none; 0 = default: the value line from
-                                 2^15 queries on                            */
+                                 none; 0 = default: the values of batches
+                                 above 2^16 queries on trees with 256 MB of
+                                 leaf lines or more                         */
     uint32_t reserved;        /* must be 0                                    */
 } gt_params;
 

@@ -2120,7 +2120,7 @@ static void launch_locate_lv(const TreeView<K>& t, const Ins<K>& v, const Launch
 template <class K>
 static void launch_locate(const TreeView<K>& t, const Ins<K>& v, const LaunchCfg& cfg, uint64_t B, uint8_t* status,
                           hipStream_t s) {
-    if (B >= kLargeBatch) launch_locate_lv<K, 8, 2>(t, v, cfg, B, status, s);
+    if (B >= kLocateBatch) launch_locate_lv<K, 8, 2>(t, v, cfg, B, status, s);
     else launch_locate_lv<K, 16, 1>(t, v, cfg, B, status, s);
 }
 

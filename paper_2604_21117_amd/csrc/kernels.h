@@ -11,16 +11,15 @@ struct LaunchCfg {
     int lanes;              // lanes per query: 4, 8, 16
     int queries_per_group;  // queries interleaved per lane group: 1, 2, 4
     int lds_levels;         // top inner levels read from LDS: 0..3
-    int value_coload;       // read a leaf's value line together with its key line
+    int value_coload;       // a leaf's value line: 1 read with its key line, 0 one value after the match, 2 by batch size
     int xcd_split;          // 0 off, 1 on from kXcdMinBatch queries, 2 always
-    int leaf_stream;        // non-temporal leaf loads: 0 value lines from kLargeBatch queries, 1 key and value lines, 2 none
-    int large_qpg;          // queries per group from kLargeBatch queries on (0 = same)
+    int leaf_stream;        // non-temporal leaf loads: 0 values of large batches, 1 key and value lines, 2 none
     int shape_auto;         // lookup shape chosen by batch size: bit 0 lanes, 1 queries per group, 2 LDS levels
 };
 
 constexpr uint64_t kXcdMinBatch = 1u << 15;
-constexpr uint64_t kLargeBatch = 1u << 15;
 constexpr uint64_t kMidBatch = 1u << 13;
+constexpr uint64_t kLocateBatch = 1u << 15;  // insert location: two queries per group from here on
 
 template <class K>
 void launch_lookup(const TreeView<K>& t, const LaunchCfg& cfg, const K* q, uint64_t B, K* vout, uint8_t* fout,

@@ -342,13 +342,24 @@ static void launch_lookup_xcd(const TreeView<K>& t, const K* q, uint64_t B, K* v
                        lds_bytes_for(2, sizeof(K)), s, t, q, B, vout, fout, nchunks);
 }
 
+constexpr uint64_t kPassBatch = 1u << 16;   // one pass of the grid at one query per group
+constexpr uint64_t kStageBatch = 1u << 17;  // from here on the top levels are staged in LDS
+
+// Values are streamed past the caches in large batches over trees whose leaf
+// lines outgrow the 256 MB memory-side cache: there a line is not read again
+// before it is evicted.  2^20 present keys of 2^24 u64 keys (256 MB of leaf
+// lines) 63.2 us against 64.2 with plain loads; below that size the lines
+// are found again, 2^20 keys of 2^21 keys 47.2 against 54.4.
+constexpr uint64_t kStreamLeafBytes = 256ull << 20;
+
 template <class K, int G, int QPG, int LV>
 static void launch_lookup_v(const TreeView<K>& t, const LaunchCfg& cfg, const K* q, uint64_t B, K* vout,
                             uint8_t* fout, hipStream_t s) {
     const bool xcd = cfg.xcd_split == 2 || (cfg.xcd_split == 1 && B >= kXcdMinBatch);
     // leaf lines read non-temporally: both (leaf_stream 1), none (2), or by
-    // default the value line from kLargeBatch queries on
-    const int nt = cfg.leaf_stream == 1 ? 3 : (cfg.leaf_stream == 0 && B >= kLargeBatch ? 2 : 0);
+    // default the values, by the rule above
+    const bool big = 2ull * t.leaf_cap * kSlots * sizeof(K) >= kStreamLeafBytes;
+    const int nt = cfg.leaf_stream == 1 ? 3 : (cfg.leaf_stream == 0 && big && B > kPassBatch ? 2 : 0);
     if (xcd) {
         if (cfg.value_coload) {
             if (nt == 3) launch_lookup_xcd<K, true, 3>(t, q, B, vout, fout, s);
@@ -383,23 +394,29 @@ static void launch_lookup_lv(const TreeView<K>& t, const LaunchCfg& cfg, const K
     }
 }
 
-// Lookup shape by batch size, for the fields the caller did not fix
-// (measured on 2^24 u64 keys): small batches are latency-bound and want
-// 16 lanes per query, one query per group and no LDS staging (the top
-// levels are L2 hits, the staging a barrier on the critical path); large
-// batches are bound by the rate of L2 misses and want 8 lanes, two queries
-// in flight per group (one is too few to hide the misses; four cost more in
-// registers and barriers than they add) and the top two levels in LDS.
+// Lookup shape by batch size, for the fields the caller did not fix.  The
+// 2048 resident workgroups hold 2^16 queries at 8 lanes each.
+//  - Below kMidBatch a batch is one latency chain: 16 lanes per query, no LDS
+//    staging (the top levels are L2 hits, the staging a barrier on the
+//    critical path), the value line read with the key line.
+//  - Up to kPassBatch one query per group is one pass of the grid: 65536
+//    queries of 2^24 u64 keys 5.4 us, 5.8 with two per group, 6.5 with the
+//    top levels staged as well.
+//  - Above it a batch is bound by the lines it reads: two queries in flight
+//    per group (one is too few to hide the misses; four cost more in
+//    registers than they add), and one value read after the match instead of
+//    the whole line before it, which an absent key does not read at all: 2^20
+//    queries of 2^23 u64 keys, half absent, 49.8 us against 60.0; 2^20
+//    present ones of 2^18 u64 keys 34.9 against 46.7.
+//  - From kStageBatch on the grid walks its tiles more than once and staging
+//    the top two levels is shared: 2^20 queries of 2^22 u64 keys 52.5 us
+//    against 53.7; 98304 queries 7.5 against 7.4, of 2^21 keys 6.9 against 6.6.
 static LaunchCfg shape_for(const LaunchCfg& cfg, uint64_t B) {
     LaunchCfg c = cfg;
-    int lanes, qpg, lds;
-    if (B < kMidBatch) { lanes = 16; qpg = 1; lds = 0; }
-    else if (B < kLargeBatch) { lanes = 8; qpg = 1; lds = 0; }
-    else { lanes = 8; qpg = cfg.large_qpg ? cfg.large_qpg : 2; lds = 2; }
-    if (cfg.shape_auto & 1) c.lanes = lanes;
-    if (cfg.shape_auto & 2) c.queries_per_group = qpg;
-    else if (B >= kLargeBatch && cfg.large_qpg) c.queries_per_group = cfg.large_qpg;
-    if (cfg.shape_auto & 4) c.lds_levels = lds;
+    if (cfg.shape_auto & 1) c.lanes = B < kMidBatch ? 16 : 8;
+    if (cfg.shape_auto & 2) c.queries_per_group = B <= kPassBatch ? 1 : 2;
+    if (cfg.shape_auto & 4) c.lds_levels = B < kStageBatch ? 0 : 2;
+    if (cfg.value_coload == 2) c.value_coload = B <= kPassBatch ? 1 : 0;
     return c;
 }
 
