@@ -95,7 +95,8 @@ typedef struct {
     float fill;               /* bulk-load fill in [0.5, 1]; default 1.0      */
     uint32_t lanes_per_query; /* lookup lanes per query: 4, 8 or 16; 0 = by
                                  batch size (16 below 2^13 queries, else 8);
-                                 ranges and insert location use 8            */
+                                 insert location uses 8 where it is 0, ranges
+                                 choose their own by batch size              */
     uint32_t lds_levels;      /* top inner levels read from an LDS copy: 1..3,
                                  4 = none; 0 = by batch size (none below 2^17
                                  queries, else 2; ranges and insert location

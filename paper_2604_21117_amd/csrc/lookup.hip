@@ -8,10 +8,10 @@
 // paper's -1 result, Section IV-D).  Results go to the caller's order.
 //
 // Range (an addition over the linked leaves of Section III): the
-// group descends to the leaf of `lo`, then walks the leaf chain; per leaf a
-// ballot marks the slots with lo <= key <= hi and the group writes them in
-// slot order at out[offset + running count], until `max` pairs are written,
-// a key above `hi` is seen or the chain ends.
+// group descends to the leaf of `lo`, then walks the leaf chain, one or a few
+// leaves at a time; a ballot marks the slots with lo <= key <= hi and the
+// group writes them in order at out[offset + running count], until `max`
+// pairs are written, a key above `hi` is seen or the chain ends.
 //
 // Both kernels are persistent: a grid of at most a few thousand
 // workgroups walks tiles of queries, so the mirror is staged once per
@@ -224,13 +224,102 @@ __global__ __launch_bounds__(kLookupBlock) void k_lookup_xcd(TreeView<K> t, cons
     }
 }
 
-template <class K, int G, int LV>
+// A scan is a chain of dependent reads, the descent and then leaf after leaf.
+// Few scans leave the chip idle, so a scan takes 16 AH lanes and reads AH
+// leaves at once: the leaf it stands on and, on the guess that they follow,
+// the leaves of the next references (a bulk load numbers them so; a split's
+// new leaf lies elsewhere).  A leaf read ahead counts only if the links of
+// the leaves before it lead to it; one that is not linked is out of the scan,
+// its contents never used.  1024 scans of 2^24 u64 keys, 1 to 100 pairs, 7.1
+// -> 4.2 us with four leaves at once, up to 400 pairs 16.4 -> 6.1; on a tree
+// grown by half with inserts 8.8 -> 7.2 and 20.9 -> 15.6.
+template <class K, int AH, int LV>
 __global__ __launch_bounds__(kLookupBlock) void k_range(TreeView<K> t, const K* __restrict__ lo,
                                                          const K* __restrict__ hi,
                                                          const uint32_t* __restrict__ maxc,
                                                          const uint64_t* __restrict__ off, uint64_t B,
                                                          K* __restrict__ okeys, K* __restrict__ ovals,
                                                          uint32_t* __restrict__ cnt_out, uint64_t ntiles) {
+    constexpr int G = kSlots;    // lanes per leaf: one slot each
+    constexpr int W = G * AH;    // lanes per scan
+    extern __shared__ __align__(16) uint8_t lds[];
+    const uint8_t* mir = t.mirror;
+    uint32_t mnodes = kMirrorMaxNodes;
+    if constexpr (LV > 0) {
+        mnodes = mirror_nodes_for_levels(LV);
+        stage_mirror<K>(t.mirror, lds, mnodes);
+        __syncthreads();
+        mir = lds;
+    }
+    const MirrorHeader* mh = reinterpret_cast<const MirrorHeader*>(mir);
+    const bool empty = mh->n_keys == 0;
+    const int lane = lane_id();
+    const int gl = lane % G, gbase = lane - gl;         // the 16-lane group of a leaf
+    const int wl = lane % W, wbase = lane - wl;         // the lanes of a scan
+    const uint32_t sub = static_cast<uint32_t>(wl / G);  // which of the leaves ahead
+    const uint64_t below = (1ull << wl) - 1ull;
+    const uint64_t group = threadIdx.x / W;
+    const uint64_t tile_q = kLookupBlock / W;
+    for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const uint64_t qi = tile * tile_q + group;
+        const bool live = qi < B;
+        K key[1] = {live ? lo[qi] : K(0)};
+        const K h = live ? hi[qi] : K(0);
+        const uint32_t mx = live ? maxc[qi] : 0u;
+        const uint64_t base = live ? off[qi] : 0ull;
+        uint32_t leaf[1];
+        descend<K, G, 1, false>(t, mir, mnodes, LV, key, leaf, gl, gbase);
+        uint32_t c = 0;
+        bool done = !live || empty || mx == 0 || key[0] > h;
+        uint32_t cur = leaf[0];
+        while (!done) {
+            // leaves the rest of the scan may reach, the first about half used
+            const bool want = sub == 0 || mx - c > kSlots * sub - kSlots / 2;
+            const uint64_t guess = static_cast<uint64_t>(cur) + sub;
+            const bool on = want && guess < t.leaf_cap;
+            const uint64_t at = on ? guess : cur;
+            const K kv = t.lkeys[at * kSlots + gl];
+            const K vv = t.lvals[at * kSlots + gl];
+            const uint2 meta = t.lmeta[at];
+            // leaf `sub` counts if every leaf before it is followed by the
+            // next reference (and is not empty: a scan ends there)
+            const uint64_t linked = group_bits<W>(
+                __ballot(on && meta.x != 0 && meta.y == static_cast<uint32_t>(guess) + 1u), wbase);
+            bool use = on;
+#pragma unroll
+            for (int s = 0; s + 1 < AH; ++s)
+                use = use && (static_cast<uint32_t>(s) >= sub || ((linked >> (s * G)) & 1ull));
+            const bool in = use && static_cast<uint32_t>(gl) < meta.x;
+            const bool ok = in && kv >= key[0] && kv <= h;
+            const uint64_t bits = group_bits<W>(__ballot(ok), wbase);
+            const uint64_t over = group_bits<W>(__ballot(in && kv > h), wbase);
+            const uint64_t used = group_bits<W>(__ballot(use), wbase);
+            const uint32_t p = c + static_cast<uint32_t>(__popcll(bits & below));
+            if (ok && p < mx) {
+                okeys[base + p] = kv;
+                ovals[base + p] = vv;
+            }
+            c += static_cast<uint32_t>(__popcll(bits));
+            // the last leaf that counted leads on
+            const int last = wbase + 63 - static_cast<int>(__builtin_clzll(used));
+            const uint32_t cnt = shfl_u32(meta.x, last), next = shfl_u32(meta.y, last);
+            done = c >= mx || over != 0 || next == kNone || cnt == 0;
+            cur = next;
+        }
+        if (live && wl == 0) cnt_out[qi] = c < mx ? c : mx;
+    }
+}
+
+// The scan for large batches: 8 lanes per scan and leaf, two slots per lane,
+// so that the resident waves hold twice as many scans and none reads ahead.
+template <class K, int LV>
+__global__ __launch_bounds__(kLookupBlock) void k_range_many(TreeView<K> t, const K* __restrict__ lo,
+                                                              const K* __restrict__ hi,
+                                                              const uint32_t* __restrict__ maxc,
+                                                              const uint64_t* __restrict__ off, uint64_t B,
+                                                              K* __restrict__ okeys, K* __restrict__ ovals,
+                                                              uint32_t* __restrict__ cnt_out, uint64_t ntiles) {
+    constexpr int G = 8;
     using T = Trav<K, G>;
     constexpr int KPL = T::KPL;
     extern __shared__ __align__(16) uint8_t lds[];
@@ -444,34 +533,62 @@ void launch_lookup(const TreeView<K>& t, const LaunchCfg& cfg0, const K* q, uint
     }
 }
 
-template <class K, int G, int LV>
+template <class K, int AH, int LV>
 static void launch_range_t(const TreeView<K>& t, const K* lo, const K* hi, const uint32_t* mx, const uint64_t* off,
                            uint64_t B, K* ok, K* ov, uint32_t* cnt, hipStream_t s) {
-    const uint64_t tile_q = kLookupBlock / G;
+    const uint64_t tile_q = kLookupBlock / (kSlots * AH);
     const uint64_t ntiles = (B + tile_q - 1) / tile_q;
     const uint64_t grid = grid_for(ntiles, LV, sizeof(K));
-    hipLaunchKernelGGL((k_range<K, G, LV>), dim3(static_cast<uint32_t>(grid)), dim3(kLookupBlock),
+    hipLaunchKernelGGL((k_range<K, AH, LV>), dim3(static_cast<uint32_t>(grid)), dim3(kLookupBlock),
                        lds_bytes_for(LV, sizeof(K)), s, t, lo, hi, mx, off, B, ok, ov, cnt, ntiles);
 }
 
-template <class K, int G>
-static void launch_range_lv(const TreeView<K>& t, int lv, const K* lo, const K* hi, const uint32_t* mx,
-                            const uint64_t* off, uint64_t B, K* ok, K* ov, uint32_t* cnt, hipStream_t s) {
-    switch (lv) {
-        case 0: launch_range_t<K, G, 0>(t, lo, hi, mx, off, B, ok, ov, cnt, s); break;
-        case 1: launch_range_t<K, G, 1>(t, lo, hi, mx, off, B, ok, ov, cnt, s); break;
-        case 2: launch_range_t<K, G, 2>(t, lo, hi, mx, off, B, ok, ov, cnt, s); break;
-        default: launch_range_t<K, G, 3>(t, lo, hi, mx, off, B, ok, ov, cnt, s); break;
+template <class K, int LV>
+static void launch_range_many_t(const TreeView<K>& t, const K* lo, const K* hi, const uint32_t* mx,
+                                const uint64_t* off, uint64_t B, K* ok, K* ov, uint32_t* cnt, hipStream_t s) {
+    const uint64_t tile_q = kLookupBlock / 8;
+    const uint64_t ntiles = (B + tile_q - 1) / tile_q;
+    const uint64_t grid = grid_for(ntiles, LV, sizeof(K));
+    hipLaunchKernelGGL((k_range_many<K, LV>), dim3(static_cast<uint32_t>(grid)), dim3(kLookupBlock),
+                       lds_bytes_for(LV, sizeof(K)), s, t, lo, hi, mx, off, B, ok, ov, cnt, ntiles);
+}
+
+// Leaves read at once by batch size.  The chip holds 2^13 scans of four
+// leaves, 2^14 of two and 2^15 of one; what it has no idle lanes for is only
+// more to read: 1024 scans take four (see k_range), 4096 two (1 to 100 pairs
+// 5.4 us, four 5.1; 1 pair 3.95, four 4.4, the old 3.9), 8192 one (7.7 us,
+// the old 8.2; on a grown tree 9.8 and 11.0).  Above kRangeMany scans of
+// 64-bit keys 8 lanes per scan read as much at once: 32768 scans of 1 to 20
+// pairs 8.3 us, with 16 lanes 9.0; of 32-bit keys, whose lines are half as
+// long, 16 lanes stay ahead (1 to 100 pairs 12.6 us, 8 lanes 14.6).
+constexpr uint64_t kRangeFour = 1u << 11, kRangeTwo = 1u << 12, kRangeMany = 1u << 14;
+
+template <class K, int LV>
+static void launch_range_lv(const TreeView<K>& t, const K* lo, const K* hi, const uint32_t* mx, const uint64_t* off,
+                            uint64_t B, K* ok, K* ov, uint32_t* cnt, hipStream_t s) {
+    if (B <= kRangeFour) {
+        launch_range_t<K, 4, LV>(t, lo, hi, mx, off, B, ok, ov, cnt, s);
+    } else if (B <= kRangeTwo) {
+        launch_range_t<K, 2, LV>(t, lo, hi, mx, off, B, ok, ov, cnt, s);
+    } else {
+        if constexpr (sizeof(K) == 8) {
+            if (B > kRangeMany) {
+                launch_range_many_t<K, LV>(t, lo, hi, mx, off, B, ok, ov, cnt, s);
+                return;
+            }
+        }
+        launch_range_t<K, 1, LV>(t, lo, hi, mx, off, B, ok, ov, cnt, s);
     }
 }
 
 template <class K>
 void launch_range(const TreeView<K>& t, const LaunchCfg& cfg, const K* lo, const K* hi, const uint32_t* mx,
                   const uint64_t* off, uint64_t B, K* ok, K* ov, uint32_t* cnt, hipStream_t s) {
-    switch (cfg.lanes) {
-        case 4: launch_range_lv<K, 4>(t, cfg.lds_levels, lo, hi, mx, off, B, ok, ov, cnt, s); break;
-        case 16: launch_range_lv<K, 16>(t, cfg.lds_levels, lo, hi, mx, off, B, ok, ov, cnt, s); break;
-        default: launch_range_lv<K, 8>(t, cfg.lds_levels, lo, hi, mx, off, B, ok, ov, cnt, s); break;
+    switch (cfg.lds_levels) {
+        case 0: launch_range_lv<K, 0>(t, lo, hi, mx, off, B, ok, ov, cnt, s); break;
+        case 1: launch_range_lv<K, 1>(t, lo, hi, mx, off, B, ok, ov, cnt, s); break;
+        case 2: launch_range_lv<K, 2>(t, lo, hi, mx, off, B, ok, ov, cnt, s); break;
+        default: launch_range_lv<K, 3>(t, lo, hi, mx, off, B, ok, ov, cnt, s); break;
     }
 }
 
