@@ -371,6 +371,95 @@ __global__ __launch_bounds__(kBlk) void k_locate(TreeView<K> t, Ins<K> v, uint8_
     ph_locate<K, G, QPG, LV, kBlk>(t, v, status);
 }
 
+// A batch of at most kRankSortMax keys, sorted, deduplicated and located in
+// one launch.  Every workgroup holds the batch in LDS and 16 lanes take one
+// key: they count the keys before it in (key, index) order, each lane a
+// sixteenth of the batch, and then descend with it.  A key's records go to
+// its rank, repeats included, so no pass compacts the distinct keys first
+// (U is the batch size here): a repeat is neither found nor new, it only
+// reports what a second occurrence reports, and the first occurrence carries
+// the last one's value.  1000 keys on 2^24 take 9.4 us, where the rank sort,
+// the compaction in one workgroup and locate took three launches of 4.5, 3.0
+// and 7.5.  The first workgroup clears the batch state.
+template <class K, int LV, bool INS>
+__global__ __launch_bounds__(kBlk) void k_rank_locate(TreeView<K> t, Ins<K> v, const K* __restrict__ keys,
+                                                       const K* __restrict__ vals, uint32_t B,
+                                                       uint8_t* __restrict__ status) {
+    constexpr int G = 16;
+    using T = Trav<K, G>;
+    extern __shared__ __align__(16) uint8_t lds[];
+    __shared__ K s_key[kRankSortMax];
+    if (blockIdx.x == 0) {
+        uint32_t* st = reinterpret_cast<uint32_t*>(v.st);
+        for (uint32_t i = threadIdx.x; i < sizeof(InsState) / 4; i += kBlk)
+            st[i] = i == offsetof(InsState, U) / 4 ? B : (i == offsetof(InsState, height) / 4 ? t.hdr->height : 0u);
+    }
+    for (uint32_t i = threadIdx.x; i < B; i += kBlk) s_key[i] = keys[i];
+    const uint8_t* mir = t.mirror;
+    uint32_t mnodes = kMirrorMaxNodes;
+    if constexpr (LV > 0) {
+        mnodes = mirror_nodes_for_levels(LV);
+        stage_mirror<K>(t.mirror, lds, mnodes);
+        mir = lds;
+    }
+    __syncthreads();
+    const int lane = lane_id();
+    const int gl = lane % G, gbase = lane - gl;
+    const uint32_t e = (blockIdx.x * kBlk + threadIdx.x) / G;
+    const bool mine = e < B && gl == 0;
+    K key[1] = {e < B ? s_key[e] : K(0)};
+    uint32_t before = 0, same = 0, last = e;  // keys before; equal keys before; the last equal key
+    // lane l takes keys l, l + 16, ...: neighbouring lanes read neighbouring
+    // LDS words (no bank conflicts), eight reads in flight
+    constexpr uint32_t R = 8;
+    uint32_t j = static_cast<uint32_t>(gl);
+    auto take = [&](K kj, uint32_t jj) {
+        const bool eq = kj == key[0];
+        before += kj < key[0] ? 1u : 0u;
+        same += eq && jj < e ? 1u : 0u;
+        if (eq && jj > last) last = jj;
+    };
+    for (; j + G * (R - 1) < B; j += G * R) {
+        K kj[R];
+#pragma unroll
+        for (uint32_t x = 0; x < R; ++x) kj[x] = s_key[j + G * x];
+#pragma unroll
+        for (uint32_t x = 0; x < R; ++x) take(kj[x], j + G * x);
+    }
+    for (; j < B; j += G) take(s_key[j], j);
+    uint32_t n = before << 16 | same;  // both at most kRankSortMax
+#pragma unroll
+    for (int m = 1; m < G; m <<= 1) {
+        n += static_cast<uint32_t>(__shfl_xor(static_cast<int>(n), m, 64));
+        const uint32_t o = static_cast<uint32_t>(__shfl_xor(static_cast<int>(last), m, 64));
+        last = o > last ? o : last;
+    }
+    same = n & 0xFFFFu;
+    const uint32_t u = (n >> 16) + same;
+    K val = K(0);
+    if constexpr (INS) {
+        if (mine) val = vals[last];
+    }
+    const bool empty = reinterpret_cast<const MirrorHeader*>(mir)->n_keys == 0;
+    uint32_t leaf[1];
+    descend<K, G, 1, true>(t, mir, mnodes, LV, key, leaf, gl, gbase, v.pn, v.pi, v.Bm, mine ? u : ~0ull, v.pc);
+    const uint32_t lcnt = mine ? t.lmeta[leaf[0]].x : 0u;
+    const typename T::KV kv = T::load_keys(t.lkeys + static_cast<uint64_t>(leaf[0]) * kSlots, gl);
+    const uint32_t slot = T::match_slot(kv, key[0], gbase);
+    if (mine) {
+        const bool present = slot < kSlots && !empty, first = same == 0;
+        v.uk[u] = key[0];
+        if constexpr (INS) v.uv[u] = val;
+        v.ufound[u] = present && first ? 1 : 0;
+        v.uleaf[u] = leaf[0];
+        v.ulc[u] = static_cast<uint8_t>(lcnt);
+        v.uslot[u] = static_cast<uint8_t>(present ? slot : 0);
+        v.f0[u] = first && !present ? 1u : 0u;
+        // a repeat: UPDATED (an earlier occurrence exists) or ABSENT (it is gone)
+        status[e] = first ? (present ? 1 : 0) : (INS ? 1 : 0);
+    }
+}
+
 // Entries u < U that count: new keys (not found in their leaf), or, for the
 // delete, runs that left their leaf below half full.
 template <class K, bool NEW>
@@ -1487,117 +1576,47 @@ static bool single_key_insert_on() { return g_single_key.load(std::memory_order_
 
 // ------------------------------------------------- small batches (B <= 2048)
 //
-// A rank sort over many workgroups orders the batch and one workgroup
-// deduplicates it; after locate, one workgroup sized to the batch plans every
-// level (k_small_plan), and up to kFusedMax keys one more workgroup applies
-// the whole batch (k_small_apply).  The results are those of the general
+// One launch over many workgroups ranks and locates the batch
+// (k_rank_locate); one workgroup sized to the batch plans every level
+// (k_small_plan), and up to kFusedMax keys one more workgroup applies the
+// whole batch (k_small_apply).  The results are those of the general
 // path: the same item arrays and level counters, the same apply bodies.
 // Batches of 2 to kFusedMax keys run all of it in one launch by default
 // (k_ins_small, below), with the same results.
 
 constexpr uint32_t kSmallInsert = 2048;
-static_assert(kSmallInsert <= kRankSortMax, "the small path sorts with rank_sort_small");
+static_assert(kSmallInsert <= kRankSortMax, "the small path ranks with k_rank_locate");
 constexpr int kSmallBlock = 1024;
 
-// A batch of at most kFusedSortMax keys is ranked here, by the waves that
-// hold its keys, each reading the batch from LDS (about B^2 / 16 cycles of
-// one CU: cheaper than a launch up to this size); a larger one arrives
-// sorted by rank_sort_small, which spreads the comparisons over B / 16 CUs.
-constexpr uint32_t kFusedSortMax = 256;
-
-template <class K>
-__global__ __launch_bounds__(kSmallBlock) void k_small_prefix(Ins<K> v, const DevHeader* hdr,
-                                                               const K* __restrict__ keys, const K* __restrict__ vals,
-                                                               uint32_t B, uint8_t* __restrict__ status,
-                                                               uint32_t presorted) {
-    __shared__ K rk[kSmallInsert];
-    __shared__ K sk[kSmallInsert];
-    __shared__ uint32_t si[kSmallInsert];
-    __shared__ uint32_t sh[33];
-    const uint32_t tid = threadIdx.x;
-    uint32_t* s = reinterpret_cast<uint32_t*>(v.st);
-    for (uint32_t i = tid; i < sizeof(InsState) / 4; i += blockDim.x) s[i] = 0;
-    if (presorted) {
-        // the pairs in (key, index) order, from rank_sort_small
-        for (uint32_t i = tid; i < B; i += blockDim.x) {
-            sk[i] = v.sk[i];
-            si[i] = v.si[i];
+// Exclusive scans of W words over the plan's workgroup with one barrier: every
+// wave adds up the waves before it by itself.  One wave needs no LDS; else
+// `sh` holds W words per wave and a barrier must separate two uses of it.
+template <int NT, int W>
+__device__ __forceinline__ void plan_scan(uint32_t (&x)[W], uint32_t* sh, uint32_t (&total)[W]) {
+    constexpr int nw = NT / 64;
+    const int w = static_cast<int>(threadIdx.x >> 6), lane = static_cast<int>(threadIdx.x & 63);
+    uint32_t inc[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) inc[i] = wave_incl_scan(x[i]);
+    if constexpr (nw == 1) {
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            total[i] = shfl_u32(inc[i], 63);
+            x[i] = inc[i] - x[i];
         }
     } else {
-        for (uint32_t i = tid; i < B; i += blockDim.x) rk[i] = keys[i];
-        __syncthreads();
-        // each element's stable rank over the batch in LDS; only the waves
-        // that hold elements count (all lanes of a wave read the same word)
-        if (tid < B) {
-            const K k0 = rk[tid];
-            uint32_t c = 0, j = 0;
-            for (; j + 8 <= B; j += 8) {
+        if (lane == 63) {
 #pragma unroll
-                for (uint32_t u = 0; u < 8; ++u) {
-                    const K kj = rk[j + u];
-                    c += (kj < k0 || (kj == k0 && j + u < tid)) ? 1u : 0u;
-                }
-            }
-            for (; j < B; ++j) c += (rk[j] < k0 || (rk[j] == k0 && j < tid)) ? 1u : 0u;
-            sk[c] = k0;
-            si[c] = tid;
+            for (int i = 0; i < W; ++i) sh[w * W + i] = inc[i];
         }
         __syncthreads();
-        for (uint32_t i = tid; i < B; i += blockDim.x) {
-            v.sk[i] = sk[i];
-            v.si[i] = si[i];  // locate writes each distinct key's status through it
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            const uint32_t s = lane < nw ? sh[lane * W + i] : 0u;
+            const uint32_t si = wave_incl_scan(s);
+            total[i] = shfl_u32(si, 63);
+            x[i] = inc[i] - x[i] + shfl_u32(si - s, w);
         }
-    }
-    __syncthreads();  // the pairs in LDS, the batch state cleared
-    if (tid == 0) v.st->height = hdr->height;
-    uint32_t f[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const uint32_t p = 2 * tid + e;
-        f[e] = (p < B && (p == 0 || sk[p] != sk[p - 1])) ? 1u : 0u;
-    }
-    uint32_t tot;
-    const uint32_t off = block_excl_scan<uint32_t>(f[0] + f[1], sh, &tot);
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const uint32_t p = 2 * tid + e;
-        if (p >= B) continue;
-        const uint32_t pos = off + (e ? f[0] : 0u);
-        if (f[e]) {
-            v.uk[pos] = sk[p];
-            v.upos[pos] = p;
-        } else {
-            status[si[p]] = 1;  // UPDATED: an earlier occurrence exists
-        }
-        if (p + 1 == B || sk[p + 1] != sk[p]) v.uv[pos + f[e] - 1] = vals[si[p]];
-    }
-    if (tid == 0) v.st->U = tot;
-}
-
-// Old entry count of node `node` at level d (0 = leaves): a leaf's count, or
-// the number of child references of an inner node.
-template <class K>
-__device__ __forceinline__ uint32_t old_count(const TreeView<K>& t, uint32_t node, bool leaf) {
-    if (leaf) return t.lmeta[node].x;
-    const uint4* ch = reinterpret_cast<const uint4*>(t.ichild + static_cast<uint64_t>(node) * kSlots);
-    uint32_t c = 0;
-#pragma unroll
-    for (int q = 0; q < kSlots / 4; ++q) {
-        const uint4 x = ch[q];
-        c += (x.x != kNone) + (x.y != kNone) + (x.z != kNone) + (x.w != kNone);
-    }
-    return c;
-}
-
-// Exclusive scan over the plan's workgroup: one wave needs no LDS.
-template <int NT>
-__device__ __forceinline__ uint32_t plan_scan(uint32_t x, uint32_t* sh, uint32_t* total) {
-    if constexpr (NT == 64) {
-        const uint32_t inc = wave_incl_scan(x);
-        *total = __shfl(inc, 63, 64);
-        return inc - x;
-    } else {
-        return block_excl_scan<uint32_t>(x, sh, total);
     }
 }
 
@@ -1614,39 +1633,41 @@ struct PlanRecs {
 
 // Plan of a small batch, one workgroup of NT threads (NT >= B / 2); thread t
 // owns new keys 2t and 2t+1.  Small NT keeps the barriers cheap (one wave
-// for B <= 128), and the level loops stay rolled so that the kernel's code
-// stays small (a single wave runs it once, so every instruction line it
-// touches is a cache miss).
+// for B <= 128).
 //
 // The nodes a new key passes through are known from the locate kernel (its
 // leaf and, at every level, its parent, the parent's size and the slot taken),
-// so the items of every level (runs of new keys through one node) are cut
-// first, level after level in LDS with block scans, each item taking its
-// node's old entry count from those records.  The piece counts then follow
-// level after level: an item gains the new keys of its run (leaves) or
-// sum(k - 1) over its child items (inner nodes), a difference of the child
-// level's piece-offset prefix taken by the run's first and last keys.  Writes
-// the same item arrays and level counters as the general path, and then the
-// values of keys already present.
+// so the items (runs of new keys through one node) are cut for kPlanLevels
+// levels at once: one round of reads, one scan of the levels' run heads, two
+// levels to a word.  The piece counts then follow level after level: an item
+// gains the new keys of its run (leaves) or sum(k - 1) over its child items
+// (inner nodes), a difference of the child level's piece-offset prefix taken
+// by the run's first and last keys; above a level where nothing split there
+// is nothing left to count.  It is bound by its chain of barriers and LDS
+// round trips: 1000 keys on 2^24 take 15.4 us, 19.8 with the levels cut one
+// after another.  Writes the same item arrays and level counters as the general
+// path, and then the values of keys already present.
+constexpr int kPlanLevels = 6;  // inner levels and leaves of 2^24 keys
+
 template <class K, int NT>
 __device__ __forceinline__ void ph_small_plan(TreeView<K> t, Ins<K> v, int H) {
-    constexpr int kL = kMaxLevels;
+    constexpr int kL = kMaxLevels, Q = kPlanLevels;
     constexpr uint32_t kCap = 2 * NT;  // new keys, items per level
-    __shared__ uint32_t sh[33];
-    __shared__ uint32_t s_a[kCap], s_b[kCap];  // key -> distinct key, node; later prefix sums at item bounds
+    __shared__ uint32_t sh[Q / 2 * (NT / 64)];
+    __shared__ uint32_t s_a[kCap], s_b[kCap];  // key -> distinct key, leaf; later prefix sums at item bounds
     __shared__ uint16_t s_ix[kL * kCap];       // item index of each key, per level
     __shared__ uint32_t s_k[kCap + 1];         // piece-offset prefix of the previous level's items
     __shared__ uint8_t s_C[kL * kCap];         // old entry count of every item
     __shared__ uint32_t s_base[kL + 1];        // first item of each level
     __shared__ uint32_t s_over;
     __shared__ InsState s_st;  // the batch state, written back at the end
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
     copy_state(&s_st, v.st, tid, NT);
+    if (tid == 0) s_over = 0;
     __syncthreads();
     const uint32_t U = s_st.U;
     const int h = static_cast<int>(s_st.height);
     const int hmax = H < h ? H : h;
-    if (tid == 0) s_over = 0;
 
     // new keys in key order (locate left f0[u] = 1 for a key not in its leaf)
     uint32_t fl[2];
@@ -1654,11 +1675,12 @@ __device__ __forceinline__ void ph_small_plan(TreeView<K> t, Ins<K> v, int H) {
         const uint32_t u = 2 * tid + j;
         fl[j] = u < U ? v.f0[u] : 0u;
     }
-    uint32_t R;
-    const uint32_t o0 = plan_scan<NT>(fl[0] + fl[1], sh, &R);
+    uint32_t o0[1] = {fl[0] + fl[1]}, tot0[1];
+    plan_scan<NT, 1>(o0, sh, tot0);
+    const uint32_t R = tot0[0];
     for (int j = 0; j < 2; ++j) {
         if (!fl[j]) continue;
-        const uint32_t u = 2 * tid + j, r = o0 + (j ? fl[0] : 0u);
+        const uint32_t u = 2 * tid + j, r = o0[0] + (j ? fl[0] : 0u);
         const uint32_t leaf = v.uleaf[u];
         v.nk[r] = v.uk[u];
         v.nv[r] = v.uv[u];
@@ -1669,72 +1691,89 @@ __device__ __forceinline__ void ph_small_plan(TreeView<K> t, Ins<K> v, int H) {
     }
     __syncthreads();
     bool valid[2];
-    // per key and level: node, its old entry count and its slot in its
-    // parent (all recorded by locate), the next level's loaded one level ahead
-    uint32_t nu[2], ixp[2], node[2], cnt[2], cs[2], pnx[2] = {0u, 0u}, pcx[2] = {0u, 0u}, pix[2] = {0u, 0u};
+    uint32_t nu[2], leaf[2], ixp[2];
     for (int j = 0; j < 2; ++j) {
         const uint32_t r = 2 * tid + j;
         valid[j] = r < R;
         nu[j] = valid[j] ? s_a[r] : 0u;
-        node[j] = valid[j] ? s_b[r] : 0u;
-        cnt[j] = valid[j] ? v.ulc[nu[j]] : 0u;
-        cs[j] = valid[j] && h >= 2 ? v.pi[static_cast<uint64_t>(h - 2) * v.Bm + nu[j]] : 0u;
+        leaf[j] = valid[j] ? s_b[r] : 0u;
         ixp[j] = r;  // at the leaf level an item's range counts keys
     }
+    // the key next to the wave's: the one before its first, after its last
+    const uint32_t nr = lane == 0 ? 2 * tid - 1 : 2 * tid + 2;
+    const bool nb = (lane == 0 && tid > 0 && nr < R) || (lane == 63 && nr < R);
+    const uint32_t nbu = nb ? s_a[nr] : 0u, nbleaf = nb ? s_b[nr] : 0u;
 
     // items of every level: heads and ends of runs, item index per key
     uint32_t hbits = 0, lbits = 0, items = 0;
 #pragma unroll 1
-    for (int d = 0; d < hmax; ++d) {
-        if (d > 0) {
+    for (int l0 = 0; l0 < hmax; l0 += Q) {
+        if (l0 > 0) __syncthreads();  // sh is rewritten
+        // per level and key: node, its old entry count and its slot in its
+        // parent, all recorded by locate
+        uint32_t node[Q][2], cnt[Q][2], cs[Q][2], nbn[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int d = l0 + q;
+            const bool on = d < hmax;
+            const uint64_t at = d > 0 && on ? static_cast<uint64_t>(h - 1 - d) * v.Bm : 0ull;
+            const uint64_t up = on && h - 2 - d >= 0 ? static_cast<uint64_t>(h - 2 - d) * v.Bm : 0ull;
             for (int j = 0; j < 2; ++j) {
-                node[j] = pnx[j];
-                cnt[j] = pcx[j];
-                cs[j] = pix[j];
-                if (valid[j]) s_b[2 * tid + j] = node[j];
+                const bool ok = on && valid[j];
+                node[q][j] = d == 0 ? leaf[j] : (ok ? v.pn[at + nu[j]] : 0u);
+                cnt[q][j] = ok ? (d == 0 ? v.ulc[nu[j]] : v.pc[at + nu[j]]) : 0u;
+                cs[q][j] = ok && h - 2 - d >= 0 ? v.pi[up + nu[j]] : 0u;
             }
-            __syncthreads();
+            nbn[q] = d == 0 ? nbleaf : (on && nb ? v.pn[at + nbu] : 0u);
         }
-        // the next level's records, in flight through this level
-        if (d + 1 < hmax)
+        uint32_t x[Q / 2], n[Q / 2];
+#pragma unroll
+        for (int i = 0; i < Q / 2; ++i) x[i] = 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int d = l0 + q;
+            if (d >= hmax) continue;
+            uint32_t before = static_cast<uint32_t>(__shfl_up(static_cast<int>(node[q][1]), 1, 64));
+            uint32_t after = static_cast<uint32_t>(__shfl_down(static_cast<int>(node[q][0]), 1, 64));
+            if (lane == 0) before = nbn[q];
+            if (lane == 63) after = nbn[q];
+            const uint32_t r = 2 * tid;
+            const uint32_t h0 = valid[0] && (r == 0 || before != node[q][0]) ? 1u : 0u;
+            const uint32_t h1 = valid[1] && node[q][1] != node[q][0] ? 1u : 0u;
+            const uint32_t e0 = valid[0] && (!valid[1] || node[q][1] != node[q][0]) ? 1u : 0u;
+            const uint32_t e1 = valid[1] && (r + 2 == R || after != node[q][1]) ? 1u : 0u;
+            hbits |= (h0 | h1 << 1) << (2 * d);
+            lbits |= (e0 | e1 << 1) << (2 * d);
+            x[q / 2] += (h0 + h1) << (16 * (q & 1));
+        }
+        plan_scan<NT, Q / 2>(x, sh, n);  // a level has at most 2048 heads: 16 bits hold its sums
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int d = l0 + q;
+            if (d >= hmax) continue;
+            const uint32_t oh = (x[q / 2] >> (16 * (q & 1))) & 0xFFFFu;
             for (int j = 0; j < 2; ++j) {
-                const uint64_t at = static_cast<uint64_t>(h - 2 - d) * v.Bm + nu[j];
-                pnx[j] = valid[j] ? v.pn[at] : 0u;
-                pcx[j] = valid[j] ? v.pc[at] : 0u;
-                pix[j] = valid[j] && h - 3 - d >= 0 ? v.pi[at - v.Bm] : 0u;
-            }
-        uint32_t hd[2], ls[2];
-        for (int j = 0; j < 2; ++j) {
-            const uint32_t r = 2 * tid + j;
-            hd[j] = valid[j] && (r == 0 || s_b[r - 1] != node[j]) ? 1u : 0u;
-            ls[j] = valid[j] && (r + 1 == R || s_b[r + 1] != node[j]) ? 1u : 0u;
-        }
-        uint32_t n;
-        const uint32_t oh = plan_scan<NT>(hd[0] + hd[1], sh, &n);
-        for (int j = 0; j < 2; ++j) {
-            const uint32_t r = 2 * tid + j;
-            const uint32_t ix = oh + (j ? hd[0] : 0u) + hd[j] - 1u;
-            const uint64_t e = static_cast<uint64_t>(items) + ix;
-            if (valid[j]) s_ix[d * kCap + r] = static_cast<uint16_t>(ix);
-            if (hd[j]) {
-                if (e < v.ip_cap) {
-                    v.it_node[e] = node[j];
-                    v.it_first[e] = ixp[j];
-                    v.it_cold[e] = cnt[j];
-                    v.it_cs[e] = static_cast<uint8_t>(cs[j]);
-                    s_C[e] = static_cast<uint8_t>(cnt[j]);
-                } else {
-                    s_over = 1;
+                const uint32_t hd = (hbits >> (2 * d + j)) & 1u, hd0 = (hbits >> (2 * d)) & 1u;
+                const uint32_t ix = oh + (j ? hd0 : 0u) + hd - 1u;
+                const uint64_t e = static_cast<uint64_t>(items) + ix;
+                if (valid[j]) s_ix[d * kCap + 2 * tid + j] = static_cast<uint16_t>(ix);
+                if (hd) {
+                    if (e < v.ip_cap) {
+                        v.it_node[e] = node[q][j];
+                        v.it_first[e] = ixp[j];
+                        v.it_cold[e] = cnt[q][j];
+                        v.it_cs[e] = static_cast<uint8_t>(cs[q][j]);
+                        s_C[e] = static_cast<uint8_t>(cnt[q][j]);
+                    } else {
+                        s_over = 1;
+                    }
                 }
+                if (((lbits >> (2 * d + j)) & 1u) && e < v.ip_cap) v.it_end[e] = ixp[j] + 1u;
+                ixp[j] = ix;
             }
-            if (ls[j] && e < v.ip_cap) v.it_end[e] = ixp[j] + 1u;
-            hbits |= hd[j] << (2 * d + j);
-            lbits |= ls[j] << (2 * d + j);
-            ixp[j] = ix;
+            if (tid == 0) s_base[d] = items;
+            items += (n[q / 2] >> (16 * (q & 1))) & 0xFFFFu;
         }
-        if (tid == 0) s_base[d] = items;
-        items += n;
-        __syncthreads();  // s_b is rewritten by the next level
     }
     if (tid == 0) s_base[hmax] = items;
     __syncthreads();
@@ -1777,12 +1816,13 @@ __device__ __forceinline__ void ph_small_plan(TreeView<K> t, Ins<K> v, int H) {
             kk[i] = in ? split_pieces(static_cast<uint64_t>(C) + (hi - lo)) : 1u;
             f[i] = in ? kk[i] - 1u : 0u;
         }
-        uint32_t nnew;
-        const uint32_t of = plan_scan<NT>(f[0] + f[1], sh, &nnew);
+        uint32_t of[1] = {f[0] + f[1]}, nn[1];
+        plan_scan<NT, 1>(of, sh, nn);  // (the barriers around s_a, s_k separate its uses of sh)
+        const uint32_t nnew = nn[0];
         // s_k now holds this level's piece-offset prefix, s_k[nd] its total
         for (int i = 0; i < 2; ++i) {
             const uint32_t jt = 2 * tid + i;
-            const uint32_t o = of + (i ? f[0] : 0u);
+            const uint32_t o = of[0] + (i ? f[0] : 0u);
             if (jt < nd) s_k[jt] = o;
             if (jt < nd && bd + jt < total) {
                 v.it_k[bd + jt] = kk[i];
@@ -1797,6 +1837,19 @@ __device__ __forceinline__ void ph_small_plan(TreeView<K> t, Ins<K> v, int H) {
             s_st.lvl_psep[d] = psep;
         }
         psep += nnew;
+        if (nnew == 0) {  // nothing splits above
+            for (uint32_t i = s_base[d + 1] + tid; i < total; i += NT) {
+                v.it_k[i] = 1u;
+                v.it_off[i] = 0u;
+            }
+            for (int a = d + 1 + static_cast<int>(tid); a < hmax; a += NT) {
+                s_st.lvl_count[a] = s_base[a + 1] - s_base[a];
+                s_st.lvl_base[a] = s_base[a];
+                s_st.lvl_new[a] = 0;
+                s_st.lvl_psep[a] = psep;
+            }
+            break;
+        }
         __syncthreads();
     }
     if (tid == 0) {
@@ -2124,6 +2177,25 @@ static void launch_locate(const TreeView<K>& t, const Ins<K>& v, const LaunchCfg
     else launch_locate_lv<K, 16, 1>(t, v, cfg, B, status, s);
 }
 
+template <class K, int LV, bool INS>
+static void launch_rank_locate_t(const TreeView<K>& t, const Ins<K>& v, const K* keys, const K* vals, uint32_t B,
+                                 uint8_t* status, hipStream_t s) {
+    const uint32_t lds = LV > 0 ? MirrorLayout<K>::bytes(mirror_nodes_for_levels(LV)) : 0;
+    hipLaunchKernelGGL((k_rank_locate<K, LV, INS>), dim3((B + kBlk / 16 - 1) / (kBlk / 16)), dim3(kBlk), lds, s, t, v,
+                       keys, vals, B, status);
+}
+
+template <class K, bool INS>
+static void launch_rank_locate(const TreeView<K>& t, const Ins<K>& v, const LaunchCfg& cfg, const K* keys,
+                               const K* vals, uint32_t B, uint8_t* status, hipStream_t s) {
+    switch (cfg.lds_levels) {
+        case 0: launch_rank_locate_t<K, 0, INS>(t, v, keys, vals, B, status, s); break;
+        case 1: launch_rank_locate_t<K, 1, INS>(t, v, keys, vals, B, status, s); break;
+        case 3: launch_rank_locate_t<K, 3, INS>(t, v, keys, vals, B, status, s); break;
+        default: launch_rank_locate_t<K, 2, INS>(t, v, keys, vals, B, status, s); break;
+    }
+}
+
 // highest tree height the pools allow (non-root inner nodes have >= 8
 // children, the root >= 2)
 static int height_bound(uint64_t leaf_cap) {
@@ -2171,11 +2243,7 @@ void launch_insert(const TreeView<K>& t, const InsertCtx& c, const K* keys, cons
         return;
     }
     if (B <= kSmallInsert) {
-        const uint32_t presorted = B > kFusedSortMax ? 1u : 0u;
-        if (presorted) rank_sort_small<K>(keys, static_cast<uint32_t>(B), v.sk, v.si, nullptr, 0, s);
-        hipLaunchKernelGGL(k_small_prefix<K>, dim3(1), dim3(kSmallBlock), 0, s, v, t.hdr, keys, vals,
-                           static_cast<uint32_t>(B), status, presorted);
-        launch_locate<K>(t, v, c.cfg, B, status, s);
+        launch_rank_locate<K, true>(t, v, c.cfg, keys, vals, static_cast<uint32_t>(B), status, s);
         if (B <= 128) hipLaunchKernelGGL((k_small_plan<K, 64>), dim3(1), dim3(64), 0, s, t, v, H);
         else if (B <= 512) hipLaunchKernelGGL((k_small_plan<K, 256>), dim3(1), dim3(256), 0, s, t, v, H);
         else hipLaunchKernelGGL((k_small_plan<K, kSmallBlock>), dim3(1), dim3(kSmallBlock), 0, s, t, v, H);
@@ -2250,35 +2318,6 @@ __device__ __forceinline__ void note_inner_write(const Ins<K>& v, int depth) {
     if (depth < kMirrorDepth) v.st->mirror_dirty = 1u;
 }
 constexpr uint64_t kDelListScan = 16384;  // above: the merge list comes from a scan, in key order
-
-// Batches up to 2048 keys (after the rank sort, which also cleared the
-// batch state): one workgroup, two sorted positions per thread, finds the
-// distinct keys, writes the statuses of repeats and the batch state.
-template <class K>
-__global__ __launch_bounds__(1024) void k_del_small_prefix(Ins<K> v, const DevHeader* hdr, uint32_t B,
-                                                           uint8_t* __restrict__ status) {
-    __shared__ uint32_t sh[33];
-    const uint32_t t = threadIdx.x, p0 = 2 * t, p1 = p0 + 1;
-    const bool h0 = p0 < B && (p0 == 0 || v.sk[p0] != v.sk[p0 - 1]);
-    const bool h1 = p1 < B && v.sk[p1] != v.sk[p0];
-    if (p0 < B && !h0) status[v.si[p0]] = 0;  // ABSENT: an earlier occurrence deleted it
-    if (p1 < B && !h1) status[v.si[p1]] = 0;
-    uint32_t tot;
-    const uint32_t base = block_excl_scan<uint32_t>((h0 ? 1u : 0u) + (h1 ? 1u : 0u), sh, &tot);
-    if (h0) {
-        v.uk[base] = v.sk[p0];
-        v.upos[base] = p0;
-    }
-    if (h1) {
-        const uint32_t e = base + (h0 ? 1u : 0u);
-        v.uk[e] = v.sk[p1];
-        v.upos[e] = p1;
-    }
-    if (t == 0) {
-        v.st->U = tot;
-        v.st->height = hdr->height;
-    }
-}
 
 // first distinct key of its leaf's run (keys are sorted, so a leaf's keys
 // are consecutive)
@@ -2934,18 +2973,15 @@ const uint32_t* launch_delete(const TreeView<K>& t, const InsertCtx& c, const K*
         return &v.st->rebuild;
     }
     if (B <= kSmallInsert) {
-        rank_sort_small<K>(keys, static_cast<uint32_t>(B), v.sk, v.si, reinterpret_cast<uint32_t*>(v.st),
-                           static_cast<uint32_t>(sizeof(InsState) / 4), s);
-        hipLaunchKernelGGL(k_del_small_prefix<K>, dim3(1), dim3(1024), 0, s, v, t.hdr, static_cast<uint32_t>(B),
-                           status);
+        launch_rank_locate<K, false>(t, v, c.cfg, keys, nullptr, static_cast<uint32_t>(B), status, s);
     } else {
         sort_from<K>(keys, v.sk, v.si, v.sk2, v.si2, B, v.sort_tmp, s, &t.hdr->error, kErrInternal);
         hipLaunchKernelGGL(k_ch_heads<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, t.hdr, B, cb.tiles, uint8_t(0), status,
                            sums);
         hipLaunchKernelGGL(k_ch_unique<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, B, cb.tiles,
                            static_cast<const K*>(nullptr), sums);
+        launch_locate<K>(t, v, c.cfg, B, status, s);
     }
-    launch_locate<K>(t, v, c.cfg, B, status, s);
     // two keys in flight per lane group once every group of the grid has more
     const uint32_t gl = grid_for(B * kSlots, kBlk);
     uint32_t* parts = reinterpret_cast<uint32_t*>(v.sk2);

@@ -448,10 +448,8 @@ constexpr uint32_t kRankLanes = 16;  // lanes sharing one element's count
 
 template <class K>
 __global__ __launch_bounds__(256) void k_rank_sort(const K* __restrict__ keys, uint32_t B, K* __restrict__ osk,
-                                                   uint32_t* __restrict__ osi, uint32_t* zero, uint32_t zero_words) {
+                                                   uint32_t* __restrict__ osi) {
     __shared__ K sk[kRankSortMax];
-    if (zero && blockIdx.x == 0)
-        for (uint32_t i = threadIdx.x; i < zero_words; i += blockDim.x) zero[i] = 0;
     for (uint32_t i = threadIdx.x; i < B; i += blockDim.x) sk[i] = keys[i];
     __syncthreads();
     const uint32_t e = (blockIdx.x * blockDim.x + threadIdx.x) / kRankLanes, l = threadIdx.x % kRankLanes;
@@ -485,17 +483,13 @@ __global__ __launch_bounds__(256) void k_rank_sort(const K* __restrict__ keys, u
 }
 
 template <class K>
-void rank_sort_small(const K* keys, uint32_t B, K* sk, uint32_t* si, uint32_t* zero, uint32_t zero_words,
-                     hipStream_t s) {
+void rank_sort_small(const K* keys, uint32_t B, K* sk, uint32_t* si, hipStream_t s) {
     const uint32_t grid = (B * kRankLanes + 255) / 256;
-    hipLaunchKernelGGL(k_rank_sort<K>, dim3(grid < 1 ? 1 : grid), dim3(256), 0, s, keys, B, sk, si, zero,
-                       zero_words);
+    hipLaunchKernelGGL(k_rank_sort<K>, dim3(grid < 1 ? 1 : grid), dim3(256), 0, s, keys, B, sk, si);
 }
 
-template void rank_sort_small<uint32_t>(const uint32_t*, uint32_t, uint32_t*, uint32_t*, uint32_t*, uint32_t,
-                                        hipStream_t);
-template void rank_sort_small<uint64_t>(const uint64_t*, uint32_t, uint64_t*, uint32_t*, uint32_t*, uint32_t,
-                                        hipStream_t);
+template void rank_sort_small<uint32_t>(const uint32_t*, uint32_t, uint32_t*, uint32_t*, hipStream_t);
+template void rank_sort_small<uint64_t>(const uint64_t*, uint32_t, uint64_t*, uint32_t*, hipStream_t);
 
 template void sort_from<uint32_t>(const uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint64_t, void*,
                                   hipStream_t, uint32_t*, uint32_t);
