@@ -1331,11 +1331,20 @@ __global__ __launch_bounds__(kFusedBlock) void k_small_apply(TreeView<K> t, Ins<
 }
 
 // The parent levels from d0 on, the root growth, the commit and the mirror
-// in one workgroup: the host starts it at the first level whose item bound
-// is at most kTailApplyMax, one round of kNodeLanes-lane groups, so the
-// upper levels (and the levels above the tree's current height, which the
-// host cannot see) cost no launch each.
-constexpr uint32_t kTailApplyMax = kFusedMax;
+// in one workgroup: the host starts it at the first level where that is no
+// slower than a launch of its own, so the upper levels (and the levels above
+// the tree's current height, which the host cannot see) cost none.  The
+// workgroup's 64 groups of kNodeLanes walk a level's items in rounds of
+// 2 us, a launch costs as much or a little more:
+//  - batches of at most kTailItems keys go to the tail from the first level
+//    on: insert, lookup and delete of 300 keys on 2^24 77.6 us, 85.0 with the
+//    levels launched; of 1000 keys 104.4, and 88.8 launched;
+//  - else the tail starts at the first level that can hold at most kTailNodes
+//    nodes.  That bound counts the whole leaf pool and 8 children a node; a
+//    level holds nearer a tenth of it, so a round or two (1000 keys 88.8 us,
+//    93.7 with the bound at one round).
+constexpr uint32_t kTailItems = 384;
+constexpr uint32_t kTailNodes = 1024;
 
 template <class K>
 __global__ __launch_bounds__(kFusedBlock) void k_apply_tail(TreeView<K> t, Ins<K> v, int d0, int H) {
@@ -2217,7 +2226,7 @@ static void launch_apply(const TreeView<K>& t, const Ins<K>& v, uint64_t B, uint
     if (updates) hipLaunchKernelGGL(k_apply_updates<K>, dim3(gB), dim3(kBlk), 0, s, t, v);
     hipLaunchKernelGGL(k_apply_leaves<K>, dim3(grid_for(B, kBlk / kNodeLanes)), dim3(kBlk), 0, s, t, v);
     int d0 = 1;
-    while (d0 < H && level_items_bound(B, leaf_cap, d0) > kTailApplyMax) ++d0;
+    while (B > kTailItems && d0 < H && level_items_bound(~0ull, leaf_cap, d0) > kTailNodes) ++d0;
     for (int d = 1; d < d0; ++d)
         hipLaunchKernelGGL(k_apply_inner<K>, dim3(grid_for(B, kBlk / kNodeLanes)), dim3(kBlk), 0, s, t, v, d);
     hipLaunchKernelGGL(k_apply_tail<K>, dim3(1), dim3(kFusedBlock), 0, s, t, v, d0, H);
