@@ -1212,24 +1212,76 @@ __device__ __forceinline__ void ph_commit(TreeView<K> t, Ins<K> v) {
 }
 
 // The upper levels of a large batch's plan, from d0 on, and the capacity check
-// in one workgroup, tile after tile.
+// in one workgroup, tile after tile.  A thread takes kChItems consecutive
+// items of a tile, all their reads in flight, and scans their pieces from its
+// registers; it is bound by a tile's three dependent reads and its barriers.
+// Above a level where nothing splits no level does, and nothing reads their
+// items but the check, the root's.  65536 new keys on 2^24 take 5.9 us, 100
+// with an item at a time per thread, a second pass for the offsets and every
+// level walked; 4096 new keys 13.9, 23.6.
 constexpr int kTailBlock = 1024;
 
 template <class K>
 __global__ __launch_bounds__(kTailBlock) void k_plan_tail(TreeView<K> t, Ins<K> v, int d0) {
     __shared__ uint32_t sh[33];
     const int h = static_cast<int>(v.st->height);
+    uint32_t bc = 0, nc = 0, split = 0, psep = 0;  // the level below: first item, items, new nodes; separators so far
+    if (d0 > 0) {
+        bc = v.st->lvl_base[d0 - 1];
+        nc = v.st->lvl_count[d0 - 1];
+        split = v.st->lvl_new[d0 - 1];
+        psep = v.st->lvl_psep[d0 - 1] + split;
+    }
     for (int d = d0; d < h && !v.st->overflow; ++d) {
         const uint32_t n = v.st->lvl_count[d], base = v.st->lvl_base[d];
-        for (uint32_t i = threadIdx.x; i < n; i += kTailBlock) v.it_k[base + i] = item_pieces<K>(v, d, i);
-        __syncthreads();
         uint32_t at = 0;
-        for (uint64_t i0 = 0; i0 < n; i0 += kTailBlock * kChItems)
-            at += piece_offsets<K, kTailBlock>(v, base, i0 + threadIdx.x * kChItems, n, at, sh);
+        if (d > 0 && split == 0) {
+            if (threadIdx.x == 0 && d == h - 1 && n) v.it_k[base] = 1u;
+        } else {
+            for (uint32_t t0 = 0; t0 < n; t0 += kTailBlock * kChItems) {
+                const uint32_t i0 = t0 + threadIdx.x * kChItems;
+                uint32_t first[kChItems], end[kChItems], k[kChItems];
+#pragma unroll
+                for (uint32_t j = 0; j < kChItems; ++j) {
+                    const bool in = i0 + j < n;
+                    first[j] = in ? v.it_first[base + i0 + j] : 0u;
+                    end[j] = in ? v.it_end[base + i0 + j] : 0u;
+                    k[j] = in ? v.it_cold[base + i0 + j] : 0u;
+                }
+                if (d > 0) {  // an item gains a child per piece beyond the first of its child items
+#pragma unroll
+                    for (uint32_t j = 0; j < kChItems; ++j) {
+                        const bool in = i0 + j < n;
+                        first[j] = in ? v.it_off[bc + first[j]] : 0u;
+                        end[j] = in ? (end[j] < nc ? v.it_off[bc + end[j]] : split) : 0u;
+                    }
+                }
+                uint32_t sum = 0;
+#pragma unroll
+                for (uint32_t j = 0; j < kChItems; ++j) {
+                    k[j] = i0 + j < n ? split_pieces(static_cast<uint64_t>(k[j]) + (end[j] - first[j])) : 1u;
+                    sum += k[j] - 1u;
+                }
+                uint32_t tot;
+                uint32_t off = at + block_excl_scan<uint32_t>(sum, sh, &tot);
+#pragma unroll
+                for (uint32_t j = 0; j < kChItems; ++j)
+                    if (i0 + j < n) {
+                        v.it_k[base + i0 + j] = k[j];
+                        v.it_off[base + i0 + j] = off;
+                        off += k[j] - 1u;
+                    }
+                at += tot;
+            }
+        }
         if (threadIdx.x == 0) {
             v.st->lvl_new[d] = at;
-            v.st->lvl_psep[d] = d ? v.st->lvl_psep[d - 1] + v.st->lvl_new[d - 1] : 0u;
+            v.st->lvl_psep[d] = psep;
         }
+        psep += at;
+        bc = base;
+        nc = n;
+        split = at;
         __syncthreads();
     }
     ph_check<K>(t, v, threadIdx.x, kTailBlock);
@@ -2270,8 +2322,10 @@ void launch_insert(const TreeView<K>& t, const InsertCtx& c, const K* keys, cons
     hipLaunchKernelGGL((k_ch_collect<K, true>), dim3(cb.n), dim3(kChBlock), 0, s, t, v, cb.tiles, sums);
     hipLaunchKernelGGL(k_ch_level_count<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, cb.tiles, sums);
     hipLaunchKernelGGL(k_ch_level_items<K>, dim3(cb.n), dim3(kChBlock), 0, s, v, cb.tiles, sums);
-    // the pieces of the lower levels by chunks, of the others in one workgroup:
-    // a tree level has at most an eighth of the nodes of the one below
+    // the pieces of the lower levels by chunks, of the others in one workgroup
+    // (4 us per 8192 items where the two chunk kernels take 13 a level): a tree
+    // level has at most an eighth of the nodes of the one below.  2^20 keys on
+    // 2^24: 835 us a pass, 846 with the third level in the workgroup
     const int d0 = B <= 8192 ? 0 : (B <= 65536 ? 1 : 3);
     for (int d = 0; d < d0; ++d) {
         const Chunks cd = chunks_for(level_items_bound(B, c.leaf_cap, d));
