@@ -46,6 +46,7 @@
 namespace gt {
 
 constexpr int kBlk = 256;
+constexpr uint32_t kSmallInsert = 2048;  // keys of the small path (below)
 
 struct InsState {
     uint32_t U, R;
@@ -371,14 +372,14 @@ __global__ __launch_bounds__(kBlk) void k_locate(TreeView<K> t, Ins<K> v, uint8_
     ph_locate<K, G, QPG, LV, kBlk>(t, v, status);
 }
 
-// A batch of at most kRankSortMax keys, sorted, deduplicated and located in
+// A batch of at most kSmallInsert keys, sorted, deduplicated and located in
 // one launch.  Every workgroup holds the batch in LDS and 16 lanes take one
 // key: they count the keys before it in (key, index) order, each lane a
 // sixteenth of the batch, and then descend with it.  A key's records go to
 // its rank, repeats included, so no pass compacts the distinct keys first
 // (U is the batch size here): a repeat is neither found nor new, it only
 // reports what a second occurrence reports, and the first occurrence carries
-// the last one's value.  1000 keys on 2^24 take 9.4 us, where the rank sort,
+// the last one's value.  1000 keys on 2^24 take 8.5 us, where the rank sort,
 // the compaction in one workgroup and locate took three launches of 4.5, 3.0
 // and 7.5.  The first workgroup clears the batch state.
 template <class K, int LV, bool INS>
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(kBlk) void k_rank_locate(TreeView<K> t, Ins<K> v, c
     constexpr int G = 16;
     using T = Trav<K, G>;
     extern __shared__ __align__(16) uint8_t lds[];
-    __shared__ K s_key[kRankSortMax];
+    __shared__ K s_key[kSmallInsert];
     if (blockIdx.x == 0) {
         uint32_t* st = reinterpret_cast<uint32_t*>(v.st);
         for (uint32_t i = threadIdx.x; i < sizeof(InsState) / 4; i += kBlk)
@@ -408,34 +409,40 @@ __global__ __launch_bounds__(kBlk) void k_rank_locate(TreeView<K> t, Ins<K> v, c
     const uint32_t e = (blockIdx.x * kBlk + threadIdx.x) / G;
     const bool mine = e < B && gl == 0;
     K key[1] = {e < B ? s_key[e] : K(0)};
-    uint32_t before = 0, same = 0, last = e;  // keys before; equal keys before; the last equal key
     // lane l takes keys l, l + 16, ...: neighbouring lanes read neighbouring
     // LDS words (no bank conflicts), eight reads in flight
     constexpr uint32_t R = 8;
+    uint32_t n = 0;  // smaller keys, and in the upper half smaller or equal ones: at most kSmallInsert
     uint32_t j = static_cast<uint32_t>(gl);
-    auto take = [&](K kj, uint32_t jj) {
-        const bool eq = kj == key[0];
-        before += kj < key[0] ? 1u : 0u;
-        same += eq && jj < e ? 1u : 0u;
-        if (eq && jj > last) last = jj;
-    };
     for (; j + G * (R - 1) < B; j += G * R) {
         K kj[R];
 #pragma unroll
         for (uint32_t x = 0; x < R; ++x) kj[x] = s_key[j + G * x];
 #pragma unroll
-        for (uint32_t x = 0; x < R; ++x) take(kj[x], j + G * x);
+        for (uint32_t x = 0; x < R; ++x) {
+            n += kj[x] < key[0] ? 1u : 0u;
+            n += kj[x] <= key[0] ? 0x10000u : 0u;
+        }
     }
-    for (; j < B; j += G) take(s_key[j], j);
-    uint32_t n = before << 16 | same;  // both at most kRankSortMax
+    for (; j < B; j += G) n += (s_key[j] < key[0] ? 1u : 0u) + (s_key[j] <= key[0] ? 0x10000u : 0u);
 #pragma unroll
-    for (int m = 1; m < G; m <<= 1) {
-        n += static_cast<uint32_t>(__shfl_xor(static_cast<int>(n), m, 64));
-        const uint32_t o = static_cast<uint32_t>(__shfl_xor(static_cast<int>(last), m, 64));
-        last = o > last ? o : last;
+    for (int m = 1; m < G; m <<= 1) n += static_cast<uint32_t>(__shfl_xor(static_cast<int>(n), m, 64));
+    uint32_t same = 0, last = e;  // equal keys before, the last equal key
+    const uint32_t below = n & 0xFFFFu;
+    if ((n >> 16) - below > 1u) {  // the key repeats (the same for its 16 lanes)
+        for (j = static_cast<uint32_t>(gl); j < B; j += G)
+            if (s_key[j] == key[0]) {
+                same += j < e ? 1u : 0u;
+                last = j > last ? j : last;
+            }
+#pragma unroll
+        for (int m = 1; m < G; m <<= 1) {
+            same += static_cast<uint32_t>(__shfl_xor(static_cast<int>(same), m, 64));
+            const uint32_t o = static_cast<uint32_t>(__shfl_xor(static_cast<int>(last), m, 64));
+            last = o > last ? o : last;
+        }
     }
-    same = n & 0xFFFFu;
-    const uint32_t u = (n >> 16) + same;
+    const uint32_t u = below + same;
     K val = K(0);
     if constexpr (INS) {
         if (mine) val = vals[last];
@@ -1645,8 +1652,6 @@ static bool single_key_insert_on() { return g_single_key.load(std::memory_order_
 // Batches of 2 to kFusedMax keys run all of it in one launch by default
 // (k_ins_small, below), with the same results.
 
-constexpr uint32_t kSmallInsert = 2048;
-static_assert(kSmallInsert <= kRankSortMax, "the small path ranks with k_rank_locate");
 constexpr int kSmallBlock = 1024;
 
 // Exclusive scans of W words over the plan's workgroup with one barrier: every

@@ -60,10 +60,12 @@ __device__ __forceinline__ T block_excl_scan(T v, T* sh, T* total) {
 
 // ------------------------------------------------------------ host side
 
-// Largest batch rank_sort_small takes (all keys sit in each workgroup's LDS).
+// Largest batch rank_sort_small takes (all keys sit in each workgroup's LDS);
+// up to kRankSortMax keys callers need no other buffer for a sort.
+constexpr uint32_t kRankSortTop = 8192;
 constexpr uint32_t kRankSortMax = 2048;
 
-// Stable sort of B <= kRankSortMax keys by rank: sk[r] = keys[i] and
+// Stable sort of B <= kRankSortTop keys by rank: sk[r] = keys[i] and
 // si[r] = i, where r is the number of pairs (keys[j], j) before (keys[i], i)
 // in (key, index) order.
 template <class K>
