@@ -57,6 +57,8 @@ constexpr uint32_t kSsSegments = 256;                    // segments of the firs
 constexpr uint64_t kSsOneLevel = 1ull << 20;
 constexpr uint64_t kSsMax = 1ull << 26;                  // largest input (256 segments of 256 groups)
 constexpr uint64_t kSsSmallMean = 512;
+constexpr uint32_t kSsRankSample = 1024;                 // largest sample ranked by counting
+constexpr uint32_t kSsRankStep = 128;                    // sample pairs a step of k_ss_sample_rank compares
 
 // What one level sorts by: `segs` segments of the input (one for the first
 // level), cut into `groups` groups each.
@@ -300,6 +302,78 @@ __global__ __launch_bounds__(1024) void k_ss_sample(const K* __restrict__ kin, c
         for (uint32_t i = tid; i + 1 < len; i += blockDim.x)
             if (m && a[w][ss_pad(i)] == a[w][ss_pad(i + 1)] && p[w][ss_pad(i)] != p[w][ss_pad(i + 1)])
                 atomicOr(dup, 1u);
+}
+
+// Sample of the first level by counting: every workgroup holds all S sampled
+// pairs and ranks a few of them, 16 lanes a pair; a pair whose rank is the
+// last of `over` is a splitter.  S^2 comparisons over S / 16 groups of lanes
+// are one short chain where sorting the sample in one workgroup is ten rounds
+// of dependent LDS reads: for the 1024 pairs of 50000 keys 6 us, 11.6 by
+// merging.  Up to kSsRankSample pairs; 4096 take 20 us longer than their runs
+// sorted by eight workgroups and ranked by search (the level-wise lookup of
+// 65537 keys 52.0 us, so 72.3).  Clears what k_ss_sample clears.
+constexpr int kSsRankThreads = 256;
+
+template <class K, bool TIE>
+__global__ __launch_bounds__(kSsRankThreads) void k_ss_sample_rank(
+    const K* __restrict__ kin, const uint32_t* __restrict__ pin, uint32_t n, uint32_t groups, uint32_t over, K* gk,
+    uint32_t* gp, uint32_t* cnt, uint32_t* cur, uint32_t* list, uint32_t* fail, uint32_t force, uint32_t* err,
+    uint32_t err_bit, uint32_t* dup) {
+    constexpr uint32_t G = 16, R = kSsRankStep / G;
+    __shared__ K a[kSsRankSample];
+    __shared__ uint32_t p[kSsRankSample];
+    const uint32_t tid = threadIdx.x, S = groups * over;  // S a multiple of kSsRankStep
+    if (blockIdx.x == 0) {
+        for (uint32_t i = tid; i < groups; i += kSsRankThreads) {
+            cnt[i] = 0;
+            cur[i] = 0;
+        }
+        if (tid == 0) {
+            list[0] = 0;
+            *fail = force;
+            if (force && err) atomicOr(err, err_bit);
+        }
+    }
+    for (uint32_t i = tid; i < S; i += kSsRankThreads) {
+        const uint32_t at = ss_sample_at(i, S, n);
+        a[i] = kin[at];
+        p[i] = pin ? pin[at] : at;
+    }
+    __syncthreads();
+    const uint32_t e = (blockIdx.x * kSsRankThreads + tid) / G, l = tid % G;
+    if (e >= S) return;  // whole groups of lanes leave together
+    const K ke = a[e];
+    uint32_t c = 0;  // smaller keys, and in the upper half smaller or equal ones
+    for (uint32_t j = l; j < S; j += G * R) {
+        K kj[R];
+#pragma unroll
+        for (uint32_t u = 0; u < R; ++u) kj[u] = a[j + G * u];
+#pragma unroll
+        for (uint32_t u = 0; u < R; ++u) {
+            c += kj[u] < ke ? 1u : 0u;
+            c += kj[u] <= ke ? 0x10000u : 0u;
+        }
+    }
+#pragma unroll
+    for (uint32_t m = 1; m < G; m <<= 1) c += __shfl_xor(c, static_cast<int>(m), 64);
+    uint32_t rank = c & 0xFFFFu;
+    if ((c >> 16) - rank > 1u) {  // equal keys, by position, then by sample (a pair sampled twice)
+        const uint32_t pe = p[e];
+        uint32_t before = 0, other = 0;
+        for (uint32_t j = l; j < S; j += G)
+            if (a[j] == ke) {
+                before += p[j] < pe || (p[j] == pe && j < e) ? 1u : 0u;
+                other |= p[j] != pe ? 1u : 0u;
+            }
+#pragma unroll
+        for (uint32_t m = 1; m < G; m <<= 1) before += __shfl_xor(before, static_cast<int>(m), 64);
+        rank += before;
+        if (!TIE && dup && other) atomicOr(dup, 1u);
+    }
+    if (l == 0 && rank % over == over - 1 && rank / over + 1 < groups) {
+        gk[rank / over] = ke;
+        gp[rank / over] = p[e];
+    }
 }
 
 // Rank of every pair of the sorted sample runs among all of them (one search
@@ -1008,17 +1082,22 @@ static void ss_partition(const SsPlan& pl, uint8_t* tmp, const K* src, const P* 
         // ties go by the position: the payload where it is one
         const uint32_t* tie = nullptr;
         if constexpr (TIE) tie = in;
-        const uint32_t len = v.groups * v.over / v.runs;
-        hipLaunchKernelGGL((k_ss_sample<K, TIE>), dim3(v.segs, v.runs), dim3(len <= 256 ? 256 : (len <= 512 ? 512 : 1024)),
-                           0, s, kin, tie, n, seg, v.groups, v.over, v.runs, gk, gp, sk, sp, cnt, cur, list, fail,
-                           force, err, err_bit, dup);
-        auto rank = [&](auto R) {
-            constexpr int N = decltype(R)::value;
-            hipLaunchKernelGGL((k_ss_rank<K, TIE, N>), dim3(N * kSsRun / 256), dim3(256), 0, s, sk, sp, v.over, gk,
-                               gp, dup);
-        };
-        if (v.runs == 8) rank(std::integral_constant<int, 8>{});
-        else if (v.runs == kSsMaxRuns) rank(std::integral_constant<int, kSsMaxRuns>{});
+        const uint32_t S = v.groups * v.over, len = S / v.runs;
+        if (v.segs == 1 && S >= kSsRankStep && S <= kSsRankSample) {
+            hipLaunchKernelGGL((k_ss_sample_rank<K, TIE>), dim3(S * 16 / kSsRankThreads), dim3(kSsRankThreads), 0, s,
+                               kin, tie, n, v.groups, v.over, gk, gp, cnt, cur, list, fail, force, err, err_bit, dup);
+        } else {
+            hipLaunchKernelGGL((k_ss_sample<K, TIE>), dim3(v.segs, v.runs), dim3(len <= 256 ? 256 : (len <= 512 ? 512 : 1024)),
+                               0, s, kin, tie, n, seg, v.groups, v.over, v.runs, gk, gp, sk, sp, cnt, cur, list, fail,
+                               force, err, err_bit, dup);
+            auto rank = [&](auto R) {
+                constexpr int N = decltype(R)::value;
+                hipLaunchKernelGGL((k_ss_rank<K, TIE, N>), dim3(N * kSsRun / 256), dim3(256), 0, s, sk, sp, v.over, gk,
+                                   gp, dup);
+            };
+            if (v.runs == 8) rank(std::integral_constant<int, 8>{});
+            else if (v.runs == kSsMaxRuns) rank(std::integral_constant<int, kSsMaxRuns>{});
+        }
         // tiles: as long as they leave two workgroups for every CU
         auto tiles = [&](auto items) {
             constexpr int N = decltype(items)::value;
