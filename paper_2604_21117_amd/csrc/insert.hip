@@ -2385,6 +2385,7 @@ template <class K>
 __device__ __forceinline__ void note_inner_write(const Ins<K>& v, int depth) {
     if (depth < kMirrorDepth) v.st->mirror_dirty = 1u;
 }
+constexpr uint64_t kDelListHere = 2048;   // up to here the leaf kernel lists the merges
 constexpr uint64_t kDelListScan = 16384;  // above: the merge list comes from a scan, in key order
 
 // first distinct key of its leaf's run (keys are sorted, so a leaf's keys
@@ -2409,9 +2410,10 @@ __device__ __forceinline__ uint32_t row_or(uint32_t x) {
 // and the leaf's lines are written whole.  A group's first read is its 16
 // next keys' records, its second the leaf of its own key, needed or not, so a
 // leaf costs two dependent rounds; R keys a group are in flight.  Returns
-// how many keys the wave removed; k_del_list then lists the leaves left below
-// half full, one thread per distinct key.
-template <class K, int R>
+// how many keys the wave removed.  The leaves left below half full are listed
+// for the merges: here (LIST, an atomic for the wave's four groups, in any
+// order) or, for larger batches, by the kernels after this one.
+template <class K, int R, bool LIST>
 __device__ __forceinline__ uint32_t ph_del_leaf(TreeView<K> t, Ins<K> v) {
     if (t.hdr->error & kErrInternal) return 0;  // e.g. the batch's device sort gave up
     const uint64_t U = v.st->U;
@@ -2475,6 +2477,9 @@ __device__ __forceinline__ uint32_t ph_del_leaf(TreeView<K> t, Ins<K> v) {
             if (head[r] && s == 0) {
                 v.f0[u] = under ? 1u : 0u;
                 v.nu[u] = under ? 1u : 0u;
+                if constexpr (LIST) {
+                    if (under) v.f1[atomicAdd(&v.st->merges, 1u)] = static_cast<uint32_t>(u);
+                }
             }
             // slot s gets the pair of the s-th kept slot; past the count the
             // last kept key with an all-ones value
@@ -2524,10 +2529,10 @@ __device__ __forceinline__ uint32_t ph_del_leaf(TreeView<K> t, Ins<K> v) {
 // buffer, at least a word per workgroup), which the commit adds up: one add a
 // wave to a single word took 12 ns each, 390 of this kernel's 394 us for 2^20
 // keys on 2^24 (88 now).
-template <class K, int R>
+template <class K, int R, bool LIST>
 __global__ __launch_bounds__(kBlk) void k_del_leaf(TreeView<K> t, Ins<K> v, uint32_t* __restrict__ parts) {
     __shared__ uint32_t s_del[kBlk / 64];
-    const uint32_t del = ph_del_leaf<K, R>(t, v);
+    const uint32_t del = ph_del_leaf<K, R, LIST>(t, v);
     if ((threadIdx.x & 63) == 0) s_del[threadIdx.x / 64] = del;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -2537,20 +2542,18 @@ __global__ __launch_bounds__(kBlk) void k_del_leaf(TreeView<K> t, Ins<K> v, uint
     }
 }
 
-// The leaf runs left below half full, listed for the merge pass: small
-// batches append with an atomic (any order); large ones place each run at
-// its prefix-scan position, so the list is in key order.
+// The leaf runs left below half full, listed for the merge pass: batches of
+// up to kDelListHere keys list them where they arise, an atomic per wave of
+// the leaf kernel (1000 keys on 2^24: 2.7 us of this kernel and its launch
+// saved; the counter takes one atomic in 12 ns, so not for more), those up to
+// kDelListScan here, an atomic per 64 keys, both in any order; larger ones
+// place each run at its prefix-scan position, so the list is in key order.
 template <class K>
-__device__ __forceinline__ void ph_del_list(TreeView<K> t, Ins<K> v) {
+__global__ void k_del_list(TreeView<K> t, Ins<K> v) {
     if (t.hdr->error & kErrInternal) return;
     const uint64_t U = v.st->U;
     for (uint64_t u = gtid(); u < U; u += gstride())
         if (v.nu[u]) v.f1[atomicAdd(&v.st->merges, 1u)] = static_cast<uint32_t>(u);
-}
-
-template <class K>
-__global__ void k_del_list(TreeView<K> t, Ins<K> v) {
-    ph_del_list<K>(t, v);
 }
 
 // A wave's LDS for merging one listed parent.
@@ -2984,11 +2987,9 @@ __global__ __launch_bounds__(kDelOneBlock) void k_del_small(TreeView<K> t, Ins<K
     ph_locate<K, 16, 1, 2, kDelOneBlock>(t, v, status);
     phase_boundary();
     {
-        const uint32_t del = ph_del_leaf<K, 1>(t, v);
+        const uint32_t del = ph_del_leaf<K, 1, true>(t, v);
         if ((tid & 63) == 0 && del) atomicAdd(&v.st->deleted, del);
     }
-    phase_boundary();
-    ph_del_list<K>(t, v);
     phase_boundary();
     ph_del_merge<K>(t, v, false, tid / 64, kDelOneBlock / 64, s_merge[tid / 64]);
     phase_boundary();
@@ -3053,15 +3054,17 @@ const uint32_t* launch_delete(const TreeView<K>& t, const InsertCtx& c, const K*
     // two keys in flight per lane group once every group of the grid has more
     const uint32_t gl = grid_for(B * kSlots, kBlk);
     uint32_t* parts = reinterpret_cast<uint32_t*>(v.sk2);
-    if (B >= 2ull * gl * (kBlk / kSlots))
-        hipLaunchKernelGGL((k_del_leaf<K, 2>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
+    if (B <= kDelListHere)
+        hipLaunchKernelGGL((k_del_leaf<K, 1, true>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
+    else if (B >= 2ull * gl * (kBlk / kSlots))
+        hipLaunchKernelGGL((k_del_leaf<K, 2, false>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
     else
-        hipLaunchKernelGGL((k_del_leaf<K, 1>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
+        hipLaunchKernelGGL((k_del_leaf<K, 1, false>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
     const bool ordered = B > kDelListScan;
     if (ordered) {
         hipLaunchKernelGGL((k_ch_count<K, false>), dim3(cb.n), dim3(kChBlock), 0, s, t, v, cb.tiles, sums);
         hipLaunchKernelGGL((k_ch_collect<K, false>), dim3(cb.n), dim3(kChBlock), 0, s, t, v, cb.tiles, sums);
-    } else {
+    } else if (B > kDelListHere) {
         hipLaunchKernelGGL(k_del_list<K>, dim3(gB), dim3(kBlk), 0, s, t, v);
     }
     const uint32_t gm = B < 16384 ? static_cast<uint32_t>(B) : 16384u;
