@@ -354,51 +354,67 @@ __global__ void k_ranges(LiView<K> li, uint32_t L, uint32_t M) {
     }
 }
 
-// Solve G w = r (G symmetric positive definite, n <= 64, row-major in LDS)
-// by one wave: Cholesky right-looking (step j takes the pivot, scales column
-// j below it and updates the trailing lower triangle, its elements dealt
-// over the lanes), then the two triangular solves with r held one entry per
-// lane.  A small ridge (relative to the mean diagonal) keeps G definite.
-// One wave's LDS accesses take effect in order, so no barrier is needed
-// between the steps.  Returns false (uniformly) when a pivot is not positive.
-__device__ bool cholesky_solve_wave(double* G, double* r, int n) {
+// A double of lane `src`, the same in every lane.
+__device__ __forceinline__ double lane_value(double x, int src) {
+    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(x));
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(u), src));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(u >> 32), src));
+    return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+
+// Solve G w = r by one wave (G positive definite, N x N in LDS; w returned in
+// r): a column-by-column Cholesky factor with lane i holding row i in
+// registers, then the two triangular solves with r held one entry per lane.
+// A small ridge (relative to the mean diagonal) keeps G definite.  It is a
+// chain of N pivots, each a square root, a division and one update a column;
+// in LDS every update also waited out its reads and found its row and column
+// by a square root (k_fit of 2^24 keys 79 us, 113 so).  One wave's LDS accesses take
+// effect in order, so no barrier is needed between the steps.  Returns false
+// (uniformly) when a pivot is not positive.
+template <int N>
+__device__ __forceinline__ bool cholesky_solve_wave(double* G, double* r) {
+    static_assert(N <= 64, "a lane per row");
     const int lane = lane_id();
-    double dg = lane < n ? G[lane * n + lane] : 0.0;
+    const bool in = lane < N;
+    double row[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) row[k] = in ? G[lane * N + k] : 0.0;
+    double dg = in ? G[lane * N + lane] : 0.0;
     for (int o = 32; o > 0; o >>= 1) dg += __shfl_xor(dg, o, 64);
-    const double ridge = 1e-10 * (dg / n) + 1e-12;
-    if (lane < n) G[lane * n + lane] += ridge;
-    __builtin_amdgcn_wave_barrier();
-    for (int j = 0; j < n; ++j) {
-        const double pv = G[j * n + j];
+    const double ridge = 1e-10 * (dg / N) + 1e-12;
+#pragma unroll
+    for (int k = 0; k < N; ++k) row[k] += lane == k ? ridge : 0.0;
+    // (entries right of the diagonal are updated too, and not used)
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const double pv = lane_value(row[j], j);
         if (!(pv > 0)) return false;
-        const double dj = sqrt(pv);
-        if (lane > j && lane < n) G[lane * n + j] /= dj;
-        if (lane == j) G[j * n + j] = dj;
-        __builtin_amdgcn_wave_barrier();
-        const int m = n - j - 1, cnt = m * (m + 1) / 2;
-        for (int e = lane; e < cnt; e += 64) {
-            // e -> (ii, kk), kk <= ii, row-major over the trailing triangle
-            int ii = static_cast<int>((sqrt(8.0 * e + 1.0) - 1.0) * 0.5);
-            if ((ii + 1) * (ii + 2) / 2 <= e) ++ii;
-            if (ii * (ii + 1) / 2 > e) --ii;
-            const int kk = e - ii * (ii + 1) / 2;
-            const int i = j + 1 + ii, k = j + 1 + kk;
-            G[i * n + k] -= G[i * n + j] * G[k * n + j];
-        }
-        __builtin_amdgcn_wave_barrier();
+        const double dj = sqrt(pv), q = row[j] / dj;
+        row[j] = lane == j ? dj : q;
+#pragma unroll
+        for (int k = j + 1; k < N; ++k) row[k] -= row[j] * lane_value(row[j], k);
     }
-    double ri = lane < n ? r[lane] : 0.0;
-    for (int k = 0; k < n; ++k) {  // L y = r
-        const double yk = __shfl(ri, k, 64) / G[k * n + k];
+    double ri = in ? r[lane] : 0.0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {  // L y = r
+        const double yk = lane_value(ri, k) / lane_value(row[k], k);
         if (lane == k) ri = yk;
-        else if (lane > k && lane < n) ri -= G[lane * n + k] * yk;
+        else if (lane > k && in) ri -= row[k] * yk;
     }
-    for (int k = n - 1; k >= 0; --k) {  // L^T w = y
-        const double wk = __shfl(ri, k, 64) / G[k * n + k];
+    // columns of L: lane i takes L[k][i]
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        if (in && k <= lane) G[lane * N + k] = row[k];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < N; ++k) row[k] = in && lane <= k ? G[k * N + lane] : 1.0;
+#pragma unroll
+    for (int k = N - 1; k >= 0; --k) {  // L^T w = y
+        const double wk = lane_value(ri, k) / lane_value(row[k], k);
         if (lane == k) ri = wk;
-        else if (lane < k) ri -= G[k * n + lane] * wk;
+        else if (lane < k) ri -= row[k] * wk;
     }
-    if (lane < n) r[lane] = ri;
+    if (in) r[lane] = ri;
     return true;
 }
 
@@ -553,7 +569,7 @@ __global__ __launch_bounds__(256) void k_fit(LiView<K> li, uint32_t L, uint32_t 
         }
         __syncthreads();
         if (threadIdx.x < 64) {
-            const bool ok = cholesky_solve_wave(G, rr, NF);
+            const bool ok = cholesky_solve_wave<NF>(G, rr);
             if (threadIdx.x == 0) solved = ok ? 1 : 0;
         }
         __syncthreads();
@@ -590,33 +606,42 @@ __global__ void k_bounds_init(int32_t* bnd, uint32_t* cnt, uint32_t cells) {
 }
 
 // Every key of the tree, one lane per key slot, through both kinds of its
-// model.  Neighbouring slots almost always share a piece: a wave whose 64
-// slots all do reduces them in registers and keeps the piece's bounds until
-// its run of windows reaches another piece, then issues one set of atomics.
+// model.  Neighbouring slots almost always share a piece: each wave takes a
+// contiguous run of 64-slot windows, every lane keeps the bounds of its own
+// slots while the piece stays the same, and where another piece begins (and
+// at the end) the lanes' bounds are reduced and go out in one set of atomics.
+// It is bound by its arithmetic (two predictions a key); reducing every window
+// over its lanes took 97 us for 2^24 keys, 78 now.
 template <class K>
 __global__ __launch_bounds__(kLiBlock) void k_bounds(TreeView<K> t, LiView<K> li, uint32_t nleaves) {
     const LiArgs a = args_of(li.hdr);
     const uint64_t total = static_cast<uint64_t>(nleaves) * kSlots;
     const int lane = lane_id();
-    // each wave takes a contiguous run of 64-slot windows and carries the
-    // bounds of its current piece across windows (consecutive windows mostly
-    // share a piece), so a piece's atomics go out once per run, not once per
-    // window
     const uint64_t nwin = (total + 63) / 64, nwave = gsz() / 64;
     const uint64_t per = (nwin + nwave - 1) / nwave;
     const uint64_t wb = (gid() / 64) * per, we = wb + per < nwin ? wb + per : nwin;
     uint32_t cur = UINT32_MAX, ccnt = 0;
-    int32_t clmin = INT32_MAX, clmax = INT32_MIN, cmmin = INT32_MAX, cmmax = INT32_MIN;
+    int32_t lmin = INT32_MAX, lmax = INT32_MIN, mmin = INT32_MAX, mmax = INT32_MIN;  // of this lane's slots
     auto flush = [&]() {
-        if (cur != UINT32_MAX && lane == 0) {
-            atomicMin(&li.bnd[4 * cur + 0], clmin);
-            atomicMax(&li.bnd[4 * cur + 1], clmax);
-            if (cmmin <= cmmax) {
-                atomicMin(&li.bnd[4 * cur + 2], cmmin);
-                atomicMax(&li.bnd[4 * cur + 3], cmmax);
+        if (cur == UINT32_MAX) return;
+        for (int d = 32; d > 0; d >>= 1) {
+            lmin = min(lmin, __shfl_xor(lmin, d, 64));
+            lmax = max(lmax, __shfl_xor(lmax, d, 64));
+            mmin = min(mmin, __shfl_xor(mmin, d, 64));
+            mmax = max(mmax, __shfl_xor(mmax, d, 64));
+        }
+        if (lane == 0) {
+            atomicMin(&li.bnd[4 * cur + 0], lmin);
+            atomicMax(&li.bnd[4 * cur + 1], lmax);
+            if (mmin <= mmax) {
+                atomicMin(&li.bnd[4 * cur + 2], mmin);
+                atomicMax(&li.bnd[4 * cur + 3], mmax);
             }
             atomicAdd(&li.cnt[cur], ccnt);
         }
+        ccnt = 0;
+        lmin = mmin = INT32_MAX;
+        lmax = mmax = INT32_MIN;
     };
     for (uint64_t wi = wb; wi < we; ++wi) {
         const uint64_t x = wi * 64 + static_cast<uint64_t>(lane);
@@ -626,10 +651,10 @@ __global__ __launch_bounds__(kLiBlock) void k_bounds(TreeView<K> t, LiView<K> li
         bool mok = false;
         if (x < total) {
             const uint32_t leaf = static_cast<uint32_t>(x / kSlots), slot = static_cast<uint32_t>(x % kSlots);
+            const uint64_t key = static_cast<uint64_t>(t.lkeys[x]);  // (read with the count, not after it)
+            const int32_t pos = static_cast<int32_t>(li.pos_of_leaf[leaf]);
             if (slot < t.lmeta[leaf].x) {
                 valid = true;
-                const uint64_t key = static_cast<uint64_t>(t.lkeys[x]);
-                const int32_t pos = static_cast<int32_t>(li.pos_of_leaf[leaf]);
                 const Route r = route(a, key);
                 const ModelFit* f = li.fit + r.j;
                 cell = r.j * kSeg + r.m;
@@ -639,32 +664,25 @@ __global__ __launch_bounds__(kLiBlock) void k_bounds(TreeView<K> t, LiView<K> li
             }
         }
         // the window's pieces in lane order (almost always one, at a piece
-        // boundary two): each is reduced over its lanes, then merged into the
-        // running piece or, when it differs, flushes the running one first
+        // boundary two)
         uint64_t rem = __ballot(valid);
         while (rem) {
             const int ld = __builtin_ctzll(rem);
-            const uint32_t cc = static_cast<uint32_t>(__shfl(static_cast<int>(cell), ld, 64));
+            const uint32_t cc = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(cell), ld));
             const bool mine = valid && cell == cc;
-            const uint64_t mm = __ballot(mine);
-            int32_t lmin = mine ? rl : INT32_MAX, lmax = mine ? rl : INT32_MIN;
-            int32_t mmin = mine && mok ? rm : INT32_MAX, mmax = mine && mok ? rm : INT32_MIN;
-            for (int d = 32; d > 0; d >>= 1) {
-                lmin = min(lmin, __shfl_xor(lmin, d, 64));
-                lmax = max(lmax, __shfl_xor(lmax, d, 64));
-                mmin = min(mmin, __shfl_xor(mmin, d, 64));
-                mmax = max(mmax, __shfl_xor(mmax, d, 64));
-            }
             if (cc != cur) {
                 flush();
                 cur = cc;
-                ccnt = 0;
-                clmin = INT32_MAX; clmax = INT32_MIN; cmmin = INT32_MAX; cmmax = INT32_MIN;
             }
-            clmin = min(clmin, lmin);
-            clmax = max(clmax, lmax);
-            cmmin = min(cmmin, mmin);
-            cmmax = max(cmmax, mmax);
+            if (mine) {
+                lmin = min(lmin, rl);
+                lmax = max(lmax, rl);
+            }
+            if (mine && mok) {
+                mmin = min(mmin, rm);
+                mmax = max(mmax, rm);
+            }
+            const uint64_t mm = __ballot(mine);
             ccnt += static_cast<uint32_t>(__popcll(mm));
             rem &= ~mm;
         }
