@@ -749,15 +749,18 @@ __global__ __launch_bounds__(256) void k_choose(LiView<K> li, uint32_t M, uint32
     }
 }
 
-// Model quality over the trained keys (one workgroup): keys whose piece
-// sends them down the tree, and the key-weighted window of the others.
-constexpr int kQualityBlock = 1024;
+// Model quality over the trained keys: keys whose piece sends them down the
+// tree, and the key-weighted window of the others, added up per workgroup and
+// then with one atomic each into the header's words (cleared by k_li_finish).
+// Four passes of a workgroup over its pieces; 131072 pieces in one workgroup
+// were a chain of 128 reads, 25 us.
+constexpr int kQualityBlock = 256;
 
 template <class K>
 __global__ __launch_bounds__(kQualityBlock) void k_quality(LiView<K> li, uint32_t cells) {
     __shared__ unsigned long long sh[3][kQualityBlock / 64];
     unsigned long long tree = 0, wsum = 0, wmax = 0;
-    for (uint32_t c = threadIdx.x; c < cells; c += kQualityBlock) {
+    for (uint32_t c = static_cast<uint32_t>(gid()); c < cells; c += static_cast<uint32_t>(gsz())) {
         const uint32_t n = li.cnt[c];
         const Piece p = li.piece[c];
         if (n == 0) continue;
@@ -789,9 +792,9 @@ __global__ __launch_bounds__(kQualityBlock) void k_quality(LiView<K> li, uint32_
             b += sh[1][i];
             m = sh[2][i] > m ? sh[2][i] : m;
         }
-        li.hdr->keys_tree = a;
-        li.hdr->window_sum = b;
-        li.hdr->max_win = static_cast<uint32_t>(m);
+        atomicAdd(reinterpret_cast<unsigned long long*>(&li.hdr->keys_tree), a);
+        atomicAdd(reinterpret_cast<unsigned long long*>(&li.hdr->window_sum), b);
+        atomicMax(&li.hdr->max_win, static_cast<uint32_t>(m));
     }
 }
 
@@ -807,6 +810,9 @@ __global__ void k_li_finish(LiView<K> li, uint64_t n_keys) {
         li.hdr->lookups = 0;
         li.hdr->fallbacks = 0;
         li.hdr->trained = 1;
+        li.hdr->keys_tree = 0;
+        li.hdr->window_sum = 0;
+        li.hdr->max_win = 0;
     }
 }
 
@@ -1247,7 +1253,7 @@ gt_status train_t(gt_learned* li, hipStream_t s) {
     hipLaunchKernelGGL(k_choose<K>, dim3(grid_of(static_cast<uint64_t>(M) * 64, 256)), dim3(256), 0, s, v, M,
                        li->p.kind, mw);
     hipLaunchKernelGGL(k_li_finish<K>, dim3(1), dim3(64), 0, s, v, dh.n_keys);
-    hipLaunchKernelGGL(k_quality<K>, dim3(1), dim3(kQualityBlock), 0, s, v, static_cast<uint32_t>(cells));
+    hipLaunchKernelGGL(k_quality<K>, dim3(grid_of(cells, 4 * kQualityBlock)), dim3(kQualityBlock), 0, s, v, static_cast<uint32_t>(cells));
     const uint32_t one = 1;
     LI_HIP(hipMemcpyAsync(v.identity, &one, 4, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_identity, dim3(grid_of(ids, 256)), dim3(256), 0, s, v.pos_of_leaf, ids, v.identity);
