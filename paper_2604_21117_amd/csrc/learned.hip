@@ -299,15 +299,35 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
     return r;
 }
 
+// Root normalisation: smallest first key and the inverse of the distance to
+// the tree's largest key, read where they are needed (three copies to the host
+// with two waits for them left the device idle for 50 us of a training).
+struct RootRange {
+    uint64_t kmin;
+    double scale;
+};
+
+template <class K>
+__device__ __forceinline__ RootRange root_range(const TreeView<K>& t, const LiView<K>& li, uint32_t L) {
+    RootRange r;
+    r.kmin = static_cast<uint64_t>(li.dir[0].fence);
+    const uint32_t last = li.dir[L - 1].leaf;
+    const uint64_t kmx = last < t.leaf_cap
+                             ? static_cast<uint64_t>(t.lkeys[static_cast<uint64_t>(last) * kSlots + kSlots - 1])
+                             : r.kmin;
+    r.scale = kmx > r.kmin ? 1.0 / static_cast<double>(kmx - r.kmin) : 1.0;
+    return r;
+}
+
 // root sums: block b covers fences [b*n/nb, (b+1)*n/nb); x = (fence - kmin) * scale
 template <class K>
-__global__ __launch_bounds__(256) void k_root_partial(LiView<K> li, uint32_t L, uint32_t M, uint64_t kmin,
-                                                      double scale) {
+__global__ __launch_bounds__(256) void k_root_partial(TreeView<K> t, LiView<K> li, uint32_t L, uint32_t M) {
     __shared__ double sh[256];
+    const RootRange rg = root_range(t, li, L);
     const uint64_t b0 = part_start(blockIdx.x, L, gridDim.x), b1 = part_start(blockIdx.x + 1, L, gridDim.x);
     double s[5] = {0, 0, 0, 0, 0};
     for (uint64_t p = b0 + threadIdx.x; p < b1; p += blockDim.x) {
-        const double x = key_diff(static_cast<uint64_t>(li.dir[p].fence), kmin) * scale;
+        const double x = key_diff(static_cast<uint64_t>(li.dir[p].fence), rg.kmin) * rg.scale;
         const double y = static_cast<double>(p) * M / L;
         s[0] += 1.0; s[1] += x; s[2] += y; s[3] += x * x; s[4] += x * y;
     }
@@ -320,9 +340,10 @@ __global__ __launch_bounds__(256) void k_root_partial(LiView<K> li, uint32_t L, 
 // f = a' x + c with x = (key - kmin) * scale, stored as a = a' * scale.
 // One workgroup of 256: strided partial sums, then the fixed-order tree.
 template <class K>
-__global__ __launch_bounds__(256) void k_root_final(LiView<K> li, uint32_t nb, uint64_t kmin, double scale,
-                                                    uint32_t L, uint32_t M, uint32_t epoch) {
+__global__ __launch_bounds__(256) void k_root_final(TreeView<K> t, LiView<K> li, uint32_t nb, uint32_t L,
+                                                    uint32_t M, uint32_t epoch) {
     __shared__ double sh[256];
+    const RootRange rg = root_range(t, li, L);
     double s[5] = {0, 0, 0, 0, 0};
     for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x)
         for (int k = 0; k < 5; ++k) s[k] += li.partial[b * 5 + k];
@@ -333,8 +354,8 @@ __global__ __launch_bounds__(256) void k_root_final(LiView<K> li, uint32_t nb, u
     if (!(a > 0)) a = 0.0;
     const double c = n > 0 ? (s[2] - a * s[1]) / n : 0.0;
     LiHeader* h = li.hdr;
-    h->kmin_root = kmin;
-    h->root_a = a * scale;
+    h->kmin_root = rg.kmin;
+    h->root_a = a * rg.scale;
     h->root_c = c;
     h->L = L;
     h->M = M;
@@ -1226,21 +1247,10 @@ gt_status train_t(gt_learned* li, hipStream_t s) {
     }
     if (n == 0 || n > ids) return GT_ERR_DEVICE;
     hipLaunchKernelGGL(k_directory<K>, dim3(grid_of(ids, 256)), dim3(256), 0, s, tv, v, ids, n);
-    // root normalisation: smallest first key .. largest key of the tree
-    DirEntry<K> d0, dl;
-    LI_HIP(hipMemcpyAsync(&d0, v.dir, sizeof d0, hipMemcpyDeviceToHost, s));
-    LI_HIP(hipMemcpyAsync(&dl, v.dir + (n - 1), sizeof dl, hipMemcpyDeviceToHost, s));
-    LI_HIP(hipStreamSynchronize(s));
-    K kmaxkey;
-    LI_HIP(hipMemcpyAsync(&kmaxkey, tv.lkeys + static_cast<uint64_t>(dl.leaf) * kSlots + kSlots - 1, sizeof(K),
-                          hipMemcpyDeviceToHost, s));
-    LI_HIP(hipStreamSynchronize(s));
-    const uint64_t kmin = static_cast<uint64_t>(d0.fence), kmx = static_cast<uint64_t>(kmaxkey);
-    const double scale = kmx > kmin ? 1.0 / static_cast<double>(kmx - kmin) : 1.0;
     const uint32_t nb = n < static_cast<uint32_t>(kMaxPartials) ? n : kMaxPartials;
     const uint64_t cells = static_cast<uint64_t>(M) * kSeg;
-    hipLaunchKernelGGL(k_root_partial<K>, dim3(nb), dim3(256), 0, s, v, n, M, kmin, scale);
-    hipLaunchKernelGGL(k_root_final<K>, dim3(1), dim3(256), 0, s, v, nb, kmin, scale, n, M, dh.epoch);
+    hipLaunchKernelGGL(k_root_partial<K>, dim3(nb), dim3(256), 0, s, tv, v, n, M);
+    hipLaunchKernelGGL(k_root_final<K>, dim3(1), dim3(256), 0, s, tv, v, nb, n, M, dh.epoch);
     hipLaunchKernelGGL(k_ranges<K>, dim3(grid_of(n, 256)), dim3(256), 0, s, v, n, M);
     hipLaunchKernelGGL(k_fit<K>, dim3(M), dim3(256), 0, s, v, n, M);
     hipLaunchKernelGGL(k_bounds_init, dim3(grid_of(cells, 256)), dim3(256), 0, s, v.bnd, v.cnt,
