@@ -1395,14 +1395,16 @@ __global__ __launch_bounds__(kFusedBlock) void k_small_apply(TreeView<K> t, Ins<
 // the tree's current height, which the host cannot see) cost none.  The
 // workgroup's 64 groups of kNodeLanes walk a level's items in rounds of
 // 2 us, a launch costs as much or a little more:
-//  - batches of at most kTailItems keys go to the tail from the first level
-//    on: insert, lookup and delete of 300 keys on 2^24 77.6 us, 85.0 with the
-//    levels launched; of 1000 keys 104.4, and 88.8 launched;
+//  - batches of at most kTailItems keys, two rounds a level, go to the tail
+//    from the first level on: inserts of 80 keys into 2^24 where nothing
+//    splits above the leaves 22.9 us, 27.9 with the levels launched, where
+//    every level splits 50.6 and 48.7; of 256 keys 24.3 and 29.5, but 78.0
+//    and 51.7;
 //  - else the tail starts at the first level that can hold at most kTailNodes
 //    nodes.  That bound counts the whole leaf pool and 8 children a node; a
-//    level holds nearer a tenth of it, so a round or two (1000 keys 88.8 us,
-//    93.7 with the bound at one round).
-constexpr uint32_t kTailItems = 384;
+//    level holds nearer a tenth of it, so a round or two (insert, lookup and
+//    delete of 1000 keys 88.8 us, 93.7 with the bound at one round).
+constexpr uint32_t kTailItems = 128;
 constexpr uint32_t kTailNodes = 1024;
 
 template <class K>
