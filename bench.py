@@ -92,7 +92,7 @@ import synth  # noqa: E402
 HBM_PEAK_GBS = 8000.0
 MAX64 = (1 << 64) - 1
 METRIC = "lookup Mops/s and \u00b5s/batch at B=1..1024, 2^24 keys; learned vs plain tree"
-LARGE_KERNEL = "k_lookup<unsigned long, 8, 2, 2, true, 2>"
+LARGE_KERNEL = "k_lookup<unsigned long, 8, 2, 2, false, 2>"
 N_LOG2 = 24
 SEED = 2
 

@@ -19,10 +19,15 @@ def test_shape_switches(width, slack, n):
     keys = key_set(n, width, seed)
     vals = synth.values_for(keys, seed, width)
     sa = oracle.SortedArray(keys, vals, width)
-    t = mk_tree(keys, vals, width // 8, max_batch=4096, leaf_slack=slack)
+    t = mk_tree(keys, vals, width // 8, max_batch=4096, leaf_slack=slack or 64)
     if slack:
         assert t.stats()["leaf_cap"] * 16 * (width // 8) * 2 >= 256 << 20
     for B in ((1 << 16) - 1, 1 << 16, (1 << 16) + 1, (1 << 17) - 1, 1 << 17, (1 << 17) + 33):
         q = synth.mixed_queries(keys, B, seed + B, width)
         q[-1] = np.iinfo(keys.dtype).max
         assert_lookup_parity(t, sa, q)
+    # once the tree took updates the whole value line is read with the keys
+    more = key_set(50, width, seed + 1)
+    t.insert(more, synth.values_for(more, 7, width))
+    sa.insert(more, synth.values_for(more, 7, width))
+    assert_lookup_parity(t, sa, synth.mixed_queries(sa.keys.astype(keys.dtype), (1 << 17) + 33, seed, width))
