@@ -51,28 +51,40 @@ __device__ __forceinline__ void finish_lookups(const TreeView<K>& t, const K (&k
     uint32_t slot[QPG];
 #pragma unroll
     for (int j = 0; j < QPG; ++j) slot[j] = T::match_slot(kv[j], key[j], gbase);
-    K val[QPG];
-    bool hit[QPG];
+    if constexpr (VC) {
+        K val[QPG];
+        bool hit[QPG];
 #pragma unroll
-    for (int j = 0; j < QPG; ++j) {
-        hit[j] = slot[j] < kSlots && !empty;
-        val[j] = kmax<K>();
-        if constexpr (VC) {
+        for (int j = 0; j < QPG; ++j) {
+            hit[j] = slot[j] < kSlots && !empty;
             const K x = T::pick_value(vv[j], hit[j] ? slot[j] : 0u, gbase);
-            if (hit[j]) val[j] = x;
-        } else {
-            if (gl == (j % G) && qi[j] != ~0ull && hit[j]) {
-                const K* vp = t.lvals + static_cast<uint64_t>(leaf[j]) * kSlots + slot[j];
-                if constexpr ((NT & 2) != 0) val[j] = __builtin_nontemporal_load(vp);
-                else val[j] = *vp;
+            val[j] = hit[j] ? x : kmax<K>();
+        }
+#pragma unroll
+        for (int j = 0; j < QPG; ++j) {
+            if (gl == (j % G) && qi[j] != ~0ull) {
+                vout[qi[j]] = val[j];
+                fout[qi[j]] = hit[j] ? 1 : 0;
             }
         }
-    }
+    } else {
+        // lane j answers query j, so a wave's values and results go out in one
+        // read and two stores
+        static_assert(QPG <= G, "one answering lane per query");
+        const uint32_t sl = own_query<QPG>(slot, gl), lf = own_query<QPG>(leaf, gl);
+        uint64_t q = 0;
 #pragma unroll
-    for (int j = 0; j < QPG; ++j) {
-        if (gl == (j % G) && qi[j] != ~0ull) {
-            vout[qi[j]] = val[j];
-            fout[qi[j]] = hit[j] ? 1 : 0;
+        for (int j = 0; j < QPG; ++j) q |= qi[j] & (gl == j ? ~0ull : 0ull);
+        if (gl < QPG && q != ~0ull) {
+            const bool hit = sl < kSlots && !empty;
+            K val = kmax<K>();
+            if (hit) {
+                const K* vp = t.lvals + static_cast<uint64_t>(lf) * kSlots + sl;
+                if constexpr ((NT & 2) != 0) val = __builtin_nontemporal_load(vp);
+                else val = *vp;
+            }
+            vout[q] = val;
+            fout[q] = hit ? 1 : 0;
         }
     }
 }
@@ -437,8 +449,8 @@ constexpr uint64_t kStageBatch = 1u << 17;  // from here on the top levels are s
 // Values are streamed past the caches in large batches over trees whose leaf
 // lines outgrow the 256 MB memory-side cache: there a line is not read again
 // before it is evicted.  2^20 present keys of 2^24 u64 keys (256 MB of leaf
-// lines) 63.2 us against 64.2 with plain loads; below that size the lines
-// are found again, 2^20 keys of 2^21 keys 47.2 against 54.4.
+// lines) 62.2 us against 62.9 with plain loads; below that size the lines
+// are found again, whole value lines of 2^21 keys 46.7 us, streamed 54.4.
 constexpr uint64_t kStreamLeafBytes = 256ull << 20;
 
 template <class K, int G, int QPG, int LV>
@@ -495,8 +507,8 @@ static void launch_lookup_lv(const TreeView<K>& t, const LaunchCfg& cfg, const K
 //    per group (one is too few to hide the misses; four cost more in
 //    registers than they add), and one value read after the match instead of
 //    the whole line before it, which an absent key does not read at all: 2^20
-//    queries of 2^23 u64 keys, half absent, 49.8 us against 60.0; 2^20
-//    present ones of 2^18 u64 keys 34.9 against 46.7.  Not on a tree that took
+//    queries of 2^23 u64 keys, half absent, 47.9 us against 59.2; 2^20
+//    present ones of 2^18 u64 keys 33.6 against 36.9.  Not on a tree that took
 //    updates: its searches read child lines too, and a round more a query
 //    costs what the lines save (2^20 present keys of 2^24 after 2^20 inserts
 //    85.5 us with the whole line, 88.7 with one value; half absent 85.2 and
