@@ -1,4 +1,5 @@
-// Sample sort of (key, payload) pairs: the library's sort above 2048 keys.
+// Sample sort of (key, payload) pairs: the library's sort above 8192 keys (up to
+// there keys are ranked by counting) and of every bulk load.
 //
 // A pass of radix sort moves every pair once per eight key bits (eight
 // passes for 64-bit keys).  A sample sort moves a pair twice however wide
@@ -10,9 +11,9 @@
 // differ.  (Frazer and McKellar, "Samplesort: a sampling approach to minimal
 // storage tree sorting", J. ACM 17(3), 1970.)
 //
-//   sample   8 or 16 G pairs at stratified positions, merge-sorted in LDS
-//            (runs of 512 and a rank kernel above 1024 pairs); every eighth or
-//            sixteenth is a splitter
+//   sample   8 or 16 G pairs at stratified positions, ranked by counting over
+//            many workgroups up to 1024 pairs, above merge-sorted in LDS (runs
+//            of 512 and a rank kernel); every eighth or sixteenth is a splitter
 //   count    each tile classifies its keys by a search of the splitters in
 //            LDS and adds its group counts to the global ones
 //   scatter  tiles rank their pairs by group in LDS, reserve room in each
