@@ -156,9 +156,9 @@ uint64_t tree_arena_bytes(const gt_params* p /*host*/, uint64_t n, uint64_t leaf
  * This call synchronises `stream` before it returns.  On success *out
  * receives a new handle; GT_ERR_DEVICE if the device sort of the keys
  * failed (the keys changed while they were sorted, or, above 2^26 keys, a
- * bounded wait between its workgroups gave up: not expected).  On an error the
- * arena's contents are unspecified (the keys are sorted inside it where they
- * fit).
+ * bounded wait between its workgroups gave up: not expected).  The arena is
+ * not written before the keys are known to be good: a refused load leaves
+ * what it holds, and keys and values may lie in it.
  */
 gt_status tree_build(const gt_params* p /*host*/, const void* keys, const void* values, uint64_t n,
                      void* arena, uint64_t arena_bytes, hipStream_t stream, gt_tree** out /*host*/);

@@ -137,10 +137,12 @@ uint64_t bytes_for_leaf_cap(int kb, uint64_t max_batch, uint64_t leaf_cap) {
         if ((x) != hipSuccess) return GT_ERR_HIP;   \
     } while (0)
 
-// Bulk load into the tree's arena.  `own_arena`: the arena holds nothing that
-// has to survive an error, so the sort's buffers may lie in it.
+// Bulk load into the tree's arena.  The pairs are sorted in allocated memory
+// and nothing is written to the arena before the keys are known to be good:
+// it may hold a tree that a refused load has to leave as it is, and the
+// caller's keys and values.
 template <class K>
-gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, bool own_arena, hipStream_t s) {
+gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, hipStream_t s) {
     const double fill = fill_of(&t->p);
     std::vector<uint64_t> sizes = level_sizes_for(n, fill);
     if (sizes.size() > static_cast<size_t>(kMaxLevels)) return GT_ERR_CAPACITY;
@@ -151,38 +153,23 @@ gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, 
     if (t->leaf_cap >= kLeafTag || t->inner_cap >= kLeafTag) return GT_ERR_CAPACITY;
 
     // temporary buffers: the sort's pairs and scratch, per-level maxima,
-    // duplicate flag.  Up to sample_sort_max() keys the pairs are sorted into
-    // the leaves; above, (key, index) pairs are sorted, the values gathered
-    // and the leaves written from them.
+    // duplicate flag.  Above kRankSortTop keys, up to sample_sort_max(), the
+    // sample sort moves (key, value) pairs; else (key, index) pairs are sorted
+    // and the values gathered (one key 52 us a load, 59 by the sample sort).
     const uint64_t nn = n ? n : 1;
-    const bool direct = n <= sample_sort_max();
+    const bool moved = n > kRankSortTop && n <= sample_sort_max();
     uint64_t maxsz = 0;
     for (uint64_t v : sizes) maxsz = std::max(maxsz, v);
     const uint64_t b_keys = align_up(nn * sizeof(K)), b_idx = align_up(nn * 4);
-    const uint64_t b_sort = align_up(direct ? sample_sort_tmp_bytes(nn, sizeof(K)) : sort_tmp_bytes(nn, sizeof(K)));
+    const uint64_t b_sort = align_up(moved ? sample_sort_tmp_bytes(nn, sizeof(K)) : sort_tmp_bytes(nn, sizeof(K)));
     const uint64_t b_max = align_up(2 * maxsz * sizeof(K));
-    // Sorting into the leaves takes one pair buffer up to 2^20 keys, two
-    // above; the first of two is free again before the leaves are written, so
-    // it can lie in the leaf pool.  What the insert scratch and the inner pool
-    // (written last) hold is taken from there too: a device allocation of the
-    // 2^24-key load's size took 340 us and now and then 12 ms.
-    const bool two = direct && sort_leaves_two_buffers(n);
-    const bool first_in_pool = two && own_arena;
-    const uint64_t b_pairs = direct ? (two && !first_in_pool ? 4 : 2) * b_keys : 3 * b_keys + 2 * b_idx;
-    const uint64_t b_small = b_sort + b_max + kAlign;  // read while the inner levels are written
-    uint8_t* tmp = nullptr;    // allocated
-    uint8_t* pairs = nullptr;
-    uint8_t* p = nullptr;
-    const bool small_in = own_arena && b_small <= t->scratch_bytes;
-    uint8_t* const room = t->scratch + (small_in ? b_small : 0);
-    const bool pairs_in = own_arena && static_cast<uint64_t>(reinterpret_cast<uint8_t*>(t->lkeys) - room) >= b_pairs;
-    const uint64_t total = (small_in ? 0 : b_small) + (pairs_in ? 0 : b_pairs);
-    if (total) HIP_TRY(hipMalloc(&tmp, total));
-    pairs = pairs_in ? room : tmp;
-    p = small_in ? t->scratch : tmp + (pairs_in ? 0 : b_pairs);
-    void* stmp = p; p += b_sort;
-    K* maxbuf = reinterpret_cast<K*>(p); p += b_max;
-    uint32_t* dflag = reinterpret_cast<uint32_t*>(p);
+    const bool two = moved && sort_pairs_two_buffers(n);
+    const uint64_t b_pairs = moved ? (two ? 4 : 2) * b_keys : 3 * b_keys + 2 * b_idx;
+    uint8_t* tmp = nullptr;
+    HIP_TRY(hipMalloc(&tmp, b_pairs + b_sort + b_max + kAlign));
+    void* stmp = tmp + b_pairs;
+    K* maxbuf = reinterpret_cast<K*>(tmp + b_pairs + b_sort);
+    uint32_t* dflag = reinterpret_cast<uint32_t*>(tmp + b_pairs + b_sort + b_max);
     K* sk = nullptr;
     K* sv = nullptr;
 
@@ -191,21 +178,20 @@ gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, 
     do {
         if (hipMemsetAsync(dflag, 0, 4, s) != hipSuccess) { st = GT_ERR_HIP; break; }
         // flag bit 0: a key occurs twice, bit 1: the sort gave up
-        if (n && direct) {
-            K* kb = reinterpret_cast<K*>(pairs);
-            K* vb = reinterpret_cast<K*>(pairs + b_keys);
-            K* ka = first_in_pool ? reinterpret_cast<K*>(t->lkeys) : (two ? reinterpret_cast<K*>(pairs + 2 * b_keys) : kb);
-            K* va = first_in_pool ? reinterpret_cast<K*>(t->lvals) : (two ? reinterpret_cast<K*>(pairs + 3 * b_keys) : vb);
-            launch_sort_leaves<K>(view<K>(t), reinterpret_cast<const K*>(keys), reinterpret_cast<const K*>(values), n,
-                                  sizes[0], ka, va, kb, vb, stmp, maxbuf, dflag, 2u, sort_forced_to_fail(n), s);
+        K* const k0 = reinterpret_cast<K*>(tmp);
+        K* const k1 = reinterpret_cast<K*>(tmp + b_keys);
+        if (n && moved) {
+            K* const k2 = two ? reinterpret_cast<K*>(tmp + 2 * b_keys) : nullptr;
+            K* const k3 = two ? reinterpret_cast<K*>(tmp + 3 * b_keys) : nullptr;
+            launch_sort_pairs<K>(reinterpret_cast<const K*>(keys), reinterpret_cast<const K*>(values), n, k0, k1, k2, k3,
+                                 stmp, dflag, 2u, sort_forced_to_fail(n), s, &sk, &sv);
         } else if (n) {
-            sk = reinterpret_cast<K*>(pairs);
-            K* sk2 = reinterpret_cast<K*>(pairs + b_keys);
-            sv = reinterpret_cast<K*>(pairs + 2 * b_keys);
-            uint32_t* si = reinterpret_cast<uint32_t*>(pairs + 3 * b_keys);
-            uint32_t* si2 = reinterpret_cast<uint32_t*>(pairs + 3 * b_keys + b_idx);
+            sk = k0;
+            sv = reinterpret_cast<K*>(tmp + 2 * b_keys);
+            uint32_t* si = reinterpret_cast<uint32_t*>(tmp + 3 * b_keys);
+            uint32_t* si2 = reinterpret_cast<uint32_t*>(tmp + 3 * b_keys + b_idx);
             // (key, position) pairs sorted by key; positions come from the sort
-            sort_from<K>(reinterpret_cast<const K*>(keys), sk, si, sk2, si2, n, stmp, s, dflag, 2u);
+            sort_from<K>(reinterpret_cast<const K*>(keys), sk, si, k1, si2, n, stmp, s, dflag, 2u);
             launch_gather<K>(reinterpret_cast<const K*>(values), si, sv, n, s);
             launch_dup_check<K>(sk, n, dflag, s);
         }
@@ -222,7 +208,7 @@ gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, 
         t->h_bound = static_cast<uint32_t>(sizes.size());
     } while (0);
     hipStreamSynchronize(s);
-    if (tmp) hipFree(tmp);
+    hipFree(tmp);
     return st;
 }
 
@@ -253,7 +239,7 @@ gt_status delete_rebuild_t(gt_tree* t, hipStream_t s) {
             break;
         }
         if (got != n) { st = GT_ERR_DEVICE; break; }
-        st = build_t<K>(t, ok, ov, n, false, s);  // the arena still holds the tree
+        st = build_t<K>(t, ok, ov, n, s);
         if (st != GT_OK) break;
         const uint32_t keep[2] = {h.error, h.epoch + 1};  // DevHeader: error, then epoch
         static_assert(offsetof(DevHeader, epoch) == offsetof(DevHeader, error) + 4, "header layout");
@@ -382,8 +368,8 @@ gt_status tree_build(const gt_params* p, const void* keys, const void* values, u
     t->cfg.shape_auto = (p->lanes_per_query ? 0 : 1) | (p->queries_per_group ? 0 : 2) | (p->lds_levels ? 0 : 4);
     t->cfg.rewritten = 0;
     layout(t, reinterpret_cast<uint8_t*>(arena), lo);
-    gt_status st = kb == 8 ? build_t<uint64_t>(t, keys, values, n, true, stream)
-                           : build_t<uint32_t>(t, keys, values, n, true, stream);
+    gt_status st = kb == 8 ? build_t<uint64_t>(t, keys, values, n, stream)
+                           : build_t<uint32_t>(t, keys, values, n, stream);
     if (st != GT_OK) {
         delete t;
         return st;
