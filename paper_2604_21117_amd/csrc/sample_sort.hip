@@ -140,9 +140,9 @@ __device__ __forceinline__ uint32_t ss_hash(uint32_t x) {
     return x ^ (x >> 16);
 }
 
-// Whether the sort is refused already (a repeated key, a failure).  The same
-// for the whole workgroup, though other workgroups may raise the word
-// meanwhile.  Only without TIE.
+// Whether the sort is refused already (a repeated key, a failure): what the
+// kernels before this one left is then not read.  The same for the whole
+// workgroup, though the word may be raised meanwhile.  Only without TIE.
 template <bool TIE>
 __device__ __forceinline__ bool ss_refused(const uint32_t* refuse) {
     if constexpr (TIE) {
@@ -265,7 +265,7 @@ __device__ __forceinline__ int ss_merge_sort(K (*a)[kSsPadded], uint32_t (*p)[kS
 // runs go to sk, sp for k_ss_rank.  Also clears the level's counters and, on
 // the first level, the failure word (`force` is the testing hook that makes
 // the sort fail).  Without TIE, equal keys at different positions set bit 0
-// of *dup.
+// of *dup, and the kernels after this one end at once.
 template <class K, bool TIE>
 __global__ __launch_bounds__(1024) void k_ss_sample(const K* __restrict__ kin, const uint32_t* __restrict__ pin,
                                                      uint32_t n, const uint32_t* __restrict__ seg_start,
@@ -276,6 +276,7 @@ __global__ __launch_bounds__(1024) void k_ss_sample(const K* __restrict__ kin, c
     __shared__ K a[2][kSsPadded];
     __shared__ uint32_t p[2][kSsPadded];
     const uint32_t s = blockIdx.x, tid = threadIdx.x, S = groups * over, len = S / runs, first = blockIdx.y * len;
+    if (seg_start && ss_refused<TIE>(dup)) return;  // the segments were not written
     if (blockIdx.y == 0)
         for (uint32_t i = tid; i < groups; i += blockDim.x) {
             cnt[static_cast<uint64_t>(s) * groups + i] = 0;
@@ -515,8 +516,10 @@ template <class K, bool TIE, int N>
 __global__ __launch_bounds__(kSsThreads) void k_ss_count(const K* __restrict__ kin, const uint32_t* __restrict__ pin,
                                                           uint32_t n, const uint32_t* __restrict__ seg_start,
                                                           uint32_t groups, const K* __restrict__ gk,
-                                                          const uint32_t* __restrict__ gp, uint32_t* cnt) {
+                                                          const uint32_t* __restrict__ gp, uint32_t* cnt,
+                                                          const uint32_t* refuse) {
     constexpr uint32_t kTile = kSsThreads * N;
+    if (ss_refused<TIE>(refuse)) return;
     __shared__ K tk[kSsMaxGroups];
     __shared__ uint32_t tp[kSsMaxGroups];
     __shared__ uint32_t h[kSsMaxGroups];
@@ -561,8 +564,9 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(const K* __restrict__
                                                             const uint32_t* __restrict__ cnt, uint32_t* cur,
                                                             uint32_t* __restrict__ start, K* __restrict__ kout,
                                                             P* __restrict__ pout, uint32_t* fail, uint32_t* err,
-                                                            uint32_t err_bit) {
+                                                            uint32_t err_bit, const uint32_t* refuse) {
     constexpr uint32_t kTile = kSsThreads * N;
+    if (ss_refused<TIE>(refuse)) return;
     __shared__ K tk[kSsMaxGroups];
     __shared__ uint32_t tp[kSsMaxGroups];
     __shared__ uint32_t h[kSsMaxGroups];       // the tile's counts
@@ -1054,9 +1058,9 @@ static void ss_partition(const SsPlan& pl, uint8_t* tmp, const K* src, const P* 
             const uint32_t ty = (n / v.segs + T - 1) / T, gy = v.segs == 1 && ty > 1024 ? 1024 : (ty < 1 ? 1 : ty);
             const dim3 grid(v.segs, gy);
             hipLaunchKernelGGL((k_ss_count<K, TIE, N>), grid, dim3(kSsThreads), 0, s, kin, tie, n, seg, v.groups, gk,
-                               gp, cnt);
+                               gp, cnt, dup);
             hipLaunchKernelGGL((k_ss_scatter<K, P, TIE, N>), grid, dim3(kSsThreads), 0, s, kin, in, n, seg, v.groups,
-                               gk, gp, cnt, cur, start, kout, out, fail, err, err_bit);
+                               gk, gp, cnt, cur, start, kout, out, fail, err, err_bit, dup);
         };
         if (n > kSsOneLevel) tiles(std::integral_constant<int, 8>{});
         else if (n > (1u << 18)) tiles(std::integral_constant<int, 4>{});
