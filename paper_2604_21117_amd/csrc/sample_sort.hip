@@ -681,10 +681,24 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(const K* __restrict__
 // a wave, 64 of its pairs at a time: by its pairs' threads it would hold up
 // every wave that has one of them.  Above kSsBinMax the merge is cheaper.
 constexpr uint32_t kSsBinOwn = 8, kSsBinMax = 256;
+// A group with a bin of more than kSsBinSpread pairs is dealt again, up to
+// kSsSpreads times (ss_spread).
+constexpr uint32_t kSsBinSpread = 64;
+constexpr int kSsSpreads = 3;
+
+// The keys of a bin and the positions of its pairs: smallest and largest.
+template <class K>
+struct SsSpan {
+    K lo, hi;
+    uint32_t first, last;
+};
 
 template <class K, bool TIE, int NT, uint32_t CAP>
 struct SsLds {
-    K k[CAP + CAP / 32];  // padded for ss_merge_held
+    union {
+        K k[CAP + CAP / 32];            // padded for ss_merge_held
+        SsSpan<K> span[CAP / kSsBinOwn];  // before the pairs are placed
+    };
     uint32_t p[TIE ? CAP + CAP / 32 : 1];
     uint32_t bin[CAP + CAP / 32];
     uint32_t big[CAP / kSsBinOwn];  // bins of more than kSsBinOwn pairs: start << 16 | pairs
@@ -780,6 +794,75 @@ __device__ __forceinline__ uint32_t ss_scan_bins(uint32_t* bin, uint32_t nb, uin
     return worst;
 }
 
+template <class K>
+__device__ __forceinline__ void lds_min(K* a, K x) {
+    if constexpr (sizeof(K) == 8) atomicMin(reinterpret_cast<unsigned long long*>(a), static_cast<unsigned long long>(x));
+    else atomicMin(a, x);
+}
+
+template <class K>
+__device__ __forceinline__ void lds_max(K* a, K x) {
+    if constexpr (sizeof(K) == 8) atomicMax(reinterpret_cast<unsigned long long*>(a), static_cast<unsigned long long>(x));
+    else atomicMax(a, x);
+}
+
+// Deals the pairs of each bin of more than kSsBinOwn among as many bins as it
+// has pairs: by their distance from its smallest key, or, where it holds one
+// key, from its first position (a key that is repeated many times fills whole
+// groups, in which only the positions differ).  bin holds starts before and
+// counts after, bn and f a pair's bin and its place there.  Without this such
+// groups were merge-sorted: the level-wise lookup of 2^20 u32 keys of which
+// 100 differ XXX us, now XXX (XXX where all differ).
+template <class K, int NT, uint32_t CAP>
+__device__ __forceinline__ void ss_spread(SsLds<K, true, NT, CAP>& L, uint32_t m, uint32_t nb, const K (&k)[CAP / NT],
+                                          const uint32_t (&p)[CAP / NT], uint32_t (&bn)[CAP / NT],
+                                          uint32_t (&f)[CAP / NT]) {
+    constexpr uint32_t E = CAP / NT;
+    const uint32_t tid = threadIdx.x;
+    uint32_t b0[E], n[E];
+    // (starts of bins above kSsBinOwn lie further apart than kSsBinOwn)
+    auto span = [&](uint32_t e) -> SsSpan<K>& { return L.span[b0[e] / kSsBinOwn]; };
+#pragma unroll
+    for (uint32_t e = 0; e < E; ++e) {
+        const bool in = e * NT + tid < m;
+        b0[e] = in ? L.bin[bn[e]] : 0u;
+        n[e] = in ? L.bin[bn[e] + 1] - b0[e] : 0u;
+        if (n[e] > kSsBinOwn && f[e] == 0) span(e) = SsSpan<K>{k[e], k[e], p[e], p[e]};  // one pair of the bin
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t e = 0; e < E; ++e)
+        if (n[e] > kSsBinOwn) {
+            SsSpan<K>& s = span(e);
+            if (k[e] < s.lo) lds_min(&s.lo, k[e]);
+            if (k[e] > s.hi) lds_max(&s.hi, k[e]);
+            if (p[e] < s.first) atomicMin(&s.first, p[e]);
+            if (p[e] > s.last) atomicMax(&s.last, p[e]);
+        }
+    for (uint32_t i = tid; i < nb; i += NT) L.bin[i] = 0;
+    if (tid == 0) {
+        L.worst = 0;
+        L.nbig = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t e = 0; e < E; ++e) {
+        uint32_t to = 0;
+        if (n[e] > kSsBinOwn) {
+            const SsSpan<K>& s = span(e);
+            // (conversions and the product round, but keep the order)
+            const bool one = s.lo == s.hi;
+            const float range = one ? static_cast<float>(s.last - s.first) : static_cast<float>(s.hi - s.lo);
+            const float off = one ? static_cast<float>(p[e] - s.first) : static_cast<float>(k[e] - s.lo);
+            to = static_cast<uint32_t>(off * (static_cast<float>(n[e]) / (range + 1.0f)));
+            to = to < n[e] ? to : n[e] - 1u;
+        }
+        bn[e] = b0[e] + to;
+        f[e] = e * NT + tid < m ? atomicAdd(&L.bin[bn[e]], 1u) : 0u;
+    }
+    __syncthreads();
+}
+
 template <class K, class P, bool TIE, int NT, uint32_t CAP>
 __device__ __forceinline__ void ss_sort_group(const K* kin, const P* pin, uint64_t b, uint32_t m,
                                               SsLds<K, TIE, NT, CAP>& L, P (&p)[CAP / NT], uint32_t (&f)[CAP / NT]) {
@@ -829,16 +912,26 @@ __device__ __forceinline__ void ss_sort_group(const K* kin, const P* pin, uint64
     const int shift = width > bits ? width - bits : 0;
     uint32_t bn[E];
 #pragma unroll
-    for (uint32_t e = 0; e < E; ++e) {
-        const bool in = e * NT + tid < m;
-        bn[e] = in ? static_cast<uint32_t>(static_cast<uint64_t>(static_cast<K>(k[e] - lo)) >> shift) : 0u;
-        f[e] = in ? atomicAdd(&L.bin[bn[e]], 1u) : 0u;
+    for (uint32_t e = 0; e < E; ++e)
+        bn[e] = e * NT + tid < m ? static_cast<uint32_t>(static_cast<uint64_t>(static_cast<K>(k[e] - lo)) >> shift) : 0u;
+#pragma unroll
+    for (uint32_t e = 0; e < E; ++e) f[e] = e * NT + tid < m ? atomicAdd(&L.bin[bn[e]], 1u) : 0u;
+    __syncthreads();
+    uint32_t worst;  // the same for the whole workgroup
+    for (int round = 0;; ++round) {
+        const uint32_t mine = ss_scan_bins<NT, CAP>(L.bin, nb, L.sh, L.big, &L.nbig);
+        if (mine > kSsBinSpread) atomicMax(&L.worst, mine);
+        __syncthreads();
+        worst = L.worst;
+        if constexpr (TIE) {
+            if (worst > kSsBinSpread && round < kSsSpreads) {
+                ss_spread<K, NT, CAP>(L, m, nb, k, p, bn, f);
+                continue;
+            }
+        }
+        break;
     }
-    __syncthreads();
-    const uint32_t worst = ss_scan_bins<NT, CAP>(L.bin, nb, L.sh, L.big, &L.nbig);
-    if (worst > kSsBinMax) atomicMax(&L.worst, worst);
-    __syncthreads();
-    if (L.worst > kSsBinMax) {  // the same for the whole workgroup
+    if (worst > kSsBinMax) {
         uint32_t q[E];
 #pragma unroll
         for (uint32_t e = 0; e < E; ++e) q[e] = TIE ? static_cast<uint32_t>(p[e]) : e * NT + tid;
@@ -870,9 +963,9 @@ __device__ __forceinline__ void ss_sort_group(const K* kin, const P* pin, uint64
                 const K y0 = L.k[x], y1 = L.k[x1];
                 bool lt0 = y0 < k[e], lt1 = y1 < k[e];
                 if constexpr (TIE) {
-                    // (the pair itself ties in every bin: not worth a read)
-                    if (y0 == k[e] && x != f[e]) lt0 = L.p[x] < static_cast<uint32_t>(p[e]);
-                    if (y1 == k[e] && x1 != f[e]) lt1 = L.p[x1] < static_cast<uint32_t>(p[e]);
+                    const uint32_t q0 = L.p[x], q1 = L.p[x1];
+                    lt0 = lt0 | ((y0 == k[e]) & (q0 < static_cast<uint32_t>(p[e])));
+                    lt1 = lt1 | ((y1 == k[e]) & (q1 < static_cast<uint32_t>(p[e])));
                 } else {
                     lt0 = lt0 || (y0 == k[e] && x < f[e]);
                     lt1 = lt1 || (y1 == k[e] && x1 < f[e]);
