@@ -11,8 +11,8 @@
 //                                  most significant; a 32-byte key's words as
 //                                  big-endian numbers) in which the keys
 //                                  below the node differ.  Slice 0 holds word
-//                                  w of the m entries, the other words follow
-//                                  in order.  Entry i < c-1: the largest key
+//                                  w of the m entries, slice w word 0, every
+//                                  other slice its own word.  Entry i < c-1: the largest key
 //                                  below child i; entries from c-1 on: the
 //                                  largest key value (all bytes 0xFF)
 //   imeta[inner]                   {first child, children | w << 8, tie mask
@@ -28,7 +28,7 @@
 //     lvals[leaves][m] 8-byte values, all ones from count on
 //   leaves of 32-byte keys (lkeys only, 40 bytes per entry): per leaf the
 //     m entries' deciding words (the parent's w; 0 without a parent), then m
-//     32-byte records {the other three words in order, value}, words as
+//     32-byte records {slices 1 to 3 as above, value}, words as
 //     big-endian numbers; the same ordering and padding
 //   lmeta[leaves]                  {count | w << 8, next leaf}
 // A key is kb = 8 * kw bytes: kw = 1 holds an 8-byte unsigned integer in

@@ -13,9 +13,9 @@
 // tie does not decide).  That word is the node's deciding word, the first in
 // which its keys differ: keys with a common prefix (2^20 lookups on 10 M keys
 // behind 256 stems of 16 bytes) took 291 / 592 / 1001 us at orders 16 / 32 / 64
-// by the leading word, which all of a node's entries tie, and take 135 / 157 /
-// 260 by the deciding one (keys without a common prefix 99 / 129 / 195 before
-// and 99 / 111 / 160 now, the lanes' counts added with DPP moves where a ballot
+// by the leading word, which all of a node's entries tie, and take 129 / 149 /
+// 244 by the deciding one (keys without a common prefix 98 / 131 / 200 before
+// and 86 / 104 / 146 now, the lanes' counts added with DPP moves where a ballot
 // per entry stood).  The node's child range comes from one 16-byte
 // record read in the same round as the deciding words, so a level costs one
 // dependent round unless an entry ties.  At the leaf each lane compares its
@@ -147,54 +147,55 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
 // A node's deciding word w is the first word in which the keys below it
 // differ (keys with a common prefix agree in all words before it).  An inner
 // node's entries are word-sliced: slice 0 is word w (as a big-endian number)
-// of its m entries in m consecutive 8-byte words, the other words follow in
-// order (word x > w is slice x), so a level reads its deciding words alone
-// (one 128-byte line at m = 16) whatever prefix the keys share.
+// of its m entries in m consecutive 8-byte words, word 0 is slice w in its
+// place and every other word x slice x, so a level reads its deciding words
+// alone (one 128-byte line at m = 16) whatever prefix the keys share.  Below a
+// node the words before w are the same for all keys, so keys that tie in slice
+// 0 compare by slices 1, 2, 3 in that order.
 
-// word x of a key, x the same for the lanes of a group (with masks: a select
-// of two array elements would become an indexed read, and the key's array a
-// memory object)
+// slice of word x in a node whose deciding word is w, and word of slice x
+inline uint32_t slice_of(uint32_t x, uint32_t w) { return x == w ? 0u : (x == 0 ? w : x); }
+
+// A key's words in the order of the slices, w the same for the lanes of a group.
 template <int KW>
-__device__ __forceinline__ uint64_t word_of(const uint64_t (&k)[KW], uint32_t x) {
-    if constexpr (KW == 1) return k[0];
-    uint64_t r = 0;
+__device__ __forceinline__ void in_slices(const uint64_t (&k)[KW], uint32_t w, uint64_t (&o)[KW]) {
+    uint64_t first = k[0];
 #pragma unroll
-    for (int i = 0; i < KW; ++i) r |= k[i] & (x == static_cast<uint32_t>(i) ? ~0ull : 0ull);
-    return r;
+    for (int i = 1; i < KW; ++i) {
+        const bool swap = w == static_cast<uint32_t>(i);
+        const uint64_t x = k[i];
+        first = swap ? x : first;
+        o[i] = swap ? k[0] : x;
+    }
+    o[0] = first;
 }
-
-// slice of word x in a node whose deciding word is w
-__device__ __forceinline__ uint32_t slice_of(uint32_t x, uint32_t w) { return x == w ? 0u : (x < w ? x + 1u : x); }
 
 // The fields of a node's record: children, deciding word, tie mask.
 __device__ __forceinline__ uint32_t meta_word(const uint4& m) { return m.y >> 8; }
 __device__ __forceinline__ uint64_t meta_ties(const uint4& m) { return static_cast<uint64_t>(m.w) << 32 | m.z; }
 
-// Whether entry `slot` of node `ref`, whose deciding word ties the query's,
-// lies below the query by the words behind it.  (A present key agrees with
+// Whether an entry whose slice 0 (at `e`, slices M apart) ties the query's
+// lies below the query; ks: the query in slices.  (A present key agrees with
 // the node's common prefix; where an absent one goes does not matter, since
 // the leaf compares whole keys.)
 template <int KW, int M>
-__device__ __forceinline__ bool tie_less(const uint64_t* ik, uint32_t ref, uint32_t slot, uint32_t w,
-                                         const uint64_t (&key)[KW]) {
-    uint64_t e[KW];
+__device__ __forceinline__ bool tie_less(const uint64_t* e, const uint64_t (&ks)[KW]) {
+    uint64_t x[KW];
 #pragma unroll
-    for (int x = 1; x < KW; ++x)
-        e[x] = static_cast<uint32_t>(x) > w ? ik[(static_cast<uint64_t>(ref) * KW + x) * M + slot] : 0ull;
-    bool l = false;
+    for (int i = 1; i < KW; ++i) x[i] = e[i * M];
+    bool l = x[KW - 1] < ks[KW - 1];
 #pragma unroll
-    for (int x = KW - 1; x >= 1; --x)
-        if (static_cast<uint32_t>(x) > w) l = (e[x] < key[x]) || (e[x] == key[x] && l);
+    for (int i = KW - 2; i >= 1; --i) l = (x[i] < ks[i]) || (x[i] == ks[i] && l);
     return l;
 }
 
 // Descend from the root to the leaf whose key range holds `key` (the first
 // child whose entry is >= key at every level), one lane per entry.  Every
 // lane of the group takes part; the result is a leaf id, lw its deciding word
-// (that of its parent).  A lane whose word ties the query's goes on to the
-// entry's words behind it (read together, one more round) -- the cascade of
-// the paper's priority comparison, taken through memory -- unless the tie
-// already decides: when the key after the entry in key order (the first of
+// (that of its parent), ks the query in the order of its slices.  A lane whose
+// word ties the query's goes on to the entry's words behind it (read together,
+// one more round) -- the cascade of the paper's priority comparison, taken
+// through memory -- unless the tie already decides: when the key after the entry in key order (the first of
 // the next child) has a larger deciding word, no key of a later child shares
 // the query's, so a present query lies at or below the entry.  Exact-match
 // lookups take that shortcut (bit s of the node's mask is set when it does
@@ -202,51 +203,62 @@ __device__ __forceinline__ bool tie_less(const uint64_t* ik, uint32_t ref, uint3
 // the exact first key >= lo, compare in full.  Entries below the child count
 // are sorted, so the "entry < query" lanes stay a prefix of the group either
 // way.
+//
+// A small batch is one chain of reads and runs each line of code once or
+// twice, from a cold instruction cache.  So a level compares with the word of
+// the level above, its node's too but for a level or two of a descent, and
+// what a node or a tie does differently is one branch of few instructions:
+// 1000 keys of 10 M at order 16 take 3.0 us, 3.5 with the word chosen at every
+// level and the leaf's entries put back into key order; behind 256 stems of 16
+// bytes 3.8 and 4.3.
 template <int KW, int M, bool Exact>
 __device__ __forceinline__ uint32_t descend(const WideView& v, const Key<KW>& key, bool valid, uint32_t root,
-                                            uint32_t height, int s, int gbase, uint32_t& lw) {
+                                            uint32_t height, int s, int gbase, uint32_t& lw, uint64_t (&ks)[KW]) {
     const uint64_t* ik = reinterpret_cast<const uint64_t*>(v.ikeys);
     uint32_t ref = root;
     lw = 0;
-    for (uint32_t d = 0; d + 1 < height; ++d) {
-        const uint64_t base = static_cast<uint64_t>(ref) * KW * M + s;
-        const uint64_t e0 = ik[base];
-        const uint4 meta = v.imeta[ref];
-        const uint32_t w = KW > 1 ? meta_word(meta) : 0u;
-        bool lt;
-        if constexpr (KW == 1) {
-            lt = e0 < key.w[0];
-        } else if constexpr (Exact) {
-            lt = e0 < key.w[0];
-            const bool need = valid && (w != 0 || e0 == key.w[0]);
-            if (__ballot(need)) {
-                if (need) {
-                    Key<KW> e;
 #pragma unroll
-                    for (int x = 0; x < KW; ++x)
-                        e.w[x] = ik[base + static_cast<uint64_t>(slice_of(static_cast<uint32_t>(x), w)) * M];
-                    lt = key_less<KW>(e, key);
+    for (int i = 0; i < KW; ++i) ks[i] = key.w[i];
+    for (uint32_t d = 0; d + 1 < height; ++d) {
+        const uint64_t* e = ik + static_cast<uint64_t>(ref) * KW * M + s;
+        const uint64_t e0 = e[0];
+        const uint4 meta = v.imeta[ref];
+        bool lt = e0 < ks[0];
+        if constexpr (KW > 1) {
+            const uint32_t w = meta_word(meta);
+            if constexpr (Exact) {  // ks stays in key order
+                if (valid && (w != 0 || e0 == ks[0])) {
+                    uint64_t x[KW], y[KW];
+                    x[0] = e0;
+#pragma unroll
+                    for (int i = 1; i < KW; ++i) x[i] = e[i * M];
+                    in_slices<KW>(x, w, y);  // and back: a swap
+                    lt = y[KW - 1] < ks[KW - 1];
+#pragma unroll
+                    for (int i = KW - 2; i >= 0; --i) lt = (y[i] < ks[i]) || (y[i] == ks[i] && lt);
                 }
-            }
-        } else {
-            const uint64_t kx = word_of<KW>(key.w, w);
-            lt = e0 < kx;
-            const bool need = valid && e0 == kx && ((meta_ties(meta) >> s) & 1ull);
-            if (__ballot(need)) {
-                if (need) lt = tie_less<KW, M>(ik, ref, static_cast<uint32_t>(s), w, key.w);
+            } else {
+                const bool open = (meta_ties(meta) >> s) & 1ull;
+                if (w != lw || (e0 == ks[0] && open)) {
+                    if (w != lw) {
+                        in_slices<KW>(key.w, w, ks);
+                        lw = w;
+                        lt = e0 < ks[0];
+                    }
+                    if (e0 == ks[0] && open) lt = tie_less<KW, M>(e, ks);
+                }
             }
         }
         lt = valid && lt;
         const uint32_t ci = static_cast<uint32_t>(__popcll(group_bits<M>(__ballot(lt), gbase)));
         ref = meta.x + ci;
-        lw = w;
     }
     return ref;
 }
 
 // Leaves of 32-byte keys: per leaf, the m entries' deciding words (those of
-// the leaf's parent; big-endian numbers), then m 32-byte records {the other
-// three words in order, value}.  Leaves of 8-byte keys: lkeys[leaf][m] keys,
+// the leaf's parent; big-endian numbers), then m 32-byte records {slices 1 to
+// 3, value}.  Leaves of 8-byte keys: lkeys[leaf][m] keys,
 // lvals[leaf][m].
 constexpr uint64_t kLeafEntry32 = 40;  // bytes per entry of a 32-byte-key leaf
 
@@ -255,7 +267,7 @@ __device__ __forceinline__ const uint64_t* leaf_words(const WideView& v, uint32_
     return reinterpret_cast<const uint64_t*>(v.lkeys + static_cast<uint64_t>(leaf) * M * (KW == 1 ? 8 : kLeafEntry32));
 }
 
-// the other words and the value of entry s of a 32-byte-key leaf
+// slices 1 to 3 and the value of entry s of a 32-byte-key leaf
 template <int M>
 __device__ __forceinline__ void leaf_record(const WideView& v, uint32_t leaf, int s, uint64_t (&w)[3], uint64_t& val) {
     const uint4* r = reinterpret_cast<const uint4*>(v.lkeys + static_cast<uint64_t>(leaf) * M * kLeafEntry32 + M * 8 +
@@ -267,11 +279,22 @@ __device__ __forceinline__ void leaf_record(const WideView& v, uint32_t leaf, in
     val = (static_cast<uint64_t>(b.w) << 32) | b.z;
 }
 
-// word i of the three a record holds when the deciding word is lw
-template <int KW>
-__device__ __forceinline__ uint64_t other_word(const uint64_t (&k)[KW], int i, uint32_t lw) {
-    const uint64_t m = lw > static_cast<uint32_t>(i) ? ~0ull : 0ull;
-    return (k[i] & m) | (k[i + 1] & ~m);
+// Whether entry s of a leaf is the query, given in the leaf's order of words
+// (and the entry's value).
+template <int KW, int M>
+__device__ __forceinline__ bool leaf_has(const WideView& v, uint32_t leaf, int s, const uint64_t (&ks)[KW],
+                                         uint64_t& val) {
+    const uint64_t w0 = leaf_words<KW, M>(v, leaf)[s];
+    bool eq = w0 == ks[0];
+    if constexpr (KW == 1) {
+        val = v.lvals[static_cast<uint64_t>(leaf) * M + s];
+    } else {
+        uint64_t w[3];
+        leaf_record<M>(v, leaf, s, w, val);
+#pragma unroll
+        for (int i = 1; i < KW; ++i) eq = eq && w[i - 1] == ks[i];
+    }
+    return eq;
 }
 
 // entry s of a leaf as a key (and its value)
@@ -285,11 +308,8 @@ __device__ __forceinline__ Key<KW> leaf_entry(const WideView& v, uint32_t leaf, 
     } else {
         uint64_t w[3];
         leaf_record<M>(v, leaf, s, w, val);
-#pragma unroll
-        for (int i = 0; i < KW; ++i) {
-            const uint64_t lo = i < KW - 1 ? w[i < 3 ? i : 2] : w0, hi = i > 0 ? w[i - 1] : w0;
-            k.w[i] = lw == static_cast<uint32_t>(i) ? w0 : (lw > static_cast<uint32_t>(i) ? lo : hi);
-        }
+        const uint64_t x[KW] = {w0, w[0], w[1], w[2]};
+        in_slices<KW>(x, lw, k.w);
 #pragma unroll
         for (int i = 0; i < KW; ++i) k.raw[i] = __builtin_bswap64(k.w[i]);
     }
@@ -324,12 +344,12 @@ __global__ __launch_bounds__(kWBlock) void k_wlookup(WideView v, const uint8_t* 
         const bool valid = i < B;
         const Key<KW> key = valid ? load_key<KW>(q + i * KB) : max_key<KW>();
         uint32_t lw;
-        const uint32_t leaf = descend<KW, M, false>(v, key, valid, root, height, s, gbase, lw);
+        uint64_t ks[KW];
+        const uint32_t leaf = descend<KW, M, false>(v, key, valid, root, height, s, gbase, lw, ks);
         // the padding repeats the last key, so the first equal slot is a
         // real one; an empty tree's one leaf holds only padding
         uint64_t val = 0;
-        const Key<KW> lk = leaf_entry<KW, M>(v, leaf, lw, s, val);
-        const bool eq = valid && !empty && key_eq<KW>(lk, key);
+        const bool eq = leaf_has<KW, M>(v, leaf, s, ks, val) && valid && !empty;
         const uint64_t gb = group_bits<M>(__ballot(eq), gbase);
         const int f = gb ? __ffsll(static_cast<long long>(gb)) - 1 : 0;
         const uint64_t fv = shfl_u64(val, gbase + f);
@@ -374,8 +394,8 @@ __global__ __launch_bounds__(kWBlock) void k_wlookupg(WideView v, const uint8_t*
     for (uint64_t base = wave * QPW; base < B; base += nwaves * QPW) {
         uint64_t i[Q];
         bool valid[Q];
-        uint64_t key[Q][KW];
-        uint32_t ref[Q], lw[Q];
+        uint64_t ks[Q][KW];
+        uint32_t ref[Q], lw[Q];  // ks: the query's words in the order of deciding word lw
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
             i[j] = base + static_cast<uint64_t>(j) * (64 / G) + lane / G;
@@ -384,7 +404,7 @@ __global__ __launch_bounds__(kWBlock) void k_wlookupg(WideView v, const uint8_t*
                 // a query past the end reads the last one's key
                 const Key<KW> k = load_key<KW>(q + (valid[j] ? i[j] : B - 1) * KB);
 #pragma unroll
-                for (int x = 0; x < KW; ++x) key[j][x] = k.w[x];
+                for (int x = 0; x < KW; ++x) ks[j][x] = k.w[x];
             }
             ref[j] = root;
             lw[j] = 0;
@@ -400,12 +420,17 @@ __global__ __launch_bounds__(kWBlock) void k_wlookupg(WideView v, const uint8_t*
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
                 const uint32_t w = KW > 1 ? meta_word(meta[j]) : 0u;
-                const uint64_t kx = word_of<KW>(key[j], w);
+                if (KW > 1 && w != lw[j]) {  // a level or two of a descent
+                    uint64_t key[KW];
+                    in_slices<KW>(ks[j], lw[j], key);  // back: a swap
+                    in_slices<KW>(key, w, ks[j]);
+                    lw[j] = w;
+                }
                 uint32_t c = 0, tied = 0;
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    c += e0[j][e] < kx ? 1u : 0u;
-                    tied |= (e0[j][e] == kx ? 1u : 0u) << e;
+                    c += e0[j][e] < ks[j][0] ? 1u : 0u;
+                    tied |= (e0[j][e] == ks[j][0] ? 1u : 0u) << e;
                 }
                 if constexpr (KW > 1) {
                     // a lane with ties goes on to its entries' next word,
@@ -419,14 +444,13 @@ __global__ __launch_bounds__(kWBlock) void k_wlookupg(WideView v, const uint8_t*
                             uint32_t eq = 0;
 #pragma unroll
                             for (int e = 0; e < E; ++e) {
-                                c += (tied >> e & 1u) && ex[e] < key[j][x] ? 1u : 0u;
-                                eq |= (ex[e] == key[j][x] ? 1u : 0u) << e;
+                                c += (tied >> e & 1u) && ex[e] < ks[j][x] ? 1u : 0u;
+                                eq |= (ex[e] == ks[j][x] ? 1u : 0u) << e;
                             }
                             tied &= eq;
                         }
                 }
                 ref[j] = meta[j].x + group_sum<G>(c);
-                lw[j] = w;
             }
         }
         // leaf: deciding words of this lane's entries, then the rest and the
@@ -439,10 +463,9 @@ __global__ __launch_bounds__(kWBlock) void k_wlookupg(WideView v, const uint8_t*
         bool hit[Q];
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
-            const uint64_t kx = word_of<KW>(key[j], lw[j]);
             uint32_t m = 0;
 #pragma unroll
-            for (int e = 0; e < E; ++e) m |= (w0[j][e] == kx ? 1u : 0u) << e;
+            for (int e = 0; e < E; ++e) m |= (w0[j][e] == ks[j][0] ? 1u : 0u) << e;
             tied[j] = valid[j] && !empty ? m : 0u;
             val[j] = 0;
             hit[j] = false;
@@ -467,7 +490,7 @@ __global__ __launch_bounds__(kWBlock) void k_wlookupg(WideView v, const uint8_t*
                         uint64_t w[3];
                         leaf_record<M>(v, ref[j], slot, w, vv);
 #pragma unroll
-                        for (int x = 0; x < 3; ++x) eq = eq && w[x] == other_word<KW>(key[j], x, lw[j]);
+                        for (int x = 0; x < 3; ++x) eq = eq && w[x] == ks[j][x + 1];
                     }
                     tied[j] &= tied[j] - 1;
                     if (eq) {
@@ -513,7 +536,8 @@ __global__ __launch_bounds__(kWBlock) void k_wrange(WideView v, const uint8_t* _
         const uint32_t mx = valid ? maxc[i] : 0u;
         const uint64_t o = valid ? off[i] : 0ull;
         uint32_t lw;
-        uint32_t leaf = descend<KW, M, true>(v, a, valid, root, height, s, gbase, lw);
+        uint64_t ks[KW];
+        uint32_t leaf = descend<KW, M, true>(v, a, valid, root, height, s, gbase, lw, ks);
         uint32_t c = 0;
         bool active = valid && !empty && mx > 0 && !key_less<KW>(b, a);
         // walk the chain; the loop runs while any group of the wave is active
@@ -623,13 +647,14 @@ __global__ void k_wleaves(uint8_t* __restrict__ lkeys, uint64_t* __restrict__ lv
                 w = deciding_word<KW>(load_key<KW>(sk + kb * KB), load_key<KW>(sk + (ke - 1) * KB));
             }
             uint8_t* lb = lkeys + j * M * kLeafEntry32;
-            reinterpret_cast<uint64_t*>(lb)[s] = word_of<KW>(k.w, w);
-            const uint64_t o0 = other_word<KW>(k.w, 0, w), o1 = other_word<KW>(k.w, 1, w), o2 = other_word<KW>(k.w, 2, w);
+            uint64_t o[KW];
+            in_slices<KW>(k.w, w, o);
+            reinterpret_cast<uint64_t*>(lb)[s] = o[0];
             uint4* r = reinterpret_cast<uint4*>(lb + M * 8 + s * 32);
-            r[0] = make_uint4(static_cast<uint32_t>(o0), static_cast<uint32_t>(o0 >> 32), static_cast<uint32_t>(o1),
-                              static_cast<uint32_t>(o1 >> 32));
-            r[1] = make_uint4(static_cast<uint32_t>(o2), static_cast<uint32_t>(o2 >> 32), static_cast<uint32_t>(val),
-                              static_cast<uint32_t>(val >> 32));
+            r[0] = make_uint4(static_cast<uint32_t>(o[1]), static_cast<uint32_t>(o[1] >> 32),
+                              static_cast<uint32_t>(o[2]), static_cast<uint32_t>(o[2] >> 32));
+            r[1] = make_uint4(static_cast<uint32_t>(o[3]), static_cast<uint32_t>(o[3] >> 32),
+                              static_cast<uint32_t>(val), static_cast<uint32_t>(val >> 32));
         }
         if (s == 0) {
             lmeta[j] = make_uint2(static_cast<uint32_t>(c) | w << 8,
@@ -661,14 +686,18 @@ __global__ void k_winner(uint8_t* __restrict__ ikeys, uint4* __restrict__ imeta,
         // word-sliced, the deciding word's slice first, each word as a
         // big-endian number (the order the search compares in)
         uint64_t* ik = reinterpret_cast<uint64_t*>(ikeys);
+        uint64_t o[KW];
+        in_slices<KW>(k.w, w, o);
 #pragma unroll
-        for (int x = 0; x < KW; ++x)
-            ik[((node_base + j) * KW + slice_of(static_cast<uint32_t>(x), w)) * M + s] = k.w[x];
+        for (int x = 0; x < KW; ++x) ik[((node_base + j) * KW + x) * M + s] = o[x];
         // the entry's deciding word is shared with the next key in key order,
         // the first of the next child
         bool shared = false;
-        if (KW > 1 && s + 1 < c)
-            shared = word_of<KW>(k.w, w) == word_of<KW>(load_key<KW>(cmin + (b + s + 1) * KB).w, w);
+        if (KW > 1 && s + 1 < c) {
+            uint64_t next[KW];
+            in_slices<KW>(load_key<KW>(cmin + (b + s + 1) * KB).w, w, next);
+            shared = o[0] == next[0];
+        }
         const uint64_t bits = group_bits<M>(__ballot(shared), gbase);
         if (s == 0) {
             imeta[node_base + j] = make_uint4(static_cast<uint32_t>(b), static_cast<uint32_t>(c) | w << 8,
@@ -1105,7 +1134,7 @@ gt_status wide_export(const WideTree* w, void* host_buf, uint64_t* bytes, hipStr
         const uint64_t dw = im[i].y >> 8, kids = im[i].y & 0xFFu;
         for (uint64_t j = 0; j < m; ++j)
             for (uint64_t wd = 0; wd < kw; ++wd) {
-                const uint64_t slice = wd == dw ? 0 : (wd < dw ? wd + 1 : wd);
+                const uint64_t slice = slice_of(static_cast<uint32_t>(wd), static_cast<uint32_t>(dw));
                 uint64_t x;
                 memcpy(&x, ik.data() + ((i * kw + slice) * m + j) * 8, 8);
                 if (kw > 1) x = __builtin_bswap64(x);
@@ -1131,9 +1160,9 @@ gt_status wide_export(const WideTree* w, void* host_buf, uint64_t* bytes, hipStr
                 uint64_t x[5];
                 memcpy(&x[0], lb + j * 8, 8);
                 memcpy(&x[1], lb + m * 8 + j * 32, 32);
-                const int dw = static_cast<int>(lm[i].x >> 8);
-                for (int wd = 0; wd < 4; ++wd) {
-                    const uint64_t be = __builtin_bswap64(x[wd == dw ? 0 : (wd < dw ? wd + 1 : wd)]);
+                const uint32_t dw = lm[i].x >> 8;
+                for (uint32_t wd = 0; wd < 4; ++wd) {
+                    const uint64_t be = __builtin_bswap64(x[slice_of(wd, dw)]);
                     memcpy(o + j * kb + wd * 8, &be, 8);
                 }
                 memcpy(o + C * kb + j * 8, &x[4], 8);
