@@ -109,9 +109,8 @@ typedef struct {
     uint32_t value_coload;    /* 1: a lookup reads the leaf's value line with
                                  its key line (one dependent load fewer);
                                  2: it reads the one value after the match;
-                                 0 = by batch size and use (1 up to 2^16
-                                 queries and once the tree took an insert or
-                                 delete batch, else 2)                        */
+                                 0 = by batch size (1 up to 2^16 queries,
+                                 else 2)                                      */
     uint32_t xcd_split;       /* 1: large lookup batches are split by key
                                  range over the 8 XCDs so that each XCD's L2
                                  holds the inner nodes of its own subtrees;

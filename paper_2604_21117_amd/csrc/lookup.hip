@@ -508,11 +508,11 @@ static void launch_lookup_lv(const TreeView<K>& t, const LaunchCfg& cfg, const K
 //    registers than they add), and one value read after the match instead of
 //    the whole line before it, which an absent key does not read at all: 2^20
 //    queries of 2^23 u64 keys, half absent, 47.9 us against 59.2; 2^20
-//    present ones of 2^18 u64 keys 33.6 against 36.9.  Not on a tree that took
-//    updates: its searches read child lines too, and a round more a query
-//    costs what the lines save (2^20 present keys of 2^24 after 2^20 inserts
-//    85.5 us with the whole line, 88.7 with one value; half absent 85.2 and
-//    82.6).
+//    present ones of 2^18 u64 keys 33.6 against 36.9.  Also on a tree that
+//    took updates, whose searches read child lines too: 2^20 present keys of
+//    2^24 after 2^20 inserts 96.9 us, 96.6 with the whole line, half absent
+//    88.4 and 96.8, Zipf half absent 65.2 and 85.1; loaded at fill 0.75 72.0
+//    and 72.4, 63.1 and 72.3, 47.5 and 53.5.
 //  - From kStageBatch on the grid walks its tiles more than once and staging
 //    the top two levels is shared: 2^20 queries of 2^22 u64 keys 52.5 us
 //    against 53.7; 98304 queries 7.5 against 7.4, of 2^21 keys 6.9 against 6.6.
@@ -521,7 +521,7 @@ static LaunchCfg shape_for(const LaunchCfg& cfg, uint64_t B) {
     if (cfg.shape_auto & 1) c.lanes = B < kMidBatch ? 16 : 8;
     if (cfg.shape_auto & 2) c.queries_per_group = B <= kPassBatch ? 1 : 2;
     if (cfg.shape_auto & 4) c.lds_levels = B < kStageBatch ? 0 : 2;
-    if (cfg.value_coload == 2) c.value_coload = B <= kPassBatch || cfg.rewritten ? 1 : 0;
+    if (cfg.value_coload == 2) c.value_coload = B <= kPassBatch ? 1 : 0;
     return c;
 }
 

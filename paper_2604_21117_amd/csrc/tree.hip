@@ -366,7 +366,6 @@ gt_status tree_build(const gt_params* p, const void* keys, const void* values, u
     t->cfg.leaf_stream = static_cast<int>(p->leaf_stream);  // 0 by batch and tree size, 1 both lines, 2 none
     // lookup shape fields the caller left at 0 follow the batch size
     t->cfg.shape_auto = (p->lanes_per_query ? 0 : 1) | (p->queries_per_group ? 0 : 2) | (p->lds_levels ? 0 : 4);
-    t->cfg.rewritten = 0;
     layout(t, reinterpret_cast<uint8_t*>(arena), lo);
     gt_status st = kb == 8 ? build_t<uint64_t>(t, keys, values, n, stream)
                            : build_t<uint32_t>(t, keys, values, n, stream);
@@ -469,7 +468,6 @@ gt_status tree_delete_batch(gt_tree* t, const void* keys, uint64_t B, uint8_t* s
                                              status_out, t->d_flag, seq, &on_host, stream);
     HIP_TRY(hipGetLastError());
     t->deletes++;
-    t->cfg.rewritten = 1;
     bool rebuild;
     if (on_host) {
         // the kernel stores (seq << 32 | flag) into the pinned word as its
@@ -550,7 +548,6 @@ gt_status tree_insert_batch(gt_tree* t, const void* keys, const void* values, ui
     const uint32_t hc = height_cap(t->leaf_cap);
     if (hc > t->h_bound) t->h_bound = hc;
     t->inserts++;
-    t->cfg.rewritten = 1;
     return hipGetLastError() == hipSuccess ? GT_OK : GT_ERR_HIP;
 }
 

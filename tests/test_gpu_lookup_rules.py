@@ -1,0 +1,75 @@
+"""What a large lookup's shape goes by: a tree's updates do not change it."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_util import assert_lookup_parity, key_set, mk_tree
+
+pytestmark = pytest.mark.gpu
+
+
+def lookup_us(t, q):
+    """Least time of one lookup of the numpy batch q, from graph replays."""
+    import torch
+    import paper_2604_21117_amd as g
+    qd = t.dev(q)
+    v = torch.empty(len(q), dtype=t.tdtype, device="cuda")
+    f = torch.empty(len(q), dtype=torch.uint8, device="cuda")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        g.tree_lookup_batch(t.h, qd, v, f)
+    torch.cuda.synchronize()
+    gr = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(gr, stream=s):
+        for _ in range(10):
+            g.tree_lookup_batch(t.h, qd, v, f)
+    gr.replay()
+    times = []
+    for _ in range(15):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        gr.replay()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 100)
+    return min(times)
+
+
+def test_one_insert_does_not_slow_large_lookups():
+    """2^20 queries, half absent, of 2^22 keys after one key more: within 1.1
+    times the time with the value read after the match (1.18 when any update
+    switched to whole value lines)."""
+    keys = key_set(1 << 22, 64, 61)
+    vals = synth.values_for(keys, 61, 64)
+    B = 1 << 20
+    absent = synth.uniform_keys(B, 62, 64, exclude=keys)
+    rng = np.random.default_rng(63)
+    q = np.where(rng.random(B) < 0.5, keys[rng.integers(0, len(keys), B)], absent)
+    us = []
+    for coload in (0, 2):
+        t = mk_tree(keys, vals, 8, leaf_slack=1 << 8, value_coload=coload)
+        t.insert(absent[:1], absent[:1])
+        us.append(lookup_us(t, q))
+        t.close()
+    assert us[0] < 1.1 * us[1], us
+
+
+@pytest.mark.parametrize("width", [32, 64])
+def test_large_lookup_after_a_rebuild(width):
+    """A delete that rebuilds the tree in place, then lookups of a size on
+    either side of each shape's line."""
+    keys = key_set(60000, width, 64 + width)
+    vals = synth.values_for(keys, 64, width)
+    sa = oracle.SortedArray(keys, vals, width)
+    t = mk_tree(keys, vals, width // 8, leaf_slack=1 << 12, max_batch=1 << 16)
+    first = np.sort(keys)
+    gone = first[:50000]
+    assert np.array_equal(t.delete(gone), sa.delete(gone))
+    for B in ((1 << 16) - 3, (1 << 16) + 1, (1 << 17) + 5, 300001):
+        assert_lookup_parity(t, sa, synth.mixed_queries(keys, B, B, width))
+    k = synth.uniform_keys(3000, 65, width, exclude=keys)
+    assert np.array_equal(t.insert(k, k), sa.insert(k, k))
+    for B in ((1 << 16) + 1, 300001):
+        assert_lookup_parity(t, sa, synth.mixed_queries(np.concatenate([keys, k]), B, B + 1, width))
+    t.close()
