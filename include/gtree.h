@@ -120,8 +120,9 @@ typedef struct {
                                  inner nodes other queries reuse from L2):
                                  1: key and value lines, every batch; 2:
                                  none; 0 = default: the values of batches
-                                 above 2^16 queries on trees with 256 MB of
-                                 leaf lines or more                         */
+                                 above 2^16 queries on trees loaded with 256
+                                 MB of leaf lines or more (skewed queries
+                                 are faster with 2)                         */
     uint32_t reserved;        /* must be 0                                    */
 } gt_params;
 

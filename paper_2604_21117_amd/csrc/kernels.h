@@ -14,6 +14,7 @@ struct LaunchCfg {
     int value_coload;       // a leaf's value line: 1 read with its key line, 0 one value after the match, 2 by batch size
     int xcd_split;          // 0 off, 1 on from kXcdMinBatch queries, 2 always
     int leaf_stream;        // non-temporal leaf loads: 0 values of large batches, 1 key and value lines, 2 none
+    uint64_t loaded_leaves; // leaves the tree was loaded with, or rebuilt to
     int shape_auto;         // lookup shape chosen by batch size: bit 0 lanes, 1 queries per group, 2 LDS levels
 };
 

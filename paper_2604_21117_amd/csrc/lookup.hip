@@ -446,11 +446,14 @@ static void launch_lookup_xcd(const TreeView<K>& t, const K* q, uint64_t B, K* v
 constexpr uint64_t kPassBatch = 1u << 16;   // one pass of the grid at one query per group
 constexpr uint64_t kStageBatch = 1u << 17;  // from here on the top levels are staged in LDS
 
-// Values are streamed past the caches in large batches over trees whose leaf
-// lines outgrow the 256 MB memory-side cache: there a line is not read again
-// before it is evicted.  2^20 present keys of 2^24 u64 keys (256 MB of leaf
-// lines) 62.2 us against 62.9 with plain loads; below that size the lines
-// are found again, whole value lines of 2^21 keys 46.7 us, streamed 54.4.
+// Values are streamed past the caches in large batches over trees loaded with
+// leaf lines that outgrow the 256 MB memory-side cache: there few lines are
+// read again before they are evicted.  2^20 uniform keys of 2^24 u64 keys (256
+// MB of leaf lines) 63.6 us against 64.4 with plain loads, loaded at fill 0.75
+// 72.0 and 74.4; below that size the lines are found again, 2^20 keys after
+// 2^20 inserts 72.9 us streamed and 60.6 not.  Skewed queries find them at any
+// size (Zipf(0.99) ones of 2^24 keys 57.2 us, 43.5 with plain loads): a program
+// that makes them turns streaming off.
 constexpr uint64_t kStreamLeafBytes = 256ull << 20;
 
 template <class K, int G, int QPG, int LV>
@@ -459,7 +462,7 @@ static void launch_lookup_v(const TreeView<K>& t, const LaunchCfg& cfg, const K*
     const bool xcd = cfg.xcd_split == 2 || (cfg.xcd_split == 1 && B >= kXcdMinBatch);
     // leaf lines read non-temporally: both (leaf_stream 1), none (2), or by
     // default the values, by the rule above
-    const bool big = 2ull * t.leaf_cap * kSlots * sizeof(K) >= kStreamLeafBytes;
+    const bool big = 2 * cfg.loaded_leaves * kSlots * sizeof(K) >= kStreamLeafBytes;
     const int nt = cfg.leaf_stream == 1 ? 3 : (cfg.leaf_stream == 0 && big && B > kPassBatch ? 2 : 0);
     if (xcd) {
         if (cfg.value_coload) {

@@ -206,6 +206,7 @@ gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, 
         launch_build<K>(v, sk, sv, n, sizes.data(), static_cast<int>(sizes.size()), maxbuf, s);
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) st = GT_ERR_HIP;
         t->h_bound = static_cast<uint32_t>(sizes.size());
+        t->cfg.loaded_leaves = sizes[0];
     } while (0);
     hipStreamSynchronize(s);
     hipFree(tmp);

@@ -1,4 +1,5 @@
-"""What a large lookup's shape goes by: a tree's updates do not change it."""
+"""What a large lookup's shape goes by: the tree as it is, not its updates or
+the pool it lies in."""
 import numpy as np
 import pytest
 
@@ -50,6 +51,23 @@ def test_one_insert_does_not_slow_large_lookups():
     for coload in (0, 2):
         t = mk_tree(keys, vals, 8, leaf_slack=1 << 8, value_coload=coload)
         t.insert(absent[:1], absent[:1])
+        us.append(lookup_us(t, q))
+        t.close()
+    assert us[0] < 1.1 * us[1], us
+
+
+def test_room_in_the_pool_does_not_slow_large_lookups():
+    """2^20 queries of 2^20 keys, half of them inserted, in a pool of 2^20 more
+    leaves (over 256 MB): within 1.1 times the time with plain loads (1.2 when
+    the pool's size decided)."""
+    keys = key_set(1 << 20, 64, 71)
+    vals = synth.values_for(keys, 71, 64)
+    half = 1 << 19
+    q = keys[np.random.default_rng(72).integers(0, len(keys), 1 << 20)]
+    us = []
+    for stream in (0, 2):
+        t = mk_tree(keys[:half], vals[:half], 8, leaf_slack=1 << 20, max_batch=half, leaf_stream=stream)
+        t.insert(keys[half:], vals[half:])
         us.append(lookup_us(t, q))
         t.close()
     assert us[0] < 1.1 * us[1], us
