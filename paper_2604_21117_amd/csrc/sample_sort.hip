@@ -43,6 +43,8 @@
 // by a valid sorted one, every key 0 and index i at position i.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
+#include <chrono>
 #include <type_traits>
 #include "common.h"
 #include "kernels.h"
@@ -133,6 +135,7 @@ __device__ __forceinline__ bool ss_less(K ka, uint32_t pa, K kb, uint32_t pb) {
     else return ka < kb;
 }
 
+// a 32-bit mixer (the lowbias32 constants of Chris Wellons' hash prospector)
 __device__ __forceinline__ uint32_t ss_hash(uint32_t x) {
     x ^= x >> 16;
     x *= 0x7feb352du;
@@ -156,11 +159,14 @@ __device__ __forceinline__ bool ss_refused(const uint32_t* refuse) {
     }
 }
 
-// position of sample i of S in a segment of m pairs: one per stratum
-__device__ __forceinline__ uint32_t ss_sample_at(uint32_t i, uint32_t S, uint32_t m) {
+// position of sample i of S in a segment of m pairs: one per stratum.  Every
+// sort takes another seed, so that no input keeps its sample from telling the
+// groups apart (positions that were a fixed hash of i and m let 2^18 keys fall
+// into one group, 29 ms for 76 us).
+__device__ __forceinline__ uint32_t ss_sample_at(uint32_t i, uint32_t S, uint32_t m, uint32_t seed) {
     const uint64_t a = static_cast<uint64_t>(i) * m / S, b = static_cast<uint64_t>(i + 1) * m / S;
     const uint32_t w = b > a ? static_cast<uint32_t>(b - a) : 1u;
-    return static_cast<uint32_t>(a) + ss_hash(i * 0x9E3779B9u + m) % w;
+    return static_cast<uint32_t>(a) + ss_hash(ss_hash(i ^ seed) + m) % w;
 }
 
 // Bitonic sort of m pairs (any m) by (key, tie): every comparator puts the
@@ -270,7 +276,7 @@ __device__ __forceinline__ int ss_merge_sort(K (*a)[kSsPadded], uint32_t (*p)[kS
 template <class K, bool TIE>
 __global__ __launch_bounds__(1024) void k_ss_sample(const K* __restrict__ kin, const uint32_t* __restrict__ pin,
                                                      uint32_t n, const uint32_t* __restrict__ seg_start,
-                                                     uint32_t groups, uint32_t over, uint32_t runs, K* gk,
+                                                     uint32_t groups, uint32_t over, uint32_t runs, uint32_t seed, K* gk,
                                                      uint32_t* gp, K* sk, uint32_t* sp, uint32_t* cnt, uint32_t* cur,
                                                      uint32_t* list, uint32_t* fail, uint32_t force, uint32_t* err,
                                                      uint32_t err_bit, uint32_t* dup) {
@@ -296,7 +302,7 @@ __global__ __launch_bounds__(1024) void k_ss_sample(const K* __restrict__ kin, c
         K k = kmax<K>();
         uint32_t q = 0xFFFFFFFFu;
         if (m) {
-            const uint32_t at = b + ss_sample_at(first + i, S, m);
+            const uint32_t at = b + ss_sample_at(first + i, S, m, seed);
             k = kin[at];
             q = pin ? pin[at] : at;
         }
@@ -334,8 +340,8 @@ constexpr int kSsRankThreads = 256;
 
 template <class K, bool TIE>
 __global__ __launch_bounds__(kSsRankThreads) void k_ss_sample_rank(
-    const K* __restrict__ kin, const uint32_t* __restrict__ pin, uint32_t n, uint32_t groups, uint32_t over, K* gk,
-    uint32_t* gp, uint32_t* cnt, uint32_t* cur, uint32_t* list, uint32_t* fail, uint32_t force, uint32_t* err,
+    const K* __restrict__ kin, const uint32_t* __restrict__ pin, uint32_t n, uint32_t groups, uint32_t over,
+    uint32_t seed, K* gk, uint32_t* gp, uint32_t* cnt, uint32_t* cur, uint32_t* list, uint32_t* fail, uint32_t force, uint32_t* err,
     uint32_t err_bit, uint32_t* dup) {
     constexpr uint32_t G = 16, R = kSsRankStep / G;
     __shared__ K a[kSsRankSample];
@@ -353,7 +359,7 @@ __global__ __launch_bounds__(kSsRankThreads) void k_ss_sample_rank(
         }
     }
     for (uint32_t i = tid; i < S; i += kSsRankThreads) {
-        const uint32_t at = ss_sample_at(i, S, n);
+        const uint32_t at = ss_sample_at(i, S, n, seed);
         a[i] = kin[at];
         p[i] = pin ? pin[at] : at;
     }
@@ -459,7 +465,8 @@ __global__ __launch_bounds__(256) void k_ss_rank(const K* __restrict__ sk, const
 // The splitters in LDS as an implicit search tree in breadth-first order
 // (node 1 the root, node i's children 2i and 2i + 1): a search of a sorted
 // array would read power-of-two strides, one LDS bank; in this order the
-// nodes of a level are neighbours.  groups is a power of two.
+// nodes of a level are neighbours.  groups is a power of two.  (Sanders and
+// Winkel, "Super Scalar Sample Sort", ESA 2004.)
 template <class K>
 __device__ __forceinline__ void ss_load_tree(const K* __restrict__ gk, const uint32_t* __restrict__ gp,
                                              uint32_t groups, K* tk, uint32_t* tp) {
@@ -1104,6 +1111,14 @@ __global__ __launch_bounds__(NT) void k_ss_groups(const K* kin, const P* pin, co
 // ------------------------------------------------------------- host side
 
 uint64_t sample_sort_max() { return kSsMax; }
+
+// The sample's seed: another one for every sort (a captured one keeps its).
+static uint32_t ss_next_seed() {
+    static std::atomic<uint32_t> next{
+        static_cast<uint32_t>(std::chrono::steady_clock::now().time_since_epoch().count())};
+    return next.fetch_add(0x9E3779B9u, std::memory_order_relaxed);
+}
+
 bool sort_pairs_two_buffers(uint64_t n) { return n > kSsOneLevel; }
 uint64_t sample_sort_tmp_bytes(uint64_t n, int key_bytes) { return ss_plan(n, key_bytes).bytes; }
 
@@ -1115,6 +1130,7 @@ static void ss_partition(const SsPlan& pl, uint8_t* tmp, const K* src, const P* 
                          hipStream_t s) {
     uint32_t* fail = reinterpret_cast<uint32_t*>(tmp + pl.o_fail);
     uint32_t* list = reinterpret_cast<uint32_t*>(tmp + pl.o_list);
+    const uint32_t seed = ss_next_seed();
     const K* kin = src;
     const P* in = pin;
     K* kout = ka;
@@ -1135,10 +1151,10 @@ static void ss_partition(const SsPlan& pl, uint8_t* tmp, const K* src, const P* 
         const uint32_t S = v.groups * v.over, len = S / v.runs;
         if (v.segs == 1 && S >= kSsRankStep && S <= kSsRankSample) {
             hipLaunchKernelGGL((k_ss_sample_rank<K, TIE>), dim3(S * 16 / kSsRankThreads), dim3(kSsRankThreads), 0, s,
-                               kin, tie, n, v.groups, v.over, gk, gp, cnt, cur, list, fail, force, err, err_bit, dup);
+                               kin, tie, n, v.groups, v.over, seed, gk, gp, cnt, cur, list, fail, force, err, err_bit, dup);
         } else {
             hipLaunchKernelGGL((k_ss_sample<K, TIE>), dim3(v.segs, v.runs), dim3(len <= 256 ? 256 : (len <= 512 ? 512 : 1024)),
-                               0, s, kin, tie, n, seg, v.groups, v.over, v.runs, gk, gp, sk, sp, cnt, cur, list, fail,
+                               0, s, kin, tie, n, seg, v.groups, v.over, v.runs, seed, gk, gp, sk, sp, cnt, cur, list, fail,
                                force, err, err_bit, dup);
             auto rank = [&](auto R) {
                 constexpr int N = decltype(R)::value;

@@ -10,21 +10,29 @@ from gpu_util import assert_lookup_parity, key_set, mk_tree
 pytestmark = pytest.mark.gpu
 
 
-def lookup_us(t, q):
+def lookup_us(t, q, levelwise=False):
     """Least time of one lookup of the numpy batch q, from graph replays."""
     import torch
     import paper_2604_21117_amd as g
     qd = t.dev(q)
     v = torch.empty(len(q), dtype=t.tdtype, device="cuda")
     f = torch.empty(len(q), dtype=torch.uint8, device="cuda")
+    ws = t.levelwise_workspace(len(q)) if levelwise else None
     s = torch.cuda.Stream()
+
+    def call():
+        if levelwise:
+            g.tree_lookup_levelwise(t.h, qd, 0, v, f, ws)
+        else:
+            g.tree_lookup_batch(t.h, qd, v, f)
+
     with torch.cuda.stream(s):
-        g.tree_lookup_batch(t.h, qd, v, f)
+        call()
     torch.cuda.synchronize()
     gr = torch.cuda.CUDAGraph()
     with torch.cuda.graph(gr, stream=s):
         for _ in range(10):
-            g.tree_lookup_batch(t.h, qd, v, f)
+            call()
     gr.replay()
     times = []
     for _ in range(15):
