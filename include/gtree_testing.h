@@ -34,6 +34,23 @@ extern "C" {
 uint32_t gt_set_sort_spin_limit(uint32_t limit);
 
 /*
+ * Testing hook of the sort above 8192 keys: the largest input that the sample
+ * sort takes (default and at most 2^26).  Larger inputs are radix-sorted, the
+ * bulk load then through (key, position) pairs, a gather and a duplicate
+ * check; 0 sends every sort above 8192 keys that way.  Process-wide, read when
+ * a sort is launched.  Returns the previous value.
+ */
+uint64_t gt_set_sample_sort_max(uint64_t keys);
+
+/*
+ * Testing hook of the sample sort: the largest group sorted in LDS (default
+ * and at most 8192 pairs, and 2048 or 4096 for most groups).  A larger group,
+ * which the sample makes very unlikely, is sorted in device memory.
+ * Process-wide, read when a sort is launched.  Returns the previous value.
+ */
+uint32_t gt_set_sample_sort_group(uint32_t pairs);
+
+/*
  * Testing switch of the one-key insert: a batch of B = 1 runs in one kernel
  * (descent, leaf and parent rewrites, header, mirror) instead of the batch
  * path's kernels, with the same resulting tree.  enable = 0 sends B = 1

@@ -118,6 +118,10 @@ def lib():
         L.tree_export.argtypes = [vp, vp, C.POINTER(u64), vp]
         L.gt_set_sort_spin_limit.argtypes = [u32]
         L.gt_set_sort_spin_limit.restype = u32
+        L.gt_set_sample_sort_max.argtypes = [u64]
+        L.gt_set_sample_sort_max.restype = u64
+        L.gt_set_sample_sort_group.argtypes = [u32]
+        L.gt_set_sample_sort_group.restype = u32
         L.gt_set_single_key_insert.argtypes = [C.c_int]
         L.gt_set_single_key_insert.restype = C.c_int
         L.gt_set_one_launch_insert.argtypes = [C.c_int]
@@ -294,6 +298,18 @@ def set_sort_spin_limit(limit: int) -> int:
     """Testing hook: the device sort's look-back limit (0 makes every sort
     of more than 4096 keys fail); returns the previous value."""
     return int(lib().gt_set_sort_spin_limit(limit))
+
+
+def set_sample_sort_max(keys: int) -> int:
+    """Testing hook: the largest input of the sample sort (larger ones are
+    radix-sorted); returns the previous value."""
+    return int(lib().gt_set_sample_sort_max(keys))
+
+
+def set_sample_sort_group(pairs: int) -> int:
+    """Testing hook: the largest group the sample sort sorts in LDS (larger
+    ones in device memory); returns the previous value."""
+    return int(lib().gt_set_sample_sort_group(pairs))
 
 
 def set_single_key_insert(enable: bool) -> bool:

@@ -104,6 +104,12 @@ template <class K>
 void sample_sort_from(const K* src, K* keys, uint32_t* idx, K* keys_alt, uint32_t* idx_alt, uint64_t n, void* tmp,
                       hipStream_t s, uint32_t* err, uint32_t err_bit, bool force_fail);
 
+// Testing hooks of the sample sort: the largest input it takes (larger ones are
+// radix-sorted) and the largest group it sorts in LDS (larger ones in device
+// memory); each returns the previous value.
+uint64_t set_sample_sort_max(uint64_t n);
+uint32_t set_sample_sort_group(uint32_t pairs);
+
 // Whether the testing hook makes a sort of n elements fail.
 bool sort_forced_to_fail(uint64_t n);
 

@@ -1050,12 +1050,12 @@ constexpr uint32_t kSsSmallCap = 2048, kSsMidCap = 4096, kSsLargeCap = 8192;
 // Group sort of (key, payload) pairs into kout, pout (which may be kin, pin).
 // `later`: the list of groups left to the large workgroups.  With TIE the
 // payload is the position, equal keys are ordered by it, and a failed sort is
-// replaced by a valid one.  Without TIE equal keys lie in one group (ties go
+// replaced by a valid one.  `cap`: the largest group to sort in LDS, for tests.  Without TIE equal keys lie in one group (ties go
 // by the key alone) and become neighbours: they set bit 0 of *refuse.
 template <class K, class P, bool TIE, int NT, uint32_t CAP>
 __global__ __launch_bounds__(NT) void k_ss_groups(const K* kin, const P* pin, const uint32_t* start, uint32_t segs,
                                                   uint32_t groups, const uint32_t* list, uint32_t* later, K* kout,
-                                                  P* pout, const uint32_t* fail, uint32_t* refuse) {
+                                                  P* pout, const uint32_t* fail, uint32_t* refuse, uint32_t cap) {
     __shared__ SsLds<K, TIE, NT, CAP> L;
     const uint32_t tid = threadIdx.x;
     if (ss_refused<TIE>(refuse)) return;
@@ -1073,7 +1073,7 @@ __global__ __launch_bounds__(NT) void k_ss_groups(const K* kin, const P* pin, co
                 return;
             }
         }
-        if (m > CAP) {
+        if (m > CAP || m > cap) {
             if (later) {
                 if (tid == 0) later[1 + atomicAdd(&later[0], 1u)] = x;
                 return;
@@ -1110,7 +1110,17 @@ __global__ __launch_bounds__(NT) void k_ss_groups(const K* kin, const P* pin, co
 
 // ------------------------------------------------------------- host side
 
-uint64_t sample_sort_max() { return kSsMax; }
+// Testing hooks: the largest input, the largest group sorted in LDS.
+static std::atomic<uint64_t> g_ss_max{kSsMax};
+static std::atomic<uint32_t> g_ss_group{kSsLargeCap};
+
+uint64_t set_sample_sort_max(uint64_t n) {
+    return g_ss_max.exchange(n < kSsMax ? n : kSsMax, std::memory_order_relaxed);
+}
+uint32_t set_sample_sort_group(uint32_t pairs) {
+    return g_ss_group.exchange(pairs < kSsLargeCap ? pairs : kSsLargeCap, std::memory_order_relaxed);
+}
+uint64_t sample_sort_max() { return g_ss_max.load(std::memory_order_relaxed); }
 
 // The sample's seed: another one for every sort (a captured one keeps its).
 static uint32_t ss_next_seed() {
@@ -1214,7 +1224,7 @@ static void ss_sort_groups(const SsPlan& pl, uint8_t* tmp, uint64_t n, const K* 
     auto groups = [&](auto NT, auto CAP, uint32_t grid, const uint32_t* from, uint32_t* later) {
         hipLaunchKernelGGL((k_ss_groups<K, P, TIE, decltype(NT)::value, decltype(CAP)::value>), dim3(grid),
                            dim3(decltype(NT)::value), 0, s, kin, pin, start, v.segs, v.groups, from, later, kout, pout,
-                           fail, refuse);
+                           fail, refuse, g_ss_group.load(std::memory_order_relaxed));
     };
     ss_launch_groups(groups, pl.levels, v.segs * v.groups, listed, list);
 }

@@ -314,6 +314,8 @@ const char* gt_status_str(gt_status s) {
 }
 
 uint32_t gt_set_sort_spin_limit(uint32_t limit) { return set_sort_spin_limit(limit); }
+uint64_t gt_set_sample_sort_max(uint64_t keys) { return set_sample_sort_max(keys); }
+uint32_t gt_set_sample_sort_group(uint32_t pairs) { return set_sample_sort_group(pairs); }
 int gt_set_single_key_insert(int enable) { return set_single_key_insert(enable); }
 int gt_set_one_launch_insert(int enable) { return set_one_launch_insert(enable); }
 int gt_set_one_launch_delete(int enable) { return set_one_launch_delete(enable); }
