@@ -204,8 +204,12 @@ def _stream(stream):
     if _raw_stream is None:
         torch = _torch()
         handle = torch.cuda.current_stream().cuda_stream  # initialises the device, or raises
-        raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-        _raw_stream = lambda: raw(device())  # noqa: E731
+        # (private to torch: where it has them no more, the public call)
+        raw, device = (getattr(torch._C, f, None) for f in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        if raw and device:
+            _raw_stream = lambda: raw(device())  # noqa: E731
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
         return handle
     return _raw_stream()
 
