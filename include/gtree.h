@@ -31,6 +31,8 @@
  *  - Results are written in caller order.  B = 0 is a no-op returning GT_OK.
  *  - Calls that modify a tree must be ordered on one stream by the caller;
  *    reads may run on several streams only while no write is in flight.
+ *  - An input must stay as it is until the call's work on `stream` is done:
+ *    what a call does with keys that change meanwhile is not defined.
  *
  * Ownership: the caller owns every input and output buffer and the arena.
  * The library places all tree state (header, node pools, a copy of the top
@@ -94,9 +96,10 @@ typedef struct {
                                  fanout - 1 for the static one; 0 = that     */
     float fill;               /* bulk-load fill in [0.5, 1]; default 1.0      */
     uint32_t lanes_per_query; /* lookup lanes per query: 4, 8 or 16; 0 = by
-                                 batch size (16 below 2^13 queries, else 8);
-                                 insert location uses 8 where it is 0, ranges
-                                 choose their own by batch size              */
+                                 batch size (16 below 2^13 queries, else 8).
+                                 Point lookups only: inserts and deletes
+                                 locate with 16 below 2^15 keys and 8 from
+                                 there on, ranges choose by batch size       */
     uint32_t lds_levels;      /* top inner levels read from an LDS copy: 1..3,
                                  4 = none; 0 = by batch size (none below 2^17
                                  queries, else 2; ranges and insert location
@@ -155,8 +158,8 @@ uint64_t tree_arena_bytes(const gt_params* p /*host*/, uint64_t n, uint64_t leaf
  * leaves are chained in key order.  n = 0 builds an empty tree.
  * This call synchronises `stream` before it returns.  On success *out
  * receives a new handle; GT_ERR_DEVICE if the device sort of the keys
- * failed (the keys changed while they were sorted, or, above 2^26 keys, a
- * bounded wait between its workgroups gave up: not expected).  The arena is
+ * failed (above 2^26 keys, a bounded wait between its workgroups gave up: not
+ * expected).  The arena is
  * not written before the keys are known to be good: a refused load leaves
  * what it holds, and keys and values may lie in it.
  */
@@ -192,8 +195,8 @@ gt_status tree_lookup_batch(gt_tree* t, const void* keys, uint64_t B, void* valu
  * workspaces.  B < 2^31.  Errors: GT_ERR_INVALID for null pointers, unknown
  * flags or B too large; GT_ERR_CAPACITY when workspace_bytes is too small.
  * Nothing is enqueued on an error.  No memory is allocated; the call is
- * graph-capturable.  Should the device sort of a batch above 2048 keys fail
- * (the keys changed while they were sorted: not expected) the tree's
+ * graph-capturable.  Should the device sort of a batch above 2^26 keys fail
+ * (a bounded wait between its workgroups gives up: not expected) the tree's
  * device error word gets the internal bit (tree_device_error: GT_ERR_DEVICE)
  * and the results are not valid.
  */
@@ -239,7 +242,7 @@ gt_status tree_lookup_levelwise_noalloc(gt_tree* t, const void* keys, uint64_t B
  * GT_DEVERR_CAPACITY, the tree is left unchanged and status_out is
  * unspecified.  A batch is not applied either while the word holds
  * GT_DEVERR_INTERNAL (set, for one, when the device sort of a batch above
- * 2048 keys fails because the keys changed meanwhile: not expected);
+ * 2^26 keys gives up a bounded wait between its workgroups: not expected);
  * tree_device_error clears the word.
  */
 gt_status tree_insert_batch(gt_tree* t, const void* keys, const void* values, uint64_t B,

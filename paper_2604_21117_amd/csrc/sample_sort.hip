@@ -38,9 +38,10 @@
 // 2.9 TB/s; about 300 vector instructions per 64 pairs are its other bound).
 //
 // No step waits on another workgroup.  A scatter that finds more pairs for a
-// group than were counted (the caller changed the input meanwhile) writes
-// only inside the group, marks the sort failed, and the result is replaced
-// by a valid sorted one, every key 0 and index i at position i.
+// group than were counted (the input changed, which no caller may do) writes
+// only inside the group and marks the sort failed; the result is then replaced
+// by a valid sorted one, every key 0 and index i at position i.  That keeps
+// such a sort's writes in bounds where it is noticed; it is no promise.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <atomic>
