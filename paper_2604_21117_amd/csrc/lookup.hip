@@ -576,11 +576,16 @@ static void launch_range_many_t(const TreeView<K>& t, const K* lo, const K* hi, 
 // leaves, 2^14 of two and 2^15 of one; what it has no idle lanes for is only
 // more to read: 1024 scans take four (see k_range), 4096 two (1 to 100 pairs
 // 5.4 us, four 5.1; 1 pair 3.95, four 4.4, the old 3.9), 8192 one (7.7 us,
-// the old 8.2; on a grown tree 9.8 and 11.0).  Above kRangeMany scans of
-// 64-bit keys 8 lanes per scan read as much at once: 32768 scans of 1 to 20
-// pairs 8.3 us, with 16 lanes 9.0; of 32-bit keys, whose lines are half as
-// long, 16 lanes stay ahead (1 to 100 pairs 12.6 us, 8 lanes 14.6).
-constexpr uint64_t kRangeFour = 1u << 11, kRangeTwo = 1u << 12, kRangeMany = 1u << 14;
+// the old 8.2; on a grown tree 9.8 and 11.0).  Above kRangeMany scans 8 lanes
+// per scan read as much at once and descend in half as many waves.  64-bit
+// keys, 16 lanes and 8: 10000 scans of 1 to 10 pairs 4.52 and 4.58 us, 16384
+// 5.05 and 4.86 (1 to 100 pairs 12.2 both).  32-bit keys, whose lines are half
+// as long: 20000 scans 4.85 and 4.99 us, 32768 6.45 and 6.17, 131072 of 2^18
+// keys 15.3 and 12.3 (1 to 100 pairs 11.2 and 12.3, 13.6 and 15.4, 33 and 37:
+// long scans would rather keep 16 lanes, but the call does not know them).
+constexpr uint64_t kRangeFour = 1u << 11, kRangeTwo = 1u << 12;
+template <class K>
+constexpr uint64_t kRangeMany = sizeof(K) == 8 ? 12288 : 24576;
 
 template <class K, int LV>
 static void launch_range_lv(const TreeView<K>& t, const K* lo, const K* hi, const uint32_t* mx, const uint64_t* off,
@@ -589,14 +594,10 @@ static void launch_range_lv(const TreeView<K>& t, const K* lo, const K* hi, cons
         launch_range_t<K, 4, LV>(t, lo, hi, mx, off, B, ok, ov, cnt, s);
     } else if (B <= kRangeTwo) {
         launch_range_t<K, 2, LV>(t, lo, hi, mx, off, B, ok, ov, cnt, s);
-    } else {
-        if constexpr (sizeof(K) == 8) {
-            if (B > kRangeMany) {
-                launch_range_many_t<K, LV>(t, lo, hi, mx, off, B, ok, ov, cnt, s);
-                return;
-            }
-        }
+    } else if (B <= kRangeMany<K>) {
         launch_range_t<K, 1, LV>(t, lo, hi, mx, off, B, ok, ov, cnt, s);
+    } else {
+        launch_range_many_t<K, LV>(t, lo, hi, mx, off, B, ok, ov, cnt, s);
     }
 }
 
