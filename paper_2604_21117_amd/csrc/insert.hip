@@ -457,6 +457,7 @@ __global__ __launch_bounds__(kBlk) void k_rank_locate(TreeView<K> t, Ins<K> v, c
         const bool present = slot < kSlots && !empty, first = same == 0;
         v.uk[u] = key[0];
         if constexpr (INS) v.uv[u] = val;
+        else v.upos[u] = n >> 16;  // the next key's place
         v.ufound[u] = present && first ? 1 : 0;
         v.uleaf[u] = leaf[0];
         v.ulc[u] = static_cast<uint8_t>(lcnt);
@@ -2388,6 +2389,7 @@ __device__ __forceinline__ void note_inner_write(const Ins<K>& v, int depth) {
     if (depth < kMirrorDepth) v.st->mirror_dirty = 1u;
 }
 constexpr uint64_t kDelListHere = 2048;   // up to here the leaf kernel lists the merges
+static_assert(kDelListHere == kSmallInsert, "its records are k_rank_locate's");
 constexpr uint64_t kDelListScan = 16384;  // above: the merge list comes from a scan, in key order
 
 // first distinct key of its leaf's run (keys are sorted, so a leaf's keys
@@ -2415,7 +2417,11 @@ __device__ __forceinline__ uint32_t row_or(uint32_t x) {
 // how many keys the wave removed.  The leaves left below half full are listed
 // for the merges: here (LIST, an atomic for the wave's four groups, in any
 // order) or, for larger batches, by the kernels after this one.
-template <class K, int R, bool LIST>
+// REP: k_rank_locate's records, of which a repeated key has one per occurrence
+// (only the first counts) and upos the place after its last one: a run goes on
+// from there, so that repeats are not walked (2048 times one key 39 us, 87
+// walked).
+template <class K, int R, bool LIST, bool REP>
 __device__ __forceinline__ uint32_t ph_del_leaf(TreeView<K> t, Ins<K> v) {
     if (t.hdr->error & kErrInternal) return 0;  // e.g. the batch's device sort gave up
     const uint64_t U = v.st->U;
@@ -2427,9 +2433,11 @@ __device__ __forceinline__ uint32_t ph_del_leaf(TreeView<K> t, Ins<K> v) {
         if (__ballot(ub < U) == 0) break;  // the wave's four groups are done
         uint32_t le[R], prev[R];  // key u + s: its leaf; the leaf of the key before u
         uint32_t rec[R];          // key u + s: found, and its slot
+        uint32_t next[R];         // the record after key u + 15 and its repeats
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const uint64_t u = ub + r * gs, e = u + static_cast<uint64_t>(s);
+            next[r] = REP && u + kSlots <= U ? v.upos[u + kSlots - 1] : 0u;
             const bool in = e < U;
             le[r] = in ? v.uleaf[e] : kNone;
             rec[r] = in ? (v.ufound[e] ? 0x100u : 0u) | v.uslot[e] : 0u;
@@ -2457,7 +2465,7 @@ __device__ __forceinline__ uint32_t ph_del_leaf(TreeView<K> t, Ins<K> v) {
             const uint64_t u = ub + r * gs;
             uint32_t gone = 0, nd = 0;
             {
-                uint32_t lx = le[r], rx = rec[r];
+                uint32_t lx = le[r], rx = rec[r], nx = next[r];
                 bool more = head[r];
                 for (uint64_t e0 = u; __ballot(more);) {
                     const bool in = more && lx == leaf[r];
@@ -2467,9 +2475,10 @@ __device__ __forceinline__ uint32_t ph_del_leaf(TreeView<K> t, Ins<K> v) {
                     nd += static_cast<uint32_t>(__popcll((__ballot(hit) >> gbase) & 0xFFFFull));
                     more = ((__ballot(in) >> gbase) & 0xFFFFull) == 0xFFFFull;  // else the run ended here
                     if (!__ballot(more)) break;
-                    e0 += kSlots;
+                    e0 = REP ? nx : e0 + kSlots;
                     const uint64_t e = e0 + static_cast<uint64_t>(s);
                     const bool ok = more && e < U;
+                    if (REP) nx = more && e0 + kSlots <= U ? v.upos[e0 + kSlots - 1] : 0u;
                     lx = ok ? v.uleaf[e] : kNone;
                     rx = ok ? (v.ufound[e] ? 0x100u : 0u) | v.uslot[e] : 0u;
                 }
@@ -2531,10 +2540,10 @@ __device__ __forceinline__ uint32_t ph_del_leaf(TreeView<K> t, Ins<K> v) {
 // buffer, at least a word per workgroup), which the commit adds up: one add a
 // wave to a single word took 12 ns each, 390 of this kernel's 394 us for 2^20
 // keys on 2^24 (88 now).
-template <class K, int R, bool LIST>
+template <class K, int R, bool LIST, bool REP>
 __global__ __launch_bounds__(kBlk) void k_del_leaf(TreeView<K> t, Ins<K> v, uint32_t* __restrict__ parts) {
     __shared__ uint32_t s_del[kBlk / 64];
-    const uint32_t del = ph_del_leaf<K, R, LIST>(t, v);
+    const uint32_t del = ph_del_leaf<K, R, LIST, REP>(t, v);
     if ((threadIdx.x & 63) == 0) s_del[threadIdx.x / 64] = del;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -2989,7 +2998,7 @@ __global__ __launch_bounds__(kDelOneBlock) void k_del_small(TreeView<K> t, Ins<K
     ph_locate<K, 16, 1, 2, kDelOneBlock>(t, v, status);
     phase_boundary();
     {
-        const uint32_t del = ph_del_leaf<K, 1, true>(t, v);
+        const uint32_t del = ph_del_leaf<K, 1, true, false>(t, v);
         if ((tid & 63) == 0 && del) atomicAdd(&v.st->deleted, del);
     }
     phase_boundary();
@@ -3057,11 +3066,11 @@ const uint32_t* launch_delete(const TreeView<K>& t, const InsertCtx& c, const K*
     const uint32_t gl = grid_for(B * kSlots, kBlk);
     uint32_t* parts = reinterpret_cast<uint32_t*>(v.sk2);
     if (B <= kDelListHere)
-        hipLaunchKernelGGL((k_del_leaf<K, 1, true>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
+        hipLaunchKernelGGL((k_del_leaf<K, 1, true, true>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
     else if (B >= 2ull * gl * (kBlk / kSlots))
-        hipLaunchKernelGGL((k_del_leaf<K, 2, false>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
+        hipLaunchKernelGGL((k_del_leaf<K, 2, false, false>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
     else
-        hipLaunchKernelGGL((k_del_leaf<K, 1, false>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
+        hipLaunchKernelGGL((k_del_leaf<K, 1, false, false>), dim3(gl), dim3(kBlk), 0, s, t, v, parts);
     const bool ordered = B > kDelListScan;
     if (ordered) {
         hipLaunchKernelGGL((k_ch_count<K, false>), dim3(cb.n), dim3(kChBlock), 0, s, t, v, cb.tiles, sums);
