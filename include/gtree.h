@@ -38,7 +38,8 @@
  * The library places all tree state (header, node pools, a copy of the top
  * tree levels, per-batch scratch) inside the arena and allocates no device
  * memory on the lookup, range or insert paths.  tree_build alone allocates
- * temporary sort buffers, released before it returns.  The arena must stay
+ * temporary sort buffers where they do not fit or may not lie in the arena,
+ * released before it returns.  The arena must stay
  * allocated until tree_destroy.
  */
 #ifndef GTREE_H
@@ -159,9 +160,10 @@ uint64_t tree_arena_bytes(const gt_params* p /*host*/, uint64_t n, uint64_t leaf
  * This call synchronises `stream` before it returns.  On success *out
  * receives a new handle; GT_ERR_DEVICE if the device sort of the keys
  * failed (above 2^26 keys, a bounded wait between its workgroups gave up: not
- * expected).  The arena is
- * not written before the keys are known to be good: a refused load leaves
- * what it holds, and keys and values may lie in it.
+ * expected).  Where a tree lies in the arena that tree_destroy has not ended,
+ * or the keys or values do, nothing is written to it before the keys are known
+ * to be good: a refused load leaves what it holds.  Else the keys are sorted
+ * inside it, and a refused load leaves its contents unspecified.
  */
 gt_status tree_build(const gt_params* p /*host*/, const void* keys, const void* values, uint64_t n,
                      void* arena, uint64_t arena_bytes, hipStream_t stream, gt_tree** out /*host*/);

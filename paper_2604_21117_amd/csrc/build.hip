@@ -139,7 +139,8 @@ void launch_build(const TreeView<K>& t, const K* sk, const K* sv, uint64_t n, co
     for (int i = 0; i < levels; ++i) maxsz = level_sizes[i] > maxsz ? level_sizes[i] : maxsz;
     K* cur = maxbuf;
     K* nxt = maxbuf + maxsz;
-    hipLaunchKernelGGL(k_build_leaves<K>, dim3(grid1d(L * kSlots, 256)), dim3(256), 0, s, t, sk, sv, n, L, cur);
+    if (sk || n == 0)
+        hipLaunchKernelGGL(k_build_leaves<K>, dim3(grid1d(L * kSlots, 256)), dim3(256), 0, s, t, sk, sv, n, L, cur);
     // inner ids top-down: level i (i >= 1 above the leaves) starts after all
     // levels above it
     uint64_t base[kMaxLevels + 1] = {0};

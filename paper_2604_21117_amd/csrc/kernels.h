@@ -33,20 +33,24 @@ void launch_range(const TreeView<K>& t, const LaunchCfg& cfg, const K* lo, const
 // Bulk build from sorted distinct keys (sk, sv): writes leaves, inner levels,
 // header and mirror.  level_sizes[0] = leaves, level_sizes[i] = nodes of the
 // i-th inner level above the leaves; `levels` entries, the last being 1.
-// maxbuf needs room for max(level_sizes) keys, twice.
+// maxbuf needs room for max(level_sizes) keys, twice.  With sk null and n > 0
+// the leaves are written already and maxbuf holds their largest keys.
 template <class K>
 void launch_build(const TreeView<K>& t, const K* sk, const K* sv, uint64_t n, const uint64_t* level_sizes,
                   int levels, K* maxbuf, hipStream_t s);
 
-// Sample sort of n (key, value) pairs by key, 1 <= n <= sample_sort_max():
-// *sk, *sv receive the buffers that hold the sorted pairs.  ka, va and, where
-// sort_pairs_two_buffers(n), kb, vb are buffers of n entries; tmp holds
-// sample_sort_tmp_bytes.  *refuse (0 before) gets bit 0 when a key occurs
-// twice and fail_bit when the sort failed; the pairs are then not valid.
+// Sample sort of n (key, value) pairs by key, 1 <= n <= sample_sort_max(),
+// straight into `leaves` leaves (evenly, as launch_build packs them) at lkeys,
+// lvals, lmeta; maxk receives each leaf's largest key.  ka, va and, where
+// sort_leaves_two_buffers(n), kb, vb are buffers of n entries, of which with
+// two the first may lie in the leaves; tmp holds sample_sort_tmp_bytes.
+// *refuse (0 before) gets bit 0 when a key occurs twice and fail_bit when the
+// sort failed; the leaves are then not valid.
 template <class K>
-void launch_sort_pairs(const K* keys, const K* vals, uint64_t n, K* ka, K* va, K* kb, K* vb, void* tmp,
-                       uint32_t* refuse, uint32_t fail_bit, bool force_fail, hipStream_t s, K** sk, K** sv);
-bool sort_pairs_two_buffers(uint64_t n);
+void launch_sort_leaves(const K* keys, const K* vals, uint64_t n, uint64_t leaves, K* ka, K* va, K* kb, K* vb,
+                        void* tmp, K* lkeys, K* lvals, uint2* lmeta, K* maxk, uint32_t* refuse, uint32_t fail_bit,
+                        bool force_fail, hipStream_t s);
+bool sort_leaves_two_buffers(uint64_t n);
 
 template <class K>
 void launch_gather(const K* src, const uint32_t* idx, K* dst, uint64_t n, hipStream_t s);

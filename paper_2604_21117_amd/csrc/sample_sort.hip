@@ -1,5 +1,5 @@
 // Sample sort of (key, payload) pairs: the library's sort above 8192 keys (up to
-// there keys are ranked by counting).
+// there keys are ranked by counting), of bulk loads straight into leaves.
 //
 // A pass of radix sort moves every pair once per eight key bits (eight
 // passes for 64-bit keys).  A sample sort moves a pair twice however wide
@@ -1048,31 +1048,24 @@ __device__ __forceinline__ void ss_each_group(const uint32_t* __restrict__ start
 constexpr int kSsSmallThreads = 256, kSsMidThreads = 512, kSsLargeThreads = 1024;
 constexpr uint32_t kSsSmallCap = 2048, kSsMidCap = 4096, kSsLargeCap = 8192;
 
-// Group sort of (key, payload) pairs into kout, pout (which may be kin, pin).
-// `later`: the list of groups left to the large workgroups.  With TIE the
-// payload is the position, equal keys are ordered by it, and a failed sort is
-// replaced by a valid one.  `cap`: the largest group to sort in LDS, for tests.  Without TIE equal keys lie in one group (ties go
-// by the key alone) and become neighbours: they set bit 0 of *refuse.
-template <class K, class P, bool TIE, int NT, uint32_t CAP>
-__global__ __launch_bounds__(NT) void k_ss_groups(const K* kin, const P* pin, const uint32_t* start, uint32_t segs,
-                                                  uint32_t groups, const uint32_t* list, uint32_t* later, K* kout,
-                                                  P* pout, const uint32_t* fail, uint32_t* refuse, uint32_t cap) {
-    __shared__ SsLds<K, TIE, NT, CAP> L;
+// Group sort of (key, position) pairs into kout, iout (which may be kin, pin).
+// `later`: the list of groups left to the large workgroups.  `cap`: the
+// largest group to sort in LDS, for tests.
+template <class K, int NT, uint32_t CAP>
+__global__ __launch_bounds__(NT) void k_ss_groups(const K* kin, const uint32_t* pin, const uint32_t* start,
+                                                  uint32_t segs, uint32_t groups, const uint32_t* list,
+                                                  uint32_t* later, K* kout, uint32_t* iout, const uint32_t* fail,
+                                                  uint32_t cap) {
+    __shared__ SsLds<K, true, NT, CAP> L;
     const uint32_t tid = threadIdx.x;
-    if (ss_refused<TIE>(refuse)) return;
     const bool failed = *fail != 0;
-    auto twin = [&](const K* k, uint32_t i) {
-        if (!TIE && i > 0 && k[i - 1] == k[i]) atomicOr(refuse, 1u);
-    };
     ss_each_group(start, segs, groups, list, [&](uint32_t x, uint32_t b, uint32_t m) {
-        if constexpr (TIE) {
-            if (failed) {
-                for (uint32_t i = tid; i < m; i += NT) {
-                    kout[b + i] = K(0);
-                    pout[b + i] = b + i;
-                }
-                return;
+        if (failed) {  // replaced by a valid result
+            for (uint32_t i = tid; i < m; i += NT) {
+                kout[b + i] = K(0);
+                iout[b + i] = b + i;
             }
+            return;
         }
         if (m > CAP || m > cap) {
             if (later) {
@@ -1082,30 +1075,102 @@ __global__ __launch_bounds__(NT) void k_ss_groups(const K* kin, const P* pin, co
             if (kin != kout) {
                 for (uint32_t i = tid; i < m; i += NT) {
                     kout[b + i] = kin[b + i];
-                    pout[b + i] = pin[b + i];
+                    iout[b + i] = pin[b + i];
                 }
                 __syncthreads();
             }
-            ss_bitonic<TIE>(kout + b, pout + b, m);
-            for (uint32_t i = tid; i < m; i += NT) twin(kout + b, i);
+            ss_bitonic<true>(kout + b, iout + b, m);
             return;
         }
-        P p[CAP / NT];
-        uint32_t f[CAP / NT];
-        ss_sort_group<K, P, TIE, NT, CAP>(kin, pin, b, m, L, p, f);
+        uint32_t p[CAP / NT], f[CAP / NT];
+        ss_sort_group<K, uint32_t, true, NT, CAP>(kin, pin, b, m, L, p, f);
         for (uint32_t i = tid; i < m; i += NT) {
             kout[b + i] = L.k[i];
-            if constexpr (TIE) pout[b + i] = L.p[i];
-            else twin(L.k, i);
+            iout[b + i] = L.p[i];
         }
-        if constexpr (!TIE) {  // the payloads take the keys' place
-            __syncthreads();
+    });
+}
+
+// Where the pair of rank r goes when n pairs fill L leaves evenly (leaf j
+// holds [j n / L, (j + 1) n / L)).  Where every leaf holds `each` pairs a
+// multiplication by inv = ceil(2^32 / each) divides exactly (r < 2^26 is off
+// by less than 2^-6, a sixteenth is the smallest step).  Else in FP64: n and L
+// are at most 2^26, so the products are exact, and a quotient that is no whole
+// number is further from one (2^-26) than its rounding error (2^-27).
+struct LeafSlot {
+    uint32_t leaf, first, end;  // the leaf and its range of ranks
+};
+
+__device__ __forceinline__ LeafSlot leaf_slot(uint32_t r, uint32_t n, uint32_t L, uint32_t each, uint32_t inv) {
+    LeafSlot s;
+    if (each) {
+        s.leaf = each == 1 ? r : __umulhi(r, inv);
+        s.first = s.leaf * each;
+        s.end = s.first + each;
+        return s;
+    }
+    const double dn = n, dl = L;
+    s.leaf = static_cast<uint32_t>(ceil((static_cast<double>(r) + 1.0) * dl / dn)) - 1u;
+    s.first = static_cast<uint32_t>(floor(static_cast<double>(s.leaf) * dn / dl));
+    s.end = static_cast<uint32_t>(floor((static_cast<double>(s.leaf) + 1.0) * dn / dl));
+    return s;
+}
+
+// Group sort of (key, value) pairs straight into leaves: a pair's rank names
+// its leaf and slot, so the sorted pairs are not written and read back.  The
+// first pair of a leaf writes its count and link, the last its padding and its
+// bound (maxk).  Equal keys lie in one group (ties go by the key alone here)
+// and become neighbours: they set bit 0 of *refuse.
+template <class K, int NT, uint32_t CAP>
+__global__ __launch_bounds__(NT) void k_ss_leaves(K* kin, K* vin, const uint32_t* start, uint32_t segs,
+                                                  uint32_t groups, const uint32_t* list, uint32_t* later, K* lkeys,
+                                                  K* lvals, uint2* lmeta, uint32_t n, uint32_t nl, uint32_t each,
+                                                  K* maxk, uint32_t* refuse, uint32_t cap) {
+    __shared__ SsLds<K, false, NT, CAP> L;
+    const uint32_t tid = threadIdx.x;
+    if (ss_refused<false>(refuse)) return;
+    const uint32_t inv = each > 1 ? static_cast<uint32_t>(((1ull << 32) + each - 1) / each) : 0u;
+    auto key_out = [&](uint32_t r, K key, bool twin) {
+        const LeafSlot s = leaf_slot(r, n, nl, each, inv);
+        const uint64_t line = static_cast<uint64_t>(s.leaf) * kSlots;
+        lkeys[line + (r - s.first)] = key;
+        if (twin) atomicOr(refuse, 1u);
+        if (r == s.first) lmeta[s.leaf] = make_uint2(s.end - s.first, s.leaf + 1 < nl ? s.leaf + 1 : kNone);
+        if (r + 1 == s.end) {
+            maxk[s.leaf] = key;
+            for (uint32_t x = s.end - s.first; x < static_cast<uint32_t>(kSlots); ++x) lkeys[line + x] = key;
+        }
+    };
+    auto value_out = [&](uint32_t r, K val) {
+        const LeafSlot s = leaf_slot(r, n, nl, each, inv);
+        const uint64_t line = static_cast<uint64_t>(s.leaf) * kSlots;
+        lvals[line + (r - s.first)] = val;
+        if (r + 1 == s.end)
+            for (uint32_t x = s.end - s.first; x < static_cast<uint32_t>(kSlots); ++x) lvals[line + x] = kmax<K>();
+    };
+    ss_each_group(start, segs, groups, list, [&](uint32_t x, uint32_t b, uint32_t m) {
+        if (m > CAP || m > cap) {
+            if (later) {
+                if (tid == 0) later[1 + atomicAdd(&later[0], 1u)] = x;
+                return;
+            }
+            ss_bitonic<false>(kin + b, vin + b, m);
+            for (uint32_t i = tid; i < m; i += NT) {
+                key_out(b + i, kin[b + i], i > 0 && kin[b + i - 1] == kin[b + i]);
+                value_out(b + i, vin[b + i]);
+            }
+            return;
+        }
+        K v[CAP / NT];
+        uint32_t f[CAP / NT];
+        ss_sort_group<K, K, false, NT, CAP>(kin, vin, b, m, L, v, f);
+        for (uint32_t i = tid; i < m; i += NT) key_out(b + i, L.k[i], i > 0 && L.k[i - 1] == L.k[i]);
+        __syncthreads();  // the values take the keys' place
 #pragma unroll
-            for (uint32_t e = 0; e < CAP / NT; ++e)
-                if (e * NT + tid < m) L.k[f[e]] = p[e];
-            __syncthreads();
-            for (uint32_t i = tid; i < m; i += NT) pout[b + i] = L.k[i];
-        }
+        for (uint32_t e = 0; e < CAP / NT; ++e)
+            if (e * NT + tid < m) L.k[f[e]] = v[e];
+        __syncthreads();
+        for (uint32_t i = tid; i < m; i += NT) value_out(b + i, L.k[i]);
     });
 }
 
@@ -1130,7 +1195,7 @@ static uint32_t ss_next_seed() {
     return next.fetch_add(0x9E3779B9u, std::memory_order_relaxed);
 }
 
-bool sort_pairs_two_buffers(uint64_t n) { return n > kSsOneLevel; }
+bool sort_leaves_two_buffers(uint64_t n) { return n > kSsOneLevel; }
 uint64_t sample_sort_tmp_bytes(uint64_t n, int key_bytes) { return ss_plan(n, key_bytes).bytes; }
 
 // Sample, count and scatter of every level.  The pairs end in the buffers
@@ -1213,54 +1278,60 @@ static void ss_launch_groups(F&& groups, int levels, uint32_t total, bool listed
                list, nullptr);
 }
 
-// The group sorts into kout, pout of what ss_partition left in kin, pin.
-template <class K, class P, bool TIE>
-static void ss_sort_groups(const SsPlan& pl, uint8_t* tmp, uint64_t n, const K* kin, const P* pin, K* kout, P* pout,
-                           uint32_t* refuse, hipStream_t s) {
-    const SsLevel& v = pl.lv[pl.levels - 1];
-    const uint32_t* fail = reinterpret_cast<const uint32_t*>(tmp + pl.o_fail);
-    uint32_t* list = reinterpret_cast<uint32_t*>(tmp + pl.o_list);
-    const uint32_t* start = reinterpret_cast<const uint32_t*>(tmp + v.o_start);
-    const bool listed = n > kSsSmallMean * kSsMaxGroups;
-    auto groups = [&](auto NT, auto CAP, uint32_t grid, const uint32_t* from, uint32_t* later) {
-        hipLaunchKernelGGL((k_ss_groups<K, P, TIE, decltype(NT)::value, decltype(CAP)::value>), dim3(grid),
-                           dim3(decltype(NT)::value), 0, s, kin, pin, start, v.segs, v.groups, from, later, kout, pout,
-                           fail, refuse, g_ss_group.load(std::memory_order_relaxed));
-    };
-    ss_launch_groups(groups, pl.levels, v.segs * v.groups, listed, list);
-}
-
 template <class K>
 void sample_sort_from(const K* src, K* keys, uint32_t* idx, K* keys_alt, uint32_t* idx_alt, uint64_t n, void* tmp,
                       hipStream_t s, uint32_t* err, uint32_t err_bit, bool force_fail) {
     const SsPlan pl = ss_plan(n, sizeof(K));
     uint8_t* b = reinterpret_cast<uint8_t*>(tmp);
+    const SsLevel& v = pl.lv[pl.levels - 1];
+    uint32_t* fail = reinterpret_cast<uint32_t*>(b + pl.o_fail);
+    uint32_t* list = reinterpret_cast<uint32_t*>(b + pl.o_list);
+    const uint32_t* start = reinterpret_cast<const uint32_t*>(b + v.o_start);
+    const uint32_t cap = g_ss_group.load(std::memory_order_relaxed);
     K* kr;
     uint32_t* pr;
     ss_partition<K, uint32_t, true>(pl, b, src, nullptr, static_cast<uint32_t>(n), keys_alt, idx_alt, keys, idx,
                                     force_fail ? 1u : 0u, err, err_bit, nullptr, &kr, &pr, s);
-    ss_sort_groups<K, uint32_t, true>(pl, b, n, kr, pr, keys, idx, nullptr, s);
+    auto groups = [&](auto NT, auto CAP, uint32_t grid, const uint32_t* from, uint32_t* later) {
+        hipLaunchKernelGGL((k_ss_groups<K, decltype(NT)::value, decltype(CAP)::value>), dim3(grid),
+                           dim3(decltype(NT)::value), 0, s, kr, pr, start, v.segs, v.groups, from, later, keys, idx,
+                           fail, cap);
+    };
+    ss_launch_groups(groups, pl.levels, v.segs * v.groups, n > kSsSmallMean * kSsMaxGroups, list);
 }
 
 template <class K>
-void launch_sort_pairs(const K* keys, const K* vals, uint64_t n, K* ka, K* va, K* kb, K* vb, void* tmp,
-                       uint32_t* refuse, uint32_t fail_bit, bool force_fail, hipStream_t s, K** sk, K** sv) {
-    const SsPlan pl = ss_plan(n, sizeof(K));
+void launch_sort_leaves(const K* keys, const K* vals, uint64_t n64, uint64_t leaves, K* ka, K* va, K* kb, K* vb,
+                        void* tmp, K* lkeys, K* lvals, uint2* lmeta, K* maxk, uint32_t* refuse, uint32_t fail_bit,
+                        bool force_fail, hipStream_t s) {
+    const SsPlan pl = ss_plan(n64, sizeof(K));
     uint8_t* b = reinterpret_cast<uint8_t*>(tmp);
-    ss_partition<K, K, false>(pl, b, keys, vals, static_cast<uint32_t>(n), ka, va, kb, vb, force_fail ? 1u : 0u,
-                              refuse, fail_bit, refuse, sk, sv, s);
-    ss_sort_groups<K, K, false>(pl, b, n, *sk, *sv, *sk, *sv, refuse, s);
+    const uint32_t n = static_cast<uint32_t>(n64), nl = static_cast<uint32_t>(leaves);
+    const SsLevel& v = pl.lv[pl.levels - 1];
+    const uint32_t each = n % nl == 0 ? n / nl : 0u;
+    uint32_t* list = reinterpret_cast<uint32_t*>(b + pl.o_list);
+    const uint32_t* start = reinterpret_cast<const uint32_t*>(b + v.o_start);
+    const uint32_t cap = g_ss_group.load(std::memory_order_relaxed);
+    K *kr, *vr;
+    ss_partition<K, K, false>(pl, b, keys, vals, n, ka, va, kb, vb, force_fail ? 1u : 0u, refuse, fail_bit, refuse,
+                              &kr, &vr, s);
+    auto groups = [&](auto NT, auto CAP, uint32_t grid, const uint32_t* from, uint32_t* later) {
+        hipLaunchKernelGGL((k_ss_leaves<K, decltype(NT)::value, decltype(CAP)::value>), dim3(grid),
+                           dim3(decltype(NT)::value), 0, s, kr, vr, start, v.segs, v.groups, from, later, lkeys, lvals,
+                           lmeta, n, nl, each, maxk, refuse, cap);
+    };
+    ss_launch_groups(groups, pl.levels, v.segs * v.groups, n64 > kSsSmallMean * kSsMaxGroups, list);
 }
 
 template void sample_sort_from<uint32_t>(const uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint32_t*, uint64_t, void*,
                                          hipStream_t, uint32_t*, uint32_t, bool);
 template void sample_sort_from<uint64_t>(const uint64_t*, uint64_t*, uint32_t*, uint64_t*, uint32_t*, uint64_t, void*,
                                          hipStream_t, uint32_t*, uint32_t, bool);
-template void launch_sort_pairs<uint32_t>(const uint32_t*, const uint32_t*, uint64_t, uint32_t*, uint32_t*, uint32_t*,
-                                          uint32_t*, void*, uint32_t*, uint32_t, bool, hipStream_t, uint32_t**,
-                                          uint32_t**);
-template void launch_sort_pairs<uint64_t>(const uint64_t*, const uint64_t*, uint64_t, uint64_t*, uint64_t*, uint64_t*,
-                                          uint64_t*, void*, uint32_t*, uint32_t, bool, hipStream_t, uint64_t**,
-                                          uint64_t**);
+template void launch_sort_leaves<uint32_t>(const uint32_t*, const uint32_t*, uint64_t, uint64_t, uint32_t*, uint32_t*,
+                                           uint32_t*, uint32_t*, void*, uint32_t*, uint32_t*, uint2*, uint32_t*,
+                                           uint32_t*, uint32_t, bool, hipStream_t);
+template void launch_sort_leaves<uint64_t>(const uint64_t*, const uint64_t*, uint64_t, uint64_t, uint64_t*, uint64_t*,
+                                           uint64_t*, uint64_t*, void*, uint64_t*, uint64_t*, uint2*, uint64_t*,
+                                           uint32_t*, uint32_t, bool, hipStream_t);
 
 }  // namespace gt

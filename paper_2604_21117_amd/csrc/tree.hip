@@ -10,6 +10,7 @@
 #include <stdint.h>
 #include <string.h>
 #include <cstddef>
+#include <mutex>
 #include <vector>
 #include <algorithm>
 
@@ -137,12 +138,40 @@ uint64_t bytes_for_leaf_cap(int kb, uint64_t max_batch, uint64_t leaf_cap) {
         if ((x) != hipSuccess) return GT_ERR_HIP;   \
     } while (0)
 
-// Bulk load into the tree's arena.  The pairs are sorted in allocated memory
-// and nothing is written to the arena before the keys are known to be good:
-// it may hold a tree that a refused load has to leave as it is, and the
-// caller's keys and values.
+bool overlap(const void* a, uint64_t na, const void* b, uint64_t nb) {
+    const uint64_t x = reinterpret_cast<uint64_t>(a), y = reinterpret_cast<uint64_t>(b);
+    return x < y + nb && y < x + na;
+}
+
+// The handles that tree_build gave out and tree_destroy has not taken back: a
+// load into memory that one of them covers must not touch it before its keys
+// are known to be good.
+std::mutex g_live_lock;
+std::vector<const gt_tree*> g_live;
+
+void live_add(const gt_tree* t) {
+    std::lock_guard<std::mutex> hold(g_live_lock);
+    g_live.push_back(t);
+}
+
+void live_remove(const gt_tree* t) {
+    std::lock_guard<std::mutex> hold(g_live_lock);
+    g_live.erase(std::remove(g_live.begin(), g_live.end(), t), g_live.end());
+}
+
+bool arena_free(const void* arena, uint64_t bytes) {
+    std::lock_guard<std::mutex> hold(g_live_lock);
+    for (const gt_tree* t : g_live)
+        if (overlap(arena, bytes, t->arena, t->arena_bytes)) return false;
+    return true;
+}
+
+// Bulk load into the tree's arena.  `own`: the arena holds nothing that has to
+// survive an error, and not the keys or values, so the sort's buffers may lie
+// in it; else nothing is written to it before the keys are
+// known to be good.
 template <class K>
-gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, hipStream_t s) {
+gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, bool own, hipStream_t s) {
     const double fill = fill_of(&t->p);
     std::vector<uint64_t> sizes = level_sizes_for(n, fill);
     if (sizes.size() > static_cast<size_t>(kMaxLevels)) return GT_ERR_CAPACITY;
@@ -154,22 +183,41 @@ gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, 
 
     // temporary buffers: the sort's pairs and scratch, per-level maxima,
     // duplicate flag.  Above kRankSortTop keys, up to sample_sort_max(), the
-    // sample sort moves (key, value) pairs; else (key, index) pairs are sorted
-    // and the values gathered (one key 52 us a load, 59 by the sample sort).
+    // sample sort writes the leaves; else (key, index) pairs are sorted, the
+    // values gathered and the leaves written from them (one key 47 us a load,
+    // 59 by the sample sort).
     const uint64_t nn = n ? n : 1;
-    const bool moved = n > kRankSortTop && n <= sample_sort_max();
+    const bool direct = n > kRankSortTop && n <= sample_sort_max();
     uint64_t maxsz = 0;
     for (uint64_t v : sizes) maxsz = std::max(maxsz, v);
     const uint64_t b_keys = align_up(nn * sizeof(K)), b_idx = align_up(nn * 4);
-    const uint64_t b_sort = align_up(moved ? sample_sort_tmp_bytes(nn, sizeof(K)) : sort_tmp_bytes(nn, sizeof(K)));
+    const uint64_t b_sort = align_up(direct ? sample_sort_tmp_bytes(nn, sizeof(K)) : sort_tmp_bytes(nn, sizeof(K)));
     const uint64_t b_max = align_up(2 * maxsz * sizeof(K));
-    const bool two = moved && sort_pairs_two_buffers(n);
-    const uint64_t b_pairs = moved ? (two ? 4 : 2) * b_keys : 3 * b_keys + 2 * b_idx;
+    const uint64_t b_small = b_sort + b_max + kAlign;  // read while the inner levels are written
+    const uint64_t b_pairs = direct ? 2 * b_keys : 3 * b_keys + 2 * b_idx;
+    // The sample sort's leaves, and the first of its two pair buffers, which is
+    // free again before they are written: the tree's own, or a copy of them.
+    // The other buffers lie in the insert scratch and the inner pool (written
+    // last) where they fit and may: a load of 2^24 keys allocated 512 MB, and
+    // freed memory is cleared in the background, at which the next allocation
+    // waits: loads one after the other took 1.1 ms each or, mostly, 15.
+    const uint64_t b_leaf = align_up(sizes[0] * kSlots * sizeof(K)), b_meta = align_up(sizes[0] * 8);
+    const uint64_t b_leaves = direct && !own ? 2 * b_leaf + b_meta : 0;
+    const bool small_in = own && b_small <= t->scratch_bytes;
+    uint8_t* const room = t->scratch + (small_in ? b_small : 0);
+    const bool pairs_in = own && static_cast<uint64_t>(reinterpret_cast<uint8_t*>(t->lkeys) - room) >= b_pairs;
     uint8_t* tmp = nullptr;
-    HIP_TRY(hipMalloc(&tmp, b_pairs + b_sort + b_max + kAlign));
-    void* stmp = tmp + b_pairs;
-    K* maxbuf = reinterpret_cast<K*>(tmp + b_pairs + b_sort);
-    uint32_t* dflag = reinterpret_cast<uint32_t*>(tmp + b_pairs + b_sort + b_max);
+    const uint64_t total = (pairs_in ? 0 : b_pairs) + b_leaves + (small_in ? 0 : b_small);
+    if (total) HIP_TRY(hipMalloc(&tmp, total));
+    uint8_t* const pairs = pairs_in ? room : tmp;
+    uint8_t* const copy = tmp + (pairs_in ? 0 : b_pairs);
+    uint8_t* const small = small_in ? t->scratch : copy + b_leaves;
+    void* stmp = small;
+    K* maxbuf = reinterpret_cast<K*>(small + b_sort);
+    uint32_t* dflag = reinterpret_cast<uint32_t*>(small + b_sort + b_max);
+    K* const lk = reinterpret_cast<K*>(b_leaves ? copy : t->lkeys);
+    K* const lv = reinterpret_cast<K*>(b_leaves ? copy + b_leaf : t->lvals);
+    uint2* const lm = b_leaves ? reinterpret_cast<uint2*>(copy + 2 * b_leaf) : t->lmeta;
     K* sk = nullptr;
     K* sv = nullptr;
 
@@ -178,18 +226,18 @@ gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, 
     do {
         if (hipMemsetAsync(dflag, 0, 4, s) != hipSuccess) { st = GT_ERR_HIP; break; }
         // flag bit 0: a key occurs twice, bit 1: the sort gave up
-        K* const k0 = reinterpret_cast<K*>(tmp);
-        K* const k1 = reinterpret_cast<K*>(tmp + b_keys);
-        if (n && moved) {
-            K* const k2 = two ? reinterpret_cast<K*>(tmp + 2 * b_keys) : nullptr;
-            K* const k3 = two ? reinterpret_cast<K*>(tmp + 3 * b_keys) : nullptr;
-            launch_sort_pairs<K>(reinterpret_cast<const K*>(keys), reinterpret_cast<const K*>(values), n, k0, k1, k2, k3,
-                                 stmp, dflag, 2u, sort_forced_to_fail(n), s, &sk, &sv);
+        K* const k0 = reinterpret_cast<K*>(pairs);
+        K* const k1 = reinterpret_cast<K*>(pairs + b_keys);
+        if (n && direct) {
+            const bool two = sort_leaves_two_buffers(n);
+            launch_sort_leaves<K>(reinterpret_cast<const K*>(keys), reinterpret_cast<const K*>(values), n, sizes[0],
+                                  two ? lk : k0, two ? lv : k1, k0, k1, stmp, lk, lv, lm, maxbuf, dflag, 2u,
+                                  sort_forced_to_fail(n), s);
         } else if (n) {
             sk = k0;
-            sv = reinterpret_cast<K*>(tmp + 2 * b_keys);
-            uint32_t* si = reinterpret_cast<uint32_t*>(tmp + 3 * b_keys);
-            uint32_t* si2 = reinterpret_cast<uint32_t*>(tmp + 3 * b_keys + b_idx);
+            sv = reinterpret_cast<K*>(pairs + 2 * b_keys);
+            uint32_t* si = reinterpret_cast<uint32_t*>(pairs + 3 * b_keys);
+            uint32_t* si2 = reinterpret_cast<uint32_t*>(pairs + 3 * b_keys + b_idx);
             // (key, position) pairs sorted by key; positions come from the sort
             sort_from<K>(reinterpret_cast<const K*>(keys), sk, si, k1, si2, n, stmp, s, dflag, 2u);
             launch_gather<K>(reinterpret_cast<const K*>(values), si, sv, n, s);
@@ -203,13 +251,19 @@ gt_status build_t(gt_tree* t, const void* keys, const void* values, uint64_t n, 
         if (hflag & 2u) { st = GT_ERR_DEVICE; break; }  // the sort gave up
         if (hflag) { st = GT_ERR_DUPLICATE; break; }
         TreeView<K> v = view<K>(t);
+        if (b_leaves && (hipMemcpyAsync(v.lkeys, lk, sizes[0] * kSlots * sizeof(K), hipMemcpyDeviceToDevice, s) != hipSuccess ||
+                         hipMemcpyAsync(v.lvals, lv, sizes[0] * kSlots * sizeof(K), hipMemcpyDeviceToDevice, s) != hipSuccess ||
+                         hipMemcpyAsync(v.lmeta, lm, sizes[0] * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)) {
+            st = GT_ERR_HIP;
+            break;
+        }
         launch_build<K>(v, sk, sv, n, sizes.data(), static_cast<int>(sizes.size()), maxbuf, s);
         if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) st = GT_ERR_HIP;
         t->h_bound = static_cast<uint32_t>(sizes.size());
         t->cfg.loaded_leaves = sizes[0];
     } while (0);
     hipStreamSynchronize(s);
-    hipFree(tmp);
+    if (tmp) hipFree(tmp);
     return st;
 }
 
@@ -240,7 +294,7 @@ gt_status delete_rebuild_t(gt_tree* t, hipStream_t s) {
             break;
         }
         if (got != n) { st = GT_ERR_DEVICE; break; }
-        st = build_t<K>(t, ok, ov, n, s);
+        st = build_t<K>(t, ok, ov, n, false, s);  // the arena still holds the tree
         if (st != GT_OK) break;
         const uint32_t keep[2] = {h.error, h.epoch + 1};  // DevHeader: error, then epoch
         static_assert(offsetof(DevHeader, epoch) == offsetof(DevHeader, error) + 4, "header layout");
@@ -341,6 +395,7 @@ gt_status tree_build(const gt_params* p, const void* keys, const void* values, u
         t->arena_bytes = w->arena_bytes;
         t->h_bound = w->height;
         t->wide = w;
+        live_add(t);
         *out = t;
         return GT_OK;
     }
@@ -370,12 +425,15 @@ gt_status tree_build(const gt_params* p, const void* keys, const void* values, u
     // lookup shape fields the caller left at 0 follow the batch size
     t->cfg.shape_auto = (p->lanes_per_query ? 0 : 1) | (p->queries_per_group ? 0 : 2) | (p->lds_levels ? 0 : 4);
     layout(t, reinterpret_cast<uint8_t*>(arena), lo);
-    gt_status st = kb == 8 ? build_t<uint64_t>(t, keys, values, n, stream)
-                           : build_t<uint32_t>(t, keys, values, n, stream);
+    const bool own = arena_free(t->arena, t->arena_bytes) && !overlap(t->arena, t->arena_bytes, keys, n * kb) &&
+                     !overlap(t->arena, t->arena_bytes, values, n * kb);
+    gt_status st = kb == 8 ? build_t<uint64_t>(t, keys, values, n, own, stream)
+                           : build_t<uint32_t>(t, keys, values, n, own, stream);
     if (st != GT_OK) {
         delete t;
         return st;
     }
+    live_add(t);
     *out = t;
     return GT_OK;
 }
@@ -556,6 +614,7 @@ gt_status tree_insert_batch(gt_tree* t, const void* keys, const void* values, ui
 
 gt_status tree_destroy(gt_tree* t) {
     if (!t) return GT_ERR_INVALID;
+    live_remove(t);
     if (t->h_flag) hipHostFree(t->h_flag);
     delete t->wide;
     delete t;
