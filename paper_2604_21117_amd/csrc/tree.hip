@@ -147,7 +147,7 @@ bool overlap(const void* a, uint64_t na, const void* b, uint64_t nb) {
 // load into memory that one of them covers must not touch it before its keys
 // are known to be good.
 std::mutex g_live_lock;
-std::vector<const gt_tree*> g_live;
+std::vector<const gt_tree*>& g_live = *new std::vector<const gt_tree*>;  // outlives every handle
 
 void live_add(const gt_tree* t) {
     std::lock_guard<std::mutex> hold(g_live_lock);
