@@ -18,6 +18,7 @@ def lookup_us(t, q, levelwise=False):
     v = torch.empty(len(q), dtype=t.tdtype, device="cuda")
     f = torch.empty(len(q), dtype=torch.uint8, device="cuda")
     ws = t.levelwise_workspace(len(q)) if levelwise else None
+    torch.cuda.synchronize()  # the inputs are there before another stream reads them
     s = torch.cuda.Stream()
 
     def call():

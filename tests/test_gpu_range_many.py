@@ -40,6 +40,7 @@ def test_many_short_scans_of_32_bit_keys():
         hi, mx = torch.full_like(lo, -1), torch.ones(B, dtype=torch.int32, device="cuda")
         off = torch.arange(B, device="cuda")
         ok, ov, cnt = torch.empty_like(lo), torch.empty_like(lo), torch.empty_like(mx)
+        torch.cuda.synchronize()  # the inputs are there before another stream reads them
         s = torch.cuda.Stream()
         with torch.cuda.stream(s):
             g.tree_range_batch(t.h, lo, hi, mx, off, ok, ov, cnt)

@@ -83,6 +83,7 @@ def test_repeated_keys_take_no_longer(width):
     us = {}
     for kind in ("hundred", "all"):
         q = t.dev(keys[:B] if kind == "all" else batch(kind, keys, B, 1))
+        torch.cuda.synchronize()  # the inputs are there before another stream reads them
         s = torch.cuda.Stream()
         with torch.cuda.stream(s):
             g.tree_lookup_levelwise(t.h, q, 0, v, f, ws)
