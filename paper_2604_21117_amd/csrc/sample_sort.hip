@@ -691,10 +691,12 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(const K* __restrict__
 // every wave that has one of them.  Above kSsBinMax the merge is cheaper.
 constexpr uint32_t kSsBinOwn = 8, kSsBinMax = 256;
 // With TIE a group with a bin of more than kSsBinSpread pairs is dealt again,
-// up to kSsSpreads times (ss_spread).  At 32 pairs 2^15 Zipf keys took 54 us
-// for 50 at 64, few keys the same.  Without TIE equal keys end the sort, and
-// the code would cost the group kernel a wave of its four per SIMD.
-constexpr uint32_t kSsBinSpread = 64;
+// up to kSsSpreads times (ss_spread).  Level-wise lookups of 32-bit keys, at
+// 64, 32 and 16 pairs: 2^18 in runs of consecutive keys 74, 66 and 68 us (70
+// with the radix sort), 2^20 146, 125 and 130 (127), clustered 144, 138 and
+// 124 (127), Zipf 134, 134 and 138-142 (127).  Without TIE equal keys end the
+// sort, and the code would cost the group kernel a wave of its four per SIMD.
+constexpr uint32_t kSsBinSpread = 32;
 constexpr int kSsSpreads = 3;
 
 // The keys of a bin and the positions of its pairs: smallest and largest.

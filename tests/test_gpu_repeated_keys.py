@@ -32,6 +32,10 @@ def batch(kind, keys, B, seed):
         q[rng.random(B) < 0.5] = keys[3]
     elif kind == "sorted_hundred":
         q = np.sort(keys[rng.integers(0, 100, B)])
+    elif kind == "runs":  # runs of consecutive keys, far apart
+        q = keys[rng.integers(0, len(keys), B // 64 + 1)].repeat(64)[:B] + np.arange(B, dtype=keys.dtype) % 64
+    elif kind == "uneven_runs":  # a few large bins among small ones
+        q[::3] = keys[5] + (np.arange(len(q[::3])) % 40).astype(keys.dtype)
     return q
 
 
@@ -42,7 +46,7 @@ def test_repeated_keys_sort_right(width, B):
     vals = synth.values_for(keys, 3, width)
     sa = oracle.SortedArray(keys, vals, width)
     t = mk_tree(keys, vals, width // 8)
-    for i, kind in enumerate(("one", "two", "hundred", "zipf", "bursts", "half", "sorted_hundred")):
+    for i, kind in enumerate(("one", "two", "hundred", "zipf", "bursts", "half", "sorted_hundred", "runs", "uneven_runs")):
         q = batch(kind, keys, B, B + i)
         gv, gf = t.lookup_levelwise(q)
         ov, of = sa.lookup(q)
