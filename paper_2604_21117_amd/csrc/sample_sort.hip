@@ -31,11 +31,12 @@
 // Above 2^20 pairs a first scatter into 256 segments comes before, and the
 // steps above run per segment.
 //
-// Measured on 2^20 (64-bit key, position) pairs, us: sample 10 and rank 11
-// (latency of a few workgroups), count 15, scatter 20, groups 21; 2^24 (key,
-// value) pairs of a bulk load: two counts of 38, two scatters of 138 (512 MiB
-// moved, 3.9 TB/s where a copy reaches 5.1), groups into leaves 182 (512 MiB,
-// 2.9 TB/s; about 300 vector instructions per 64 pairs are its other bound).
+// Measured on 2^20 (64-bit key, position) pairs, us: sample 11 and rank 11
+// (latency of a few workgroups), count 15, scatter 21, groups 17 and 5; 2^24
+// (key, value) pairs of a bulk load: two counts of 39, two scatters of 140
+// (512 MiB moved, 3.8 TB/s where a copy reaches 5.1), groups into leaves 193
+// (512 MiB, 2.8 TB/s; about 300 vector instructions per 64 pairs are its other
+// bound).
 //
 // No step waits on another workgroup.  A scatter that finds more pairs for a
 // group than were counted (the input changed, which no caller may do) writes
@@ -691,12 +692,13 @@ __global__ __launch_bounds__(kSsThreads) void k_ss_scatter(const K* __restrict__
 // every wave that has one of them.  Above kSsBinMax the merge is cheaper.
 constexpr uint32_t kSsBinOwn = 8, kSsBinMax = 256;
 // With TIE a group with a bin of more than kSsBinSpread pairs is dealt again,
-// up to kSsSpreads times (ss_spread).  Level-wise lookups of 32-bit keys, at
-// 64, 32 and 16 pairs: 2^18 in runs of consecutive keys 74, 66 and 68 us (70
-// with the radix sort), 2^20 146, 125 and 130 (127), clustered 144, 138 and
-// 124 (127), Zipf 134, 134 and 138-142 (127).  Without TIE equal keys end the
-// sort, and the code would cost the group kernel a wave of its four per SIMD.
-constexpr uint32_t kSsBinSpread = 32;
+// up to kSsSpreads times (ss_spread).  Level-wise lookups of 2^20 32-bit keys,
+// us, at 64, 32, 24 and 16 pairs (the radix sort before): runs of consecutive
+// keys 146, 127, 126, 130 (127), clustered 144, 141, 129, 122 (128), Zipf 134,
+// 133, 135, 142 (127), 100 different keys 128, 129, 129, 134 (124).  Without
+// TIE equal keys end the sort, and the code would cost the group kernel a wave
+// of its four per SIMD.
+constexpr uint32_t kSsBinSpread = 24;
 constexpr int kSsSpreads = 3;
 
 // The keys of a bin and the positions of its pairs: smallest and largest.
@@ -825,8 +827,8 @@ __device__ __forceinline__ void lds_max(K* a, K x) {
 // groups, in which only the positions differ).  bin holds starts before and
 // counts after, bn and f a pair's bin and its place there.  Without this such
 // groups were merge-sorted, ten rounds and more: the level-wise lookup of 2^20
-// u32 keys of which 100 differ 193 us, now 136, of Zipf ones 204 and 152 (140
-// where all differ); of 2^15 75 and 45, 76 and 48 (38).
+// u32 keys of which 100 differ 239 us, now 129, of Zipf ones 190 and 135 (120
+// where all differ); of 2^15 69 and 39, 70 and 43 (33).
 template <class K, int NT, uint32_t CAP>
 __device__ __forceinline__ void ss_spread(SsLds<K, true, NT, CAP>& L, uint32_t m, uint32_t nb, const K (&k)[CAP / NT],
                                           const uint32_t (&p)[CAP / NT], uint32_t (&bn)[CAP / NT],
