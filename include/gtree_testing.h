@@ -16,13 +16,13 @@ extern "C" {
 
 /*
  * Testing hook for the failure path of the device sorts (inputs above
- * 2048 keys: tree_build, tree_insert_batch, tree_delete_batch,
+ * 8192 keys: tree_build, tree_insert_batch, tree_delete_batch,
  * tree_lookup_levelwise).  The radix sort's workgroups wait on the published
  * counts of earlier ones; `limit` is how many look-back steps that find
  * nothing new one takes before it gives up (default 1 << 20, never reached in
  * practice).  0 makes every workgroup but the first of a pass give up at once,
  * and the sample sort (which waits on nothing) report a failure, so any sort of
- * more than 4096 keys fails.  A failed sort reports GT_ERR_DEVICE from
+ * more than 8192 keys fails.  A failed sort reports GT_ERR_DEVICE from
  * tree_build; in an insert, delete or level-wise lookup it sets
  * GT_DEVERR_INTERNAL in the tree's error word, an insert or delete batch is
  * refused with the tree unchanged, and the lookup's outputs are

@@ -300,7 +300,7 @@ def tree_device_error(h, stream=None) -> int:
 
 def set_sort_spin_limit(limit: int) -> int:
     """Testing hook: the device sort's look-back limit (0 makes every sort
-    of more than 4096 keys fail); returns the previous value."""
+    of more than 8192 keys fail); returns the previous value."""
     return int(lib().gt_set_sort_spin_limit(limit))
 
 

@@ -1154,7 +1154,7 @@ gt_status wide_export(const WideTree* w, void* host_buf, uint64_t* bytes, hipStr
             memcpy(o, lk.data() + i * m * kb, C * kb);
             memcpy(o + C * kb, lvv.data() + i * m, C * 8);
         } else {
-            // leading word and record back to key bytes (big-endian words)
+            // deciding word and record back to key bytes (big-endian words)
             const uint8_t* lb = lk.data() + i * m * kLeafEntry32;
             for (uint64_t j = 0; j < C; ++j) {
                 uint64_t x[5];
